@@ -788,14 +788,19 @@ lola_status lola_state_init(const lola_config *c, const lola_state *st, void *st
     void *ptrs[14] = {st->H, st->s, st->win_k, st->win_v, st->sp_k, st->sp_v, st->sp_idx, st->sp_count, st->n_tokens,
                       c->fold_defer ? st->pend_phi : nullptr, c->fold_defer ? st->pend_v : nullptr,
                       c->fold_defer ? st->pend_count : nullptr, sk ? st->win_score : nullptr, sk ? st->sp_score : nullptr};
+    static_assert(generic::FILL_FIELDS == 14, "one fill per field");
+    generic::FillArgs fa;
+    fa.fields = 0;
+    uint32_t blocks = 0;
     for (int i = 0; i < 14; i++) {
         if (!ptrs[i] || fb[i] == 0) continue;
-        size_t n = fb[i] / 4;   // every field is a multiple of 4 bytes (head_dim is even)
-        unsigned blocks = (unsigned)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-        hipLaunchKernelGGL(generic::fill_u32_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream,
-                           (uint32_t *)ptrs[i], n, i == 6 ? 0xFFFFFFFFu : 0u);
-        LAUNCH_CHECK();
+        const size_t n = fb[i] / 4;   // every field is a multiple of 4 bytes (head_dim is even)
+        blocks += (uint32_t)((n + generic::FILL_WORDS - 1) / generic::FILL_WORDS);
+        fa.p[fa.fields] = (uint32_t *)ptrs[i]; fa.n[fa.fields] = n;
+        fa.val[fa.fields] = i == 6 ? 0xFFFFFFFFu : 0u; fa.end[fa.fields++] = blocks;
     }
+    hipLaunchKernelGGL(generic::fill_fields_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, fa);
+    LAUNCH_CHECK();
     return LOLA_OK;
 }
 
