@@ -610,7 +610,38 @@ struct PrefillArgs {
     int32_t *next_j;          // [B*Hkv] hand-over of the chunk position between the kernels of a pass
     float *tok_score;         // [B*Hkv][eta + T] query-dependent scores: entry window (virtual rows lam ..), then the call's tokens
     int R2;                   // keys / queries per tile of band_score_kernel
+    int32_t *spc_in;          // [B*Hkv] pairs in the sparse cache at the call's entry
+    int fill_closed;          // 1: prefix_kernel does the call's filling chunks (below), the state-evolution kernels start at the first
+                              // scored chunk; 0: the shape-generic evolution does every chunk
 };
+
+// While the eligible pairs number at most lambda nothing is scored and H, s stay as they are, so the filling chunks of a
+// call have a closed form: pair i that leaves the window (counted from the call's entry) is token L0 + i, L0 = max(0,
+// a0 - eta), sits in virtual row P + L0 - a0 + i and takes slot spc_in + i.  The copies are made by prefix_kernel, a
+// filling chunk's cache rows are computed where its outputs are, and all filling chunks share the entry's snapshot of H
+// and s.  Evolved chunk by chunk on the shape-generic kernel, each snapshot written anew, a filling chunk took 9 - 12 us and
+// a ragged last one (which the MFMA kernels now do as well) 45 - 150 us; a request (8B shape) of 8 x 333 tokens 313 -> 138 us,
+// of 16 x 1513 tokens in two calls 1.21 -> 0.86 ms, of 4 x 2048 at eta = lambda = 256 1.18 -> 1.08 ms.
+// pairs that have left the window, counted from the call's entry, once `tok` of its tokens have joined it
+template <typename T>
+__device__ __forceinline__ int left_after(const PrefillArgs<T> &a, int64_t a0, int tok) {
+    const int64_t eta = a.dm.eta;
+    return (int)(max((int64_t)0, a0 + tok - eta) - max((int64_t)0, a0 - eta));
+}
+// the first chunk of the call that is scored (n_chunks if there is none)
+template <typename T>
+__device__ __forceinline__ int first_scored_chunk(const PrefillArgs<T> &a, int64_t a0, int spc_in) {
+    // scored as soon as spc_in + left_after(tok) > lambda, i.e. from this many tokens on
+    const int64_t tok = (int64_t)a.dm.lam - spc_in + max((int64_t)0, a.dm.eta - a0) + 1;
+    return tok > a.T_tokens ? a.n_chunks : (int)((tok - 1) / a.dm.C);
+}
+// virtual row of cache slot sl at the entry of filling chunk j (-1: empty)
+template <typename T>
+__device__ __forceinline__ int fill_row(const PrefillArgs<T> &a, int64_t a0, int spc_in, int j, int sl) {
+    if (sl < spc_in) return sl;
+    if (sl - spc_in >= left_after(a, a0, j * a.dm.C)) return -1;
+    return a.dm.lam + a.dm.eta - (int)min(a0, (int64_t)a.dm.eta) + (sl - spc_in);
+}
 
 // grid (stream, part): the parts of a stream share its rows evenly
 template <typename T>
@@ -626,8 +657,9 @@ __global__ __launch_bounds__(NT) void prefix_kernel(PrefillArgs<T> a) {
     const int ppr = d * (int)sizeof(T) / 16;
     const uint4 *sk4 = reinterpret_cast<const uint4 *>(sp_k), *sv4 = reinterpret_cast<const uint4 *>(sp_v);
     uint4 *pK4 = reinterpret_cast<uint4 *>(pK), *pV4 = reinterpret_cast<uint4 *>(pV);
-    for (int p = tid; p < lam * ppr; p += nth) { pK4[p] = sk4[p]; pV4[p] = sv4[p]; }
-    for (int s = tid; s < lam; s += nth) a.sp_row[(size_t)si * lam + s] = s;
+    const int spc = a.fill_closed ? a.st.sp_count[si] : lam;
+    for (int p = tid; p < spc * ppr; p += nth) { pK4[p] = sk4[p]; pV4[p] = sv4[p]; }
+    for (int s = tid; s < spc; s += nth) a.sp_row[(size_t)si * lam + s] = s;
     const int nw = (int)min((int64_t)eta, a0);
     const uint4 *wk4 = reinterpret_cast<const uint4 *>(win_k), *wv4 = reinterpret_cast<const uint4 *>(win_v);
     for (int p = tid; p < nw * ppr; p += nth) {
@@ -636,6 +668,37 @@ __global__ __launch_bounds__(NT) void prefix_kernel(PrefillArgs<T> a) {
         size_t row = (size_t)(P - back);
         pK4[row * ppr + i] = wk4[(size_t)slot * ppr + i];
         pV4[row * ppr + i] = wv4[(size_t)slot * ppr + i];
+    }
+    if (a.fill_closed) {
+        // the filling chunks: the pairs they move from the window (of the entry, or tokens of the call) into free slots
+        const int js = first_scored_chunk(a, a0, spc);
+        const int nfill = left_after(a, a0, (int)min((int64_t)a.T_tokens, (int64_t)js * dm.C));
+        const int64_t L0 = max((int64_t)0, a0 - eta);
+        uint4 *dk4 = reinterpret_cast<uint4 *>(a.st.sp_k + ((size_t)si * lam + spc) * d), *dv4 = reinterpret_cast<uint4 *>(a.st.sp_v + ((size_t)si * lam + spc) * d);
+        const uint4 *kc4 = reinterpret_cast<const uint4 *>(a.k + (size_t)si * a.T_tokens * d), *vc4 = reinterpret_cast<const uint4 *>(a.v + (size_t)si * a.T_tokens * d);
+        for (int p = tid; p < nfill * ppr; p += nth) {
+            const int64_t t = L0 + p / ppr;
+            const int i = p % ppr;
+            const bool old = t < a0;
+            const size_t row = old ? (size_t)(t % eta) : (size_t)(t - a0);
+            dk4[p] = (old ? wk4 : kc4)[row * ppr + i];
+            dv4[p] = (old ? wv4 : vc4)[row * ppr + i];
+        }
+        int32_t *sp_idx = a.st.sp_idx + (size_t)si * lam, *sp_row = a.sp_row + (size_t)si * lam;
+        for (int s = spc + tid; s < lam; s += nth) {
+            const bool in = s - spc < nfill;
+            if (in) sp_idx[s] = (int32_t)(L0 + (s - spc));
+            sp_row[s] = in ? (int)(lam + eta + L0 - a0) + (s - spc) : -1;
+        }
+        if (a.sel_trace) {
+            int32_t *tr = a.sel_trace + (size_t)si * a.n_chunks * lam;
+            for (int p = tid; p < js * lam; p += nth) {
+                const int j = p / lam, s = p - j * lam;
+                const int held = spc + left_after(a, a0, min(a.T_tokens, (j + 1) * dm.C));
+                tr[p] = s < spc ? sp_idx[s] : (s < held ? (int32_t)(L0 + (s - spc)) : -1);
+            }
+        }
+        if (tid == 0) { a.spc_in[si] = spc; a.next_j[si] = js; }
     }
 }
 
@@ -665,7 +728,10 @@ __global__ __launch_bounds__(NT) void finalize_kernel(PrefillArgs<T> a) {
         for (int64_t t = t_lo + tid; t < a0 + Tn; t += NT) win_score[t % eta] = ts[eta + (t - a0)];
     }
     __syncthreads();
-    if (tid == 0) a.st.n_tokens[si] = a0 + Tn;
+    if (tid == 0) {
+        if (a.fill_closed) a.st.sp_count[si] = min(dm.lam, a.spc_in[si] + left_after(a, a0, Tn));
+        a.st.n_tokens[si] = a0 + Tn;
+    }
 }
 
 // Query-dependent scores of a prefill call (Sec. 4 / appendix "scoring ablation"): row x of tok_score belongs to token

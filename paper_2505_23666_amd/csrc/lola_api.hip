@@ -214,7 +214,7 @@ bool wide_scan_ok(const lola_config *c) {
 }
 
 struct PrefillPlan {
-    size_t off_prefK, off_prefV, off_sp_row, off_phiE, off_next, off_score, off_snap;   // byte offsets
+    size_t off_prefK, off_prefV, off_sp_row, off_phiE, off_next, off_spc, off_score, off_snap;   // byte offsets
     size_t snap_bytes_per_chunk;                                    // all streams, one chunk (snapshots + phi of its keys)
     size_t phik_bytes_per_chunk;
     size_t fixed_bytes;
@@ -229,6 +229,7 @@ PrefillPlan plan_prefill(const lola_config *c, int with_outputs, size_t Tn) {
     p.off_sp_row = off; off += up(ns * lam * 4);
     p.off_phiE = off; off += up(ns * (lam + c->chunk) * D * 4);
     p.off_next = off; off += up(ns * 4);
+    p.off_spc = off; off += up(ns * 4);
     p.off_score = off; if (c->score_kind != LOLA_SCORE_SRE) off += up(ns * ((size_t)c->window + Tn) * 4);
     p.off_snap = off;
     p.fixed_bytes = off;
@@ -386,9 +387,7 @@ struct SideStream {
 constexpr int SCAN_RT128 = LOLA_SCAN_RT128;   // row tiles of H^T per wavefront in the MFMA scan at head_dim 128
 constexpr int CHIP_CUS = 256;                 // compute units of the MI355X
 constexpr size_t OVERLAP_MAX_STREAMS = 128;   // beyond this many streams the serial evolution fills the chip by itself
-constexpr int OVERLAP_MIN_PIECE = 8;          // chunks per piece on average at least.  The first piece, at least half of the
-                                              // pass and so at least 8 chunks, is longer than the (256 + 64) / 64 chunks
-                                              // after which the sparse cache of the MFMA shapes is full
+constexpr int OVERLAP_MIN_PIECE = 8;          // chunks per piece on average at least
 constexpr size_t OVERLAP_MIN_WORK = 4096;     // output workgroups (in units of 64 head columns) per piece at least: below
                                               // this the restart of the evolution costs more than the overlap hides
 
@@ -485,6 +484,7 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
     a.sp_row = (int32_t *)(ws + p.off_sp_row);
     a.phiE = (float *)(ws + p.off_phiE);
     a.next_j = (int32_t *)(ws + p.off_next);
+    a.spc_in = (int32_t *)(ws + p.off_spc);
     a.scan_mode = 0;
     int S = a.n_chunks > 0 ? a.n_chunks : 1;
     if (p.snap_bytes_per_chunk > 0) {
@@ -511,6 +511,9 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
     const bool fast_att = a.want_out && fast_output_ok(c);
     const bool wide_att = a.want_out && !fast_att && wide_output_ok(c);
     a.snap_split = (fast_att || wide_att) ? 1 : 0;
+    // The MFMA evolution kernels do every scored chunk, a ragged last one included; what comes before the first of them has
+    // a closed form (generic_kernels.h, first_scored_chunk).
+    a.fill_closed = std::is_same<T, bf16_t>::value && (wide_scan_ok(c) || (fast_attend_ok(c) && lam > 0)) ? 1 : 0;
     if (a.R <= 0 || (a.want_out && a.QT <= 0)) return LOLA_ERR_UNSUPPORTED;
     const size_t lds_scan = 4 * (scan_fixed + (size_t)a.R * (3 * d + D + 1));
     const size_t lds_att = 4 * ((size_t)a.QT * (d + D + (lam + a.dm.eta + a.dm.C) + 3));
@@ -583,12 +586,9 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
             }
             const bool wide = wide_scan_ok(c);   // (run-time window / budget kernels; else the compile-time shapes)
             if (wide || fast_attend_ok(c)) {
-                // The serial evolution in legs that hand the chunk position over in next_j: generic kernel until the first
-                // regular chunk (a full chunk with a full window behind it and a full cache), MFMA kernel over the regular
-                // chunks, generic kernel for what is left (a ragged last chunk); phi of the keys chunk-parallel
-                // beforehand: at the compile-time shapes of every key of the pass, at the run-time shapes (per piece,
-                // behind the generic leg) of the pairs that leave the window in each chunk and of the cache slots as
-                // they stand.
+                // The serial evolution over the scored chunks of the pass; phi of the keys chunk-parallel beforehand: at the
+                // compile-time shapes of every key of the pass, at the run-time shapes (per piece) of the pairs that leave
+                // the window in each chunk and of the cache slots as they stand.
                 // (a compile-time shape whose cache does not stay in LDS takes its features the run-time way)
                 const bool big = !wide && c->sparse_budget > 128;
                 if (!wide && !big) {
@@ -655,15 +655,6 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                     const int p0 = bnd[ip];
                     a.j0 = p0;
                     a.j1 = bnd[ip + 1];
-                    // At the compile-time shapes later pieces start on regular chunks (the first piece is longer than the
-                    // (lambda + eta) / C chunks after which the cache is full); with a long window and a large budget a
-                    // piece may still begin while they fill, so the run-time shapes run the generic leg in every piece (it
-                    // returns at once on a regular chunk).
-                    if (ip == 0 || wide) {
-                        a.scan_mode = 1;
-                        hipLaunchKernelGGL((generic::scan_kernel<T>), gs, block, lds_scan, stream, a);
-                        LAUNCH_CHECK();
-                    }
                     // The previous piece's outputs may start once the evolution kernel of this piece is next in line (the
                     // event) and are enqueued after its launch: the evolution's workgroups, which need a compute unit's whole
                     // register file, should be resident before the output workgroups arrive, instead of queueing for
@@ -692,12 +683,6 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                     }
                     LAUNCH_CHECK();
                     if (side && ip > 0 && !attend_aside(ip - 1, prev0, p0)) return LOLA_ERR_HIP;
-                    if (a.j1 == a.n_chunks && Tn % a.dm.C != 0) {   // only a ragged last chunk is left to the generic kernel
-                        a.scan_mode = 2;
-                        hipLaunchKernelGGL((generic::scan_kernel<T>), gs, block, lds_scan, stream, a);
-                        LAUNCH_CHECK();
-                    }
-                    a.scan_mode = 0;
                     if (a.want_out && !side) {
                         attend(stream, a.j0, a.j1);
                         LAUNCH_CHECK();

@@ -53,8 +53,12 @@ __global__ __launch_bounds__(256, 2) void attend_fast_kernel(generic::PrefillArg
     const int cl = min(C, Tn - j * C);              // queries in this chunk
     const int64_t aj = a0 + (int64_t)j * C;         // token index of the chunk's first query
     const size_t sj = (size_t)si * a.S + jj;
-    const uint16_t *Hsnap = reinterpret_cast<const uint16_t *>(a.snapH) + sj * (2 * DH * D);
-    const float *ssnap = a.snapS + sj * D;
+    // filling chunks share one snapshot of H and s, that of the launch's first chunk, and have their rows in closed form
+    const int spc_in = a.fill_closed ? a.spc_in[si] : 0;
+    const bool filling = a.fill_closed && j < generic::first_scored_chunk(a, a0, spc_in);
+    const size_t sh = filling ? (size_t)si * a.S + (a.j0 - a.jb) : sj;
+    const uint16_t *Hsnap = reinterpret_cast<const uint16_t *>(a.snapH) + sh * (2 * DH * D);
+    const float *ssnap = a.snapS + sh * D;
     const int32_t *Gsnap = a.snapG + sj * LAM;
     const bf16_t *pK = a.prefK + (size_t)si * P * DH, *pV = a.prefV + (size_t)si * P * DH;
     const bf16_t *kc = a.k + (size_t)si * Tn * DH, *vc = a.v + (size_t)si * Tn * DH;
@@ -72,7 +76,7 @@ __global__ __launch_bounds__(256, 2) void attend_fast_kernel(generic::PrefillArg
     for (int ks = 0; ks < KS; ks++) BQ[ks] = ld_bf16x8(qh + (size_t)(qi < cl ? qi : 0) * DH + 32 * ks + 8 * g4);
     if (tid < D / 4) reinterpret_cast<float4 *>(s_l)[tid] = reinterpret_cast<const float4 *>(ssnap)[tid];
     bool gneg = false;
-    for (int x = tid; x < LAM; x += 256) { const int gr = Gsnap[x]; G_l[x] = gr; gneg |= gr < 0; }
+    for (int x = tid; x < LAM; x += 256) { const int gr = filling ? generic::fill_row(a, a0, spc_in, j, x) : Gsnap[x]; G_l[x] = gr; gneg |= gr < 0; }
     if (lane == 0) gneg_l[w] = 0;
     if (gneg) gneg_l[w] = 1;   // (after the store of 0 in program order; lanes of one wavefront, same value)
     lds_barrier();
@@ -302,8 +306,12 @@ __global__ __launch_bounds__(256, 2) void attend_wide_kernel(generic::PrefillArg
     const int cl = min(C, Tn - j * C);              // queries in this chunk
     const int64_t aj = a0 + (int64_t)j * C;         // token index of the chunk's first query
     const size_t sj = (size_t)si * a.S + jj;
-    const uint16_t *Hsnap = reinterpret_cast<const uint16_t *>(a.snapH) + sj * (2 * DH * DF);
-    const float *ssnap = a.snapS + sj * DF;
+    // filling chunks share one snapshot of H and s, that of the launch's first chunk, and have their rows in closed form
+    const int spc_in = a.fill_closed ? a.spc_in[si] : 0;
+    const bool filling = a.fill_closed && j < generic::first_scored_chunk(a, a0, spc_in);
+    const size_t sh = filling ? (size_t)si * a.S + (a.j0 - a.jb) : sj;
+    const uint16_t *Hsnap = reinterpret_cast<const uint16_t *>(a.snapH) + sh * (2 * DH * DF);
+    const float *ssnap = a.snapS + sh * DF;
     const int32_t *Gsnap = a.snapG + sj * LAM;
     const bf16_t *pK = a.prefK + (size_t)si * P * DH, *pV = a.prefV + (size_t)si * P * DH;
     const bf16_t *kc = a.k + (size_t)si * Tn * DH, *vc = a.v + (size_t)si * Tn * DH;
@@ -319,7 +327,7 @@ __global__ __launch_bounds__(256, 2) void attend_wide_kernel(generic::PrefillArg
     for (int ks = 0; ks < KS; ks++) BQ[ks] = ld_bf16x8(qh + (size_t)(qi < cl ? qi : 0) * DH + 32 * ks + 8 * g4);
     for (int x = tid; x < DF / 4; x += 256) reinterpret_cast<float4 *>(s_l)[x] = reinterpret_cast<const float4 *>(ssnap)[x];
     bool gneg = false;
-    for (int x = tid; x < LAM; x += 256) { const int gr = Gsnap[x]; G_l[x] = gr; gneg |= gr < 0; }
+    for (int x = tid; x < LAM; x += 256) { const int gr = filling ? generic::fill_row(a, a0, spc_in, j, x) : Gsnap[x]; G_l[x] = gr; gneg |= gr < 0; }
     if (lane == 0) gneg_l[w] = 0;
     if (gneg) gneg_l[w] = 1;   // (after the store of 0 in program order; lanes of one wavefront, same value)
     __syncthreads();
@@ -640,8 +648,9 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
     const bf16_t *pK = a.prefK + (size_t)si * P * DH, *pV = a.prefV + (size_t)si * P * DH;
     const bf16_t *kc = a.k + (size_t)si * a.T_tokens * DH, *vc = a.v + (size_t)si * a.T_tokens * DH;
     const int64_t a0 = a.st.n_tokens[si];
-    const int spc = a.st.sp_count[si];
-    int j = a.next_j[si];
+    const int spc0 = a.spc_in[si];
+    int j = a.next_j[si];                    // the first chunk that is scored, or where the launch before this one stopped
+    const bool fill_snap = a.want_out && a.j0 < generic::first_scored_chunk(a, a0, spc0);   // filling chunks: one snapshot for all
 
     // H^T row 16 (RT w + rt) + r16, features 32ks + 16hf + 4g4 + 0..3 (the names of row tile 1 stay unused when RT = 1)
 #define LOLA_SREP1(X, rt) X(rt, 0, 0) X(rt, 0, 1) X(rt, 1, 0) X(rt, 1, 1) X(rt, 2, 0) X(rt, 2, 1) X(rt, 3, 0) X(rt, 3, 1)
@@ -651,7 +660,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
 #define LOLA_SLOAD(rt, ks, hf) if (rt < RT) hreg##rt##ks##hf = *reinterpret_cast<const f32x4 *>(Hg + LOLA_SADDR(rt, ks, hf));
 #define LOLA_SSTORE(rt, ks, hf) if (rt < RT) *reinterpret_cast<f32x4 *>(Hg + LOLA_SADDR(rt, ks, hf)) = hreg##rt##ks##hf;
     LOLA_SREP(LOLA_SDECL)
-    bool started = false;
+    const bool started = j < a.j1;
     bool idx_valid = false;     // rows [0, LAM) of cidx hold the cache slots' token indices
     if (tid0 == 0) thr_s = 0;   // published by the barrier that follows the loading of the state
     bool phi_valid = false;     // PERSIST: rows [0, LAM) of PB hold phi of the cache slots, and PHn / vvn the rows requested ahead
@@ -668,19 +677,38 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
 #pragma unroll
     for (int x = 0; x < PHN; x++) PHn[x] = make_uint4(0, 0, 0, 0);
 
+    if (started || fill_snap) {
+        LOLA_SREP(LOLA_SLOAD)
+        if (tid0 < D) s_l[tid0] = sg[tid0];
+        // The state is waited for here, once: left to the first use, the wait would stand in the loop body behind the
+        // chunk's own requests (the counter is in order) and hold every chunk until half of those had arrived.
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+        __syncthreads();
+    }
+    // the snapshot's pieces of row tile rt, k-step ks (bf16 high + low parts): one contiguous 1 KB piece per store
+#define LOLA_SSNAP(rt, ks) if (rt < RT) { float sv[8]; \
+        _Pragma("unroll") for (int x = 0; x < 4; x++) { sv[x] = hreg##rt##ks##0[x]; sv[4 + x] = hreg##rt##ks##1[x]; } \
+        bf16x8 hi8, lo8; split8(sv, hi8, lo8); \
+        const int off = (((RT * w + rt) * 4 + ks) * 64 + lane) << 3; \
+        *reinterpret_cast<uint4 *>(s16 + off) = __builtin_bit_cast(uint4, hi8); \
+        *reinterpret_cast<uint4 *>(s16 + D * DH + off) = __builtin_bit_cast(uint4, lo8); }
+#define LOLA_SSNAP_ALL LOLA_SSNAP(0, 0) LOLA_SSNAP(0, 1) LOLA_SSNAP(0, 2) LOLA_SSNAP(0, 3) \
+                       LOLA_SSNAP(1, 0) LOLA_SSNAP(1, 1) LOLA_SSNAP(1, 2) LOLA_SSNAP(1, 3)
+    if (fill_snap) {
+        const int w = w0, lane = tid0 & 63;
+        const size_t sj = (size_t)si * a.S + (a.j0 - a.jb);
+        uint16_t *s16 = reinterpret_cast<uint16_t *>(a.snapH) + sj * (2 * D * DH);
+        LOLA_SSNAP_ALL
+        if (tid0 < D) a.snapS[sj * D + tid0] = s_l[tid0];
+    }
+
     for (; j < a.j1; j++) {
+        // A scored chunk has a full window behind it.  Its candidates: the cache slots [0, spc), and the first cl of the 64
+        // rows before the chunk, which leave the window (cl < 64: a ragged last chunk); nf of them are folded.  The
+        // positions of missing candidates are computed along and kept out of the selection by a score above all others.
         const int cl = min(C, a.T_tokens - j * C);
         const int64_t aj = a0 + (int64_t)j * C;
-        if (!(cl == C && aj >= ETA && spc == LAM)) break;   // not a regular chunk: the generic kernel takes over
-        if (!started) {
-            LOLA_SREP(LOLA_SLOAD)
-            if (tid0 < D) s_l[tid0] = sg[tid0];
-            started = true;
-            // The state is waited for here, once: left to the first use, the wait would stand in the loop body behind the
-            // chunk's own requests (the counter is in order) and hold every chunk until half of those had arrived.
-            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-            __syncthreads();
-        }
+        const int spc = min(LAM, spc0 + generic::left_after(a, a0, j * C)), nf = spc + cl - LAM;
         // The lane coordinates are made opaque once per chunk: everything derived from them (LDS and global
         // addresses of every phase) is then recomputed inside the loop instead of being hoisted out of it as
         // hundreds of loop-invariant registers, which the register file cannot hold next to H^T.
@@ -969,7 +997,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
             // recall GEMM (it waits for the other wavefront of its SIMD anyway), by the others while wavefront 0 runs the
             // selection.  Issued by all wavefronts ahead of the recall GEMM they cost 1.3 us per chunk.
             if (w == 0 && t0 + TB >= NTILE) {
-                if (PERSIST) {   // this chunk's own pairs leave the window in the next chunk
+                if (PERSIST && cl == C) {   // this chunk's own pairs leave the window in the next chunk
                     const uint4 *ph = reinterpret_cast<const uint4 *>(a.phiK + ((size_t)si * a.S + (j - a.jb)) * C * 2 * D);
 #pragma unroll
                     for (int it = 0; it < PHN; it++) PHn[it] = ph[tid + NTH * it];
@@ -996,7 +1024,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
         }
         }
 
-        // ---- 3. selection: the 64 candidates with the smallest squared error are folded (order: score descending,
+        // ---- 3. selection: the nf candidates with the smallest squared error are folded (order: score descending,
         // token index ascending, the first LAM stay).  The squared error is |P|^2 / (phi.s)^2 - 2 P.v / (phi.s) + |v|^2
         // (recall = 0 while phi.s = 0, i.e. nothing folded yet); the bit pattern of a float >= 0 orders like an integer.
         for (int e = tid; e < NE; e += NTH) {
@@ -1005,16 +1033,16 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
 #pragma unroll
             for (int x = 0; x < NW; x++) { sa += part[0][x][e]; sb += part[1][x][e]; sc += part[2][x][e]; }
             const float sq = fmaxf(fmaf(rd * rd, sa, fmaf(-2.0f * rd, sb, sc)), 0.f);
-            skey[e] = __float_as_uint(sq) & 0x7FFFFFFFu;
+            skey[e] = (e < LAM ? e < spc : e < LAM + cl) ? __float_as_uint(sq) & 0x7FFFFFFFu : 0xFFFFFFFFu;
         }
         lds_barrier();
-        // One wavefront holds all scores (NK per lane) and finds the 64th smallest by building it bit by bit: a trial
-        // value is kept when fewer than 64 scores lie below it (votes counted on the scalar unit).  Scores equal to
+        // One wavefront holds all scores (NK per lane) and finds the nf-th smallest by building it bit by bit: a trial
+        // value is kept when fewer than nf scores lie below it (votes counted on the scalar unit).  Scores equal to
         // the threshold are folded too if that makes exactly 64; otherwise (exact ties across the cut) the same search
         // over their token indices picks the largest ones.  The lists follow from the fold predicate by ballots:
         // candidates to fold; entrants paired with the slots of the leavers.
         if (w != 0) {   // the requests wavefront 0 issued before the recall GEMM (H^T is still the chunk's entry state)
-            if (PERSIST) {
+            if (PERSIST && cl == C) {
                 const uint4 *ph = reinterpret_cast<const uint4 *>(a.phiK + ((size_t)si * a.S + (j - a.jb)) * C * 2 * D);
 #pragma unroll
                 for (int it = 0; it < PHN; it++) PHn[it] = ph[tid + NTH * it];
@@ -1026,25 +1054,17 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
             }
             if (a.want_out) {
                 uint16_t *s16 = reinterpret_cast<uint16_t *>(a.snapH) + ((size_t)si * a.S + (j - a.jb)) * (2 * D * DH);
-#define LOLA_SSNAP(rt, ks) if (rt < RT) { float sv[8]; \
-                _Pragma("unroll") for (int x = 0; x < 4; x++) { sv[x] = hreg##rt##ks##0[x]; sv[4 + x] = hreg##rt##ks##1[x]; } \
-                bf16x8 hi8, lo8; split8(sv, hi8, lo8); \
-                const int off = (((RT * w + rt) * 4 + ks) * 64 + lane) << 3; \
-                *reinterpret_cast<uint4 *>(s16 + off) = __builtin_bit_cast(uint4, hi8); \
-                *reinterpret_cast<uint4 *>(s16 + D * DH + off) = __builtin_bit_cast(uint4, lo8); }
-                LOLA_SSNAP(0, 0) LOLA_SSNAP(0, 1) LOLA_SSNAP(0, 2) LOLA_SSNAP(0, 3)
-                LOLA_SSNAP(1, 0) LOLA_SSNAP(1, 1) LOLA_SSNAP(1, 2) LOLA_SSNAP(1, 3)
-#undef LOLA_SSNAP
+                LOLA_SSNAP_ALL
             }
         } else {
             uint32_t sb[NK]; int ix[NK];
 #pragma unroll
             for (int x = 0; x < NK; x++) { sb[x] = skey[64 * x + lane]; ix[x] = cidx[64 * x + lane]; }
             uint32_t thr = 0;
-            uint32_t cut = 0;               // != 0: exactly 64 scores lie below it, the search can stop there
+            uint32_t cut = 0;               // != 0: exactly nf scores lie below it, the search can stop there
             int bit0 = 28;
             {   // The threshold moves little from chunk to chunk: if the leading 13 bits of the last one still bracket
-                // the 64th smallest score (fewer than 64 scores below the prefix, at least 64 below the next prefix),
+                // the nf-th smallest score (fewer than nf scores below the prefix, at least nf below the next prefix),
                 // the search resumes below them, in the state it would have reached bit by bit.
                 const uint32_t tA = (uint32_t)__builtin_amdgcn_readfirstlane((int)thr_s) & 0xFFFC0000u, tB = tA + (1u << 18);
                 unsigned long long mA[NK], mB[NK];
@@ -1053,14 +1073,14 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                 int cA = 0, cB = 0;
 #pragma unroll
                 for (int x = 0; x < NK; x++) { cA += __popcll(mA[x]); cB += __popcll(mB[x]); }
-                if (cA < C && cB >= C) {
+                if (cA < nf && cB >= nf) {
                     thr = tA; bit0 = 16;
-                    if (cB == C) cut = tB;
+                    if (cB == nf) cut = tB;
                 } else {   // bit 30 alone, then two bits per step (three trial values counted side by side)
                     int c = 0;
 #pragma unroll
                     for (int x = 0; x < NK; x++) c += __popcll(__ballot(sb[x] < (1u << 30)));
-                    if (c < C) thr = 1u << 30;
+                    if (c < nf) thr = 1u << 30;
                 }
             }
 #pragma unroll 1
@@ -1072,17 +1092,17 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                 int c1 = 0, c2 = 0, c3 = 0;
 #pragma unroll
                 for (int x = 0; x < NK; x++) { c1 += __popcll(m1[x]); c2 += __popcll(m2[x]); c3 += __popcll(m3[x]); }
-                cut = c1 == C ? t1 : (c2 == C ? t2 : (c3 == C ? t3 : 0u));
-                thr = c3 < C ? t3 : (c2 < C ? t2 : (c1 < C ? t1 : thr));
+                cut = c1 == nf ? t1 : (c2 == nf ? t2 : (c3 == nf ? t3 : 0u));
+                thr = c3 < nf ? t3 : (c2 < nf ? t2 : (c1 < nf ? t1 : thr));
             }
             int n_lt = 0, n_eq = 0;
             if (lane == 0) thr_s = cut != 0 ? cut : thr;
-            if (cut != 0) { thr = cut; n_lt = C; }   // everything below the cut is folded, nothing at or above it
+            if (cut != 0) { thr = cut; n_lt = nf; }   // everything below the cut is folded, nothing at or above it
             else {
 #pragma unroll
                 for (int x = 0; x < NK; x++) { n_lt += __popcll(__ballot(sb[x] < thr)); n_eq += __popcll(__ballot(sb[x] == thr)); }
             }
-            const int need = C - n_lt;      // ties at the threshold to fold: 0 after an early stop, else 1 <= need <= n_eq
+            const int need = nf - n_lt;      // ties at the threshold to fold: 0 after an early stop, else 1 <= need <= n_eq
             uint32_t imin = need == 0 ? 0xFFFFFFFFu : 0u;   // ties are folded from token index imin upwards
             if (need != 0 && n_eq != need) {
 #pragma unroll 1
@@ -1094,23 +1114,26 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                     if (c >= need) imin = trial;
                 }
             }
-            int nf = 0, nen = 0, nlv = 0;
+            int nfo = 0, nen = 0, nlv = 0;
 #pragma unroll
             for (int x = 0; x < NK; x++) {
                 const int e = 64 * x + lane;
                 const bool fo = sb[x] < thr || (sb[x] == thr && (uint32_t)ix[x] >= imin);
-                const bool en = !fo && e >= LAM, lv = fo && e < LAM;
+                const bool en = !fo && e >= LAM && e < LAM + cl, lv = fo && e < LAM;
                 const unsigned long long mf = __ballot(fo), me = __ballot(en), ml = __ballot(lv);
                 const unsigned long long below = (1ull << lane) - 1ull;
-                if (fo) flist[nf + __popcll(mf & below)] = e;
+                if (fo) flist[nfo + __popcll(mf & below)] = e;
                 if (en) ecand[nen + __popcll(me & below)] = e;
                 if (lv) eslot[nlv + __popcll(ml & below)] = e;
-                nf += __popcll(mf); nen += __popcll(me); nlv += __popcll(ml);
+                nfo += __popcll(mf); nen += __popcll(me); nlv += __popcll(ml);
             }
+            // places left: the list of folded pairs is padded (with zeros, below), entrants beyond the leavers take unused slots
+            if (lane >= nf) flist[lane] = 0;
+            if (nlv + lane < nen) eslot[nlv + lane] = spc + lane;
             if (lane == 0) ne_s = nen;
         }
         lds_barrier();
-        // exactly 64 are folded, so entrants and leavers pair up
+        // exactly nf are folded, so entrants pair up with leavers and unused slots
         const int ne = ne_s;
 
         // ---- 4. fold: operands of the folded pairs transposed into LDS, then H[f][c] += sum_e phi_e[f] v_e[c].
@@ -1144,6 +1167,20 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                 const int ep = 2 * (vpair0 + (NTH / PR) * vit);
                 va[vit] = reinterpret_cast<const uint4 *>(vrow(flist[ep]))[vch];
                 vb[vit] = reinterpret_cast<const uint4 *>(vrow(flist[ep + 1]))[vch];
+            }
+            if (nf < C) {   // fewer than 64 folded pairs: the rest of the contraction is zeros
+#pragma unroll
+                for (int it = 0; it < PIT; it++) {
+                    const int ep = 8 * ((w >> 1) + CPW * it) + 2 * pairpos;
+                    if (ep >= nf) pa[it] = make_uint4(0, 0, 0, 0);
+                    if (ep + 1 >= nf) pb[it] = make_uint4(0, 0, 0, 0);
+                }
+#pragma unroll
+                for (int vit = 0; vit < VIT; vit++) {
+                    const int ep = 2 * (vpair0 + (NTH / PR) * vit);
+                    if (ep >= nf) va[vit] = make_uint4(0, 0, 0, 0);
+                    if (ep + 1 >= nf) vb[vit] = make_uint4(0, 0, 0, 0);
+                }
             }
             // feature held by element x of piece ch (operand order): 32 (ch / 4) + 16 (x / 4) + 4 (ch % 4) + x % 4
 #pragma unroll
@@ -1284,6 +1321,8 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
 #undef LOLA_SDECL
 #undef LOLA_SLOAD
 #undef LOLA_SSTORE
+#undef LOLA_SSNAP
+#undef LOLA_SSNAP_ALL
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1393,29 +1432,55 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
     const bf16_t *pK = a.prefK + (size_t)si * P * DH, *pV = a.prefV + (size_t)si * P * DH;
     const bf16_t *kc = a.k + (size_t)si * a.T_tokens * DH, *vc = a.v + (size_t)si * a.T_tokens * DH;
     const int64_t a0 = a.st.n_tokens[si];
-    const int spc = a.st.sp_count[si];
-    int j = a.next_j[si];
+    const int spc0 = a.spc_in[si];
+    int j = a.next_j[si];   // the first chunk that is scored, or where the launch before this one stopped
+    const bool fill_snap = a.want_out && a.j0 < generic::first_scored_chunk(a, a0, spc0);   // filling chunks: one snapshot for all
 
     // H^T row 16 w + r16, features 16 mt + 4 g4 + 0..3
     f32x4 hacc[NMT];
 #pragma unroll
     for (int mt = 0; mt < NMT; mt++) hacc[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    bool started = false;
+    const bool started = j < a.j1;
+    if (started || fill_snap) {
+        const float *hrow = Hg + (size_t)(16 * w0 + (tid0 & 15)) * DF + 4 * ((tid0 & 63) >> 4);
+#pragma unroll
+        for (int mt = 0; mt < NMT; mt++) hacc[mt] = *reinterpret_cast<const f32x4 *>(hrow + 16 * mt);
+        for (int x = tid0; x < DF; x += NTH) s_l[x] = sg[x];
+        for (int e = tid0; e < LAM; e += NTH) cidx[e] = sp_idx[e];
+        if (SCORED && a.j0 == 0) {   // given scores: the filling chunks' pairs bring theirs (prefix_kernel placed the pairs)
+            const int js = generic::first_scored_chunk(a, a0, spc0), nfill = generic::left_after(a, a0, min(a.T_tokens, js * C));
+            const int x0 = max(0, ETA - (int)min(a0, (int64_t)ETA));   // row of tok_score of the first pair to leave
+            for (int x = tid0; x < nfill; x += NTH)
+                a.st.sp_score[(size_t)si * LAM + spc0 + x] = a.tok_score[(size_t)si * (ETA + a.T_tokens) + x0 + x];
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+        __syncthreads();
+    }
+    if (fill_snap) {
+        const size_t sj = (size_t)si * a.S + (a.j0 - a.jb);
+        uint16_t *s16 = reinterpret_cast<uint16_t *>(a.snapH) + sj * (2 * DF * DH);
+#pragma unroll
+        for (int ks = 0; ks < KF; ks++) {
+            const float x8[8] = {hacc[2 * ks][0], hacc[2 * ks][1], hacc[2 * ks][2], hacc[2 * ks][3],
+                                 hacc[2 * ks + 1][0], hacc[2 * ks + 1][1], hacc[2 * ks + 1][2], hacc[2 * ks + 1][3]};
+            bf16x8 hi, lo;
+            split8(x8, hi, lo);
+            const int off = ((w0 * KF + ks) * 64 + (tid0 & 63)) << 3;
+            *reinterpret_cast<uint4 *>(s16 + off) = __builtin_bit_cast(uint4, hi);
+            *reinterpret_cast<uint4 *>(s16 + DF * DH + off) = __builtin_bit_cast(uint4, lo);
+        }
+        for (int x = tid0; x < DF; x += NTH) a.snapS[sj * DF + x] = s_l[x];
+    }
 
     for (; j < a.j1; j++) {
+        // The candidates of a scored chunk: the cache slots [0, spc), and rows [i0, cl) of the 64 rows before the chunk's
+        // window moves on, which leave it (cl < 64: a ragged last chunk; i0 > 0: without a cache, before the window is
+        // full); nf of them are folded.  The positions of missing candidates are computed along and kept out of the
+        // selection by a score above all others.
         const int cl = min(C, a.T_tokens - j * C);
         const int64_t aj = a0 + (int64_t)j * C;
-        if (!(cl == C && aj >= ETA && spc == LAM)) break;   // not a regular chunk: the generic kernel takes over
-        if (!started) {
-            const float *hrow = Hg + (size_t)(16 * w0 + (tid0 & 15)) * DF + 4 * ((tid0 & 63) >> 4);
-#pragma unroll
-            for (int mt = 0; mt < NMT; mt++) hacc[mt] = *reinterpret_cast<const f32x4 *>(hrow + 16 * mt);
-            for (int x = tid0; x < DF; x += NTH) s_l[x] = sg[x];
-            for (int e = tid0; e < LAM; e += NTH) cidx[e] = sp_idx[e];
-            started = true;
-            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-            __syncthreads();
-        }
+        const int spc = min(LAM, spc0 + generic::left_after(a, a0, j * C));
+        const int i0 = aj >= ETA ? 0 : ETA - (int)aj, nf = spc + cl - i0 - LAM;
         // the lane coordinates are made opaque once per chunk, so that the addresses derived from them are recomputed in
         // the loop instead of being kept as loop-invariant registers next to H^T
         int tl_ = threadIdx.x;
@@ -1572,12 +1637,12 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
                 if (tid + NTH * x < LAM) a.snapG[sj * LAM + tid + NTH * x] = sprow_ld[x];
         }
 
-        // ---- 3. selection: the 64 candidates with the smallest squared error are folded (order: score descending,
+        // ---- 3. selection: the nf candidates with the smallest squared error are folded (order: score descending,
         // token index ascending, the first lambda stay).  The squared error is |P|^2 / (phi.s)^2 - 2 P.v / (phi.s) + |v|^2
         // (recall = 0 while phi.s = 0); the bit pattern of a float >= 0 orders like an integer.
         if (LAM == 0) {
             // no sparse cache: nothing to select, every pair that leaves is folded
-            if (tid < C) flist[tid] = tid;
+            if (tid < C) flist[tid] = tid < nf ? i0 + tid : i0;
             if (tid == 0) ne_s = 0;
         } else if (SCORED) {
             // given scores (sums of non-negative terms): the cache slots' from the state, the leaving pairs' from the
@@ -1585,22 +1650,23 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
             const float *sps = a.st.sp_score + (size_t)si * LAM;
             const float *tsc = a.tok_score + (size_t)si * (ETA + a.T_tokens) + (size_t)j * C;
             for (int e = tid; e < NE; e += NTH) {
-                const float sc = e < LAM ? sps[e] : tsc[e - LAM];
+                const bool in = e < LAM ? e < spc : e < LAM + cl;
+                const float sc = !in ? 0.f : (e < LAM ? sps[e] : tsc[e - LAM]);
                 tot[0][e] = sc;
-                skey[e] = __float_as_uint(sc) & 0x7FFFFFFFu;
+                skey[e] = in ? __float_as_uint(sc) & 0x7FFFFFFFu : 0xFFFFFFFFu;
             }
         } else {
         for (int e = tid; e < NE; e += NTH) {
             const float dn = dn_l[e], rd = dn > 0.f ? __builtin_amdgcn_rcpf(dn) : 0.f;
             const float sq = fmaxf(fmaf(rd * rd, tot[0][e], fmaf(-2.0f * rd, tot[1][e], tot[2][e])), 0.f);
-            skey[e] = __float_as_uint(sq) & 0x7FFFFFFFu;
+            skey[e] = (e < LAM ? e < spc : e < LAM + cl) ? __float_as_uint(sq) & 0x7FFFFFFFu : 0xFFFFFFFFu;
         }
         }
         lds_barrier();
         if (w == 0 && LAM > 0) {
-            // One wavefront holds all scores (up to 17 per lane) and builds the 64th smallest bit by bit: a trial value is
-            // kept while fewer than 64 scores lie below it.  Scores equal to the threshold are folded too if that makes
-            // exactly 64; otherwise (exact ties across the cut) the same search over their token indices picks the
+            // One wavefront holds all scores (up to 17 per lane) and builds the nf-th smallest bit by bit: a trial value is
+            // kept while fewer than nf scores lie below it.  Scores equal to the threshold are folded too if that makes
+            // exactly nf; otherwise (exact ties across the cut) the same search over their token indices picks the
             // largest ones.  The lists follow from the fold predicate by ballots (candidate order kept).
             uint32_t sb[NKMAX]; int ix[NKMAX];
 #pragma unroll
@@ -1608,24 +1674,24 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
                 sb[x] = 0xFFFFFFFFu; ix[x] = 0;
                 if (x < nk) { sb[x] = skey[64 * x + lane]; ix[x] = cidx[64 * x + lane]; }
             }
-            uint32_t thr = 0, cut = 0;   // cut != 0: exactly 64 scores lie below it
+            uint32_t thr = 0, cut = 0;   // cut != 0: exactly nf scores lie below it
 #pragma unroll 1
             for (int bit = 30; bit >= 0 && cut == 0; bit--) {
                 const uint32_t trial = thr | (1u << bit);
                 int c = 0;
 #pragma unroll
                 for (int x = 0; x < NKMAX; x++) if (x < nk) c += __popcll(__ballot(sb[x] < trial));
-                if (c == C) cut = trial;
-                if (c < C) thr = trial;
+                if (c == nf) cut = trial;
+                if (c < nf) thr = trial;
             }
             int n_lt = 0, n_eq = 0;
-            if (cut != 0) { thr = cut; n_lt = C; }
+            if (cut != 0) { thr = cut; n_lt = nf; }
             else {
 #pragma unroll
                 for (int x = 0; x < NKMAX; x++)
                     if (x < nk) { n_lt += __popcll(__ballot(sb[x] < thr)); n_eq += __popcll(__ballot(sb[x] == thr)); }
             }
-            const int need = C - n_lt;      // ties at the threshold to fold: 0 after an early stop, else 1 <= need <= n_eq
+            const int need = nf - n_lt;      // ties at the threshold to fold: 0 after an early stop, else 1 <= need <= n_eq
             uint32_t imin = need == 0 ? 0xFFFFFFFFu : 0u;   // ties are folded from token index imin upwards
             if (need != 0 && n_eq != need) {
 #pragma unroll 1
@@ -1637,25 +1703,28 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
                     if (c >= need) imin = trial;
                 }
             }
-            int nf = 0, nen = 0, nlv = 0;
+            int nfo = 0, nen = 0, nlv = 0;
             const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
             for (int x = 0; x < NKMAX; x++) {
                 if (x < nk) {
                     const int e = 64 * x + lane;
                     const bool fo = sb[x] < thr || (sb[x] == thr && (uint32_t)ix[x] >= imin);
-                    const bool en = !fo && e >= LAM, lv = fo && e < LAM;
+                    const bool en = !fo && e >= LAM && e < LAM + cl, lv = fo && e < LAM;
                     const unsigned long long mf = __ballot(fo), me = __ballot(en), ml = __ballot(lv);
-                    if (fo) flist[nf + __popcll(mf & below)] = e;
+                    if (fo) flist[nfo + __popcll(mf & below)] = e;
                     if (en) ecand[nen + __popcll(me & below)] = e;
                     if (lv) eslot[nlv + __popcll(ml & below)] = e;
-                    nf += __popcll(mf); nen += __popcll(me); nlv += __popcll(ml);
+                    nfo += __popcll(mf); nen += __popcll(me); nlv += __popcll(ml);
                 }
             }
+            // places left: the list of folded pairs is padded (with zeros, below), entrants beyond the leavers take unused slots
+            if (lane >= nf) flist[lane] = 0;
+            if (nlv + lane < nen) eslot[nlv + lane] = spc + lane;
             if (lane == 0) ne_s = nen;
         }
         lds_barrier();
-        const int ne = ne_s;   // exactly 64 are folded, so entrants and leavers pair up
+        const int ne = ne_s;   // exactly nf are folded, so entrants pair up with leavers and unused slots
 
         // ---- 4. fold: H[f][c] += sum_e phi_e[f] v_e[c], s[f] += sum_e phi_e[f] over the 64 folded pairs, whose rows are
         // gathered into LDS ([pair][part][position] and [pair][column], 16-byte pieces XOR-swizzled with bits of the pair number: fswz, vswz2)
@@ -1692,6 +1761,12 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
         lds_barrier();
+        if (nf < C) {   // fewer than 64 folded pairs: the rest of the contraction is zeros
+            uint4 *fp0 = reinterpret_cast<uint4 *>(FP + nf * FR), *fv0 = reinterpret_cast<uint4 *>(FV + nf * DH);
+            for (int x = tid; x < (C - nf) * (FR / 8); x += NTH) fp0[x] = make_uint4(0, 0, 0, 0);
+            for (int x = tid; x < (C - nf) * PR; x += NTH) fv0[x] = make_uint4(0, 0, 0, 0);
+            lds_barrier();
+        }
         // contraction slots of lane group g4 in k-step kst: pairs 32 kst + 4 g4 + 0..3, then + 16 (the order in which the
         // transposing read delivers them, the same for both operands)
 #pragma unroll

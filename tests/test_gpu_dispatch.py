@@ -32,3 +32,39 @@ def test_reset_empties_every_field(B, Hkv, d, D, eta, lam, kw):
         want = 0xFF if n == "sp_idx" else 0
         assert bool((raw[:nb] == want).all()), n
         assert bool((raw[nb:] == 0x5A).all()), n
+
+
+def case_inputs(seed, B, Hq, Hkv, d, D, N, wscale=1.0):
+    g = wl.rng(seed, 5)
+    mk = lambda *shape: wl.store(g.standard_normal(shape, dtype=np.float32), "bf16")
+    w = lambda H: wl.store((wscale * g.standard_normal((H, d, D // 2), dtype=np.float32) / np.sqrt(d)).astype(np.float32), "bf16")
+    return mk(B, Hq, N, d), mk(B, Hkv, N, d), mk(B, Hkv, N, d), w(Hq), w(Hkv)
+
+
+@pytest.mark.parametrize("d,D,eta,lam,kw", [(128, 128, 64, 128, {}), (64, 128, 64, 64, {}), (128, 128, 64, 256, dict(prefill_overlap=1)),
+                                            (64, 128, 64, 256, {}), (128, 256, 128, 192, {}), (64, 256, 192, 64, dict(phi_kind=1)),
+                                            (128, 128, 128, 0, {}), (64, 256, 192, 0, {}), (128, 128, 64, 128, dict(score_kind=4)),
+                                            (128, 256, 64, 128, dict(score_kind=1))])
+def test_calls_that_end_while_window_and_cache_fill(d, D, eta, lam, kw):
+    """Calls of every awkward length before, across and behind the point where window and cache are full: their filling
+    chunks are copied in one go, the first scored chunk may find an incomplete cache, a ragged last one folds fewer than
+    64 pairs; every third call in one-chunk workspace passes.  Outputs, memories and every chunk's selection against the
+    oracle, then the same without outputs."""
+    full = eta + lam
+    lens = [1, 62, 2, 65, 30, max(1, full - 170), 11, 64, 129, 3, 200]
+    cuts = np.concatenate([[0], np.cumsum(lens)])
+    sh = wl.Shape("fill", "bf16", 2, 4, 2, d, D, T=0, eta=eta, lam=lam, C=64, seed=0)
+    q, k, v, Wq, Wk = case_inputs(40 + d + D + eta + lam, 2, 4, 2, d, D, int(cuts[-1]), wscale=0.5 if kw.get("phi_kind") else 1.0)
+    for outputs in (True, False):
+        if not outputs and kw.get("score_kind"):
+            continue
+        layer, o = None, None
+        for i, (a, b) in enumerate(zip(cuts, cuts[1:])):
+            print("fill", d, D, eta, lam, kw, "call", i, int(a), int(b), "outputs", outputs, flush=True)
+            layer, o, rep = P.prefill_parity(sh, q[:, :, a:b], k[:, :, a:b], v[:, :, a:b], Wq, Wk, layer=layer, oracle=o, layer_kw=kw,
+                                             with_outputs=outputs, workspace_limit=0 if i % 3 == 2 else None)
+            assert layer.lola_path[0] == "mfma"
+        assert rep["scored"] > 0 or lam == 0
+    # one call from empty memories that crosses the point, in one-chunk passes: the filling chunks of later passes too
+    for T in (full + 64 + 5, max(64, full - 3)):
+        P.prefill_parity(sh, q[:, :, :T], k[:, :, :T], v[:, :, :T], Wq, Wk, layer_kw=kw, workspace_limit=0)
