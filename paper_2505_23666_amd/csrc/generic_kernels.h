@@ -373,7 +373,6 @@ struct DecodeArgs {
     void *out;
     int R;          // rows scored per tile
     int no_out;               // 1: the memories are updated only (another kernel computes the outputs)
-    int skip_steady;          // 1: streams in steady state (window and cache full) were updated by another kernel already
 };
 
 template <typename T, typename TO>
@@ -413,7 +412,6 @@ __global__ __launch_bounds__(NT) void decode_kernel(DecodeArgs<T> a) {
     const int slot = eta > 0 ? (int)(tok % eta) : 0;
     const int32_t pidx = (int32_t)(tok - eta);
     int spc = a.st.sp_count[si];
-    if (a.skip_steady && popped && lam > 0 && spc == lam) return;   // (a stream stays in steady state once it is there)
     float *win_score = sk ? a.st.win_score + (size_t)si * eta : nullptr;
     float *sp_score = sk ? a.st.sp_score + (size_t)si * lam : nullptr;
     if (sk) {

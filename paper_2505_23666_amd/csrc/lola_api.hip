@@ -293,12 +293,10 @@ lola_status run_decode(const lola_config *c, const lola_state *st, const void *q
     const size_t lds = 4 * (fixed + (size_t)a.R * (3 * a.dm.d + a.dm.D + 1 + (sk ? a.dm.D : 0)));
     dim3 grid(a.dm.B * a.dm.Hkv), block(generic::NT);
     a.no_out = 0;
-    a.skip_steady = 0;
-    bool wide_out = false;
+    bool wide_out = false, updated = false;
     if constexpr (std::is_same<T, bf16_t>::value) {
         if (wide_decode_ok(c)) {
-            // streams in steady state (window and cache full: scoring, arg-min, fold, slot replacement) by the MFMA update
-            // kernel; the others (still filling) are left to the step kernel, which skips the steady ones
+            // scoring, arg-min, fold, slot replacement by the MFMA update kernel, streams that are still filling included
             fast::StepUpdateArgs ua;
             ua.st = a.st; ua.k = a.k; ua.v = a.v; ua.Wk = a.Wk;
             ua.Hkv = a.dm.Hkv; ua.lam = a.dm.lam; ua.eta = a.dm.eta; ua.phi_kind = a.dm.phi_kind;
@@ -325,16 +323,18 @@ lola_status run_decode(const lola_config *c, const lola_state *st, const void *q
             else { if (c->feat_dim == 256) LOLA_UPD(64, 256); else LOLA_UPD(64, 128); }
 #undef LOLA_UPD
             LAUNCH_CHECK();
-            a.skip_steady = 1;
+            updated = true;
         }
         if (wide_step_out_ok(c)) {
             a.no_out = 1;
             wide_out = true;
         }
     }
-    if (c->out_dtype == LOLA_F32) hipLaunchKernelGGL((generic::decode_kernel<T, float>), grid, block, lds, stream, a);
-    else hipLaunchKernelGGL((generic::decode_kernel<T, bf16_t>), grid, block, lds, stream, a);
-    LAUNCH_CHECK();
+    if (!updated) {
+        if (c->out_dtype == LOLA_F32) hipLaunchKernelGGL((generic::decode_kernel<T, float>), grid, block, lds, stream, a);
+        else hipLaunchKernelGGL((generic::decode_kernel<T, bf16_t>), grid, block, lds, stream, a);
+        LAUNCH_CHECK();
+    }
     if constexpr (std::is_same<T, bf16_t>::value) {
         if (wide_out) {   // the outputs from the updated memories (streams in any state)
             auto launch = [&](auto *o) {

@@ -2256,7 +2256,7 @@ __global__ __launch_bounds__(256) void step_out_combine_kernel(StepOutArgs<TO> a
 //   3. wavefront 0: arg-min (ties: the larger token index goes), phi of the folded pair as fp32 (W_k requested ahead);
 //   4. rank-1 fold on the registers, H^T and s written back; the leaving pair takes the folded pair's slot unless it is
 //      the one folded; the new pair takes the ring slot; the token counter advances.
-// Streams that are not in steady state are left untouched (the shape-generic step kernel takes them).
+// Streams that are not in steady state take fill_step.
 struct StepUpdateArgs {
     State<bf16_t> st;
     const bf16_t *k, *v, *Wk;
@@ -2265,6 +2265,34 @@ struct StepUpdateArgs {
 };
 
 constexpr int STEP_UPDATE_LAMMAX = 2048;
+
+// A step of a stream that is still filling: the new pair takes its ring slot, the pair it displaces (if the window is
+// full) the next cache slot; nothing is scored or folded.  A launch of its own for these streams (the shape-generic step,
+// empty in steady state) took 4.5 us of every step.  Called by all threads of a workgroup, which leaves afterwards.
+template <int DH, bool SCORED>
+__device__ __forceinline__ void fill_step(const StepUpdateArgs &a, int si, int64_t tok, int spc) {
+    constexpr int PR = DH / 8;
+    const int tid = threadIdx.x, slot = (int)(tok % a.eta);
+    const bool popped = tok >= (int64_t)a.eta, isk = tid < PR;
+    const size_t wrow = (size_t)si * a.eta + slot, crow = (size_t)si * a.lam + spc;
+    __syncthreads();   // every thread has read the counters
+    if (tid < 2 * PR) {
+        const int p = tid % PR;
+        uint4 *win = reinterpret_cast<uint4 *>((isk ? a.st.win_k : a.st.win_v) + wrow * DH) + p;
+        const uint4 nw = reinterpret_cast<const uint4 *>((isk ? a.k : a.v) + (size_t)si * DH)[p];
+        if (popped) reinterpret_cast<uint4 *>((isk ? a.st.sp_k : a.st.sp_v) + crow * DH)[p] = *win;
+        *win = nw;
+    }
+    if (tid == 0) {
+        if (popped) {
+            a.st.sp_idx[crow] = (int)(tok - a.eta);
+            a.st.sp_count[si] = spc + 1;
+            if (SCORED) a.st.sp_score[crow] = a.st.win_score[wrow];
+        }
+        if (SCORED) a.st.win_score[wrow] = 0.f;
+        a.st.n_tokens[si] = tok + 1;
+    }
+}
 
 // SCORED: the candidates' scores are the query-dependent sums kept in the state (Sec. 4 / appendix "scoring ablation":
 // sp_score per cache slot, the leaving pair's finished sum in its ring slot) instead of self-recall errors: step 2 is
@@ -2315,7 +2343,11 @@ __global__ __launch_bounds__(512) void step_update_wide_kernel(StepUpdateArgs a)
     for (int x = tid; x < DF; x += 512) s_l[x] = sg[x];
     for (int e = tid; e < LAM; e += 512) idx_l[e] = sp_idx[e];
     const int64_t tok = a.st.n_tokens[si];
-    if (!(tok >= (int64_t)ETA && a.st.sp_count[si] == LAM)) return;
+    const int spc = a.st.sp_count[si];
+    if (!(tok >= (int64_t)ETA && spc == LAM)) {
+        if (MODE != 1) fill_step<DH, SCORED>(a, si, tok, spc);
+        return;
+    }
     const int slot = (int)(tok % ETA), pidx = (int)(tok - ETA);
     bf16_t *sp_k = a.st.sp_k + (size_t)si * LAM * DH, *sp_v = a.st.sp_v + (size_t)si * LAM * DH;
     bf16_t *win_k = a.st.win_k + ((size_t)si * ETA + slot) * DH, *win_v = a.st.win_v + ((size_t)si * ETA + slot) * DH;

@@ -68,3 +68,32 @@ def test_calls_that_end_while_window_and_cache_fill(d, D, eta, lam, kw):
     # one call from empty memories that crosses the point, in one-chunk passes: the filling chunks of later passes too
     for T in (full + 64 + 5, max(64, full - 3)):
         P.prefill_parity(sh, q[:, :, :T], k[:, :, :T], v[:, :, :T], Wq, Wk, layer_kw=kw, workspace_limit=0)
+
+
+@pytest.mark.parametrize("d,D,eta,lam,kw", [(128, 256, 64, 512, {}), (64, 128, 128, 64, {}), (64, 256, 1, 128, {}), (128, 128, 64, 64, dict(score_kind=2))])
+def test_step_with_sequences_at_different_stages(d, D, eta, lam, kw):
+    """One batch holds an empty sequence, sequences that fill their window or cache at different steps, and one in steady
+    state: the same memories, bit for bit, as each sequence stepped by itself; outputs to rounding (their sums over the
+    keys may be split differently at another batch size)."""
+    n, lens = 4, [0, eta - 1, eta, eta + lam - 2, eta + lam + 70]
+    names = FIELDS + (("win_score", "sp_score") if kw else ())
+    sh = wl.Shape("stages", "bf16", 1, 4, 2, d, D, T=0, eta=eta, lam=lam, C=64, seed=0)
+    q, k, v, Wq, Wk = (case_inputs(70 + d + D, len(lens), 4, 2, d, D, max(lens) + n))
+    dq, dk, dv, dWq, dWk = P.to_dev(q, "bf16"), P.to_dev(k, "bf16"), P.to_dev(v, "bf16"), P.w_to_dev(Wq, "bf16"), P.w_to_dev(Wk, "bf16")
+    batch = P.make_layer(sh, B=len(lens), **kw)
+    alone = []
+    for b, T in enumerate(lens):
+        lay = P.make_layer(sh, **kw)
+        if T:
+            lay.prefill(*(x[b:b + 1, :, :T].contiguous() for x in (dq, dk, dv)), dWq, dWk)
+        for nm in names:
+            getattr(batch, nm)[b].copy_(getattr(lay, nm)[0])
+        alone.append(lay)
+    for i in range(n):
+        tok = [[x[b, :, T + i] for b, T in enumerate(lens)] for x in (dq, dk, dv)]
+        out = batch.decode_step(*(torch.stack(x).contiguous() for x in tok), dWq, dWk)
+        for b, lay in enumerate(alone):
+            o1 = lay.decode_step(*(x[b][None].contiguous() for x in tok), dWq, dWk)
+            assert P.row_rel_err(out[b:b + 1].cpu().numpy(), o1.cpu().numpy().astype(np.float64)).max() < 1e-5, (i, b)
+            for nm in names:
+                assert torch.equal(getattr(batch, nm)[b], getattr(lay, nm)[0]), (i, b, nm)
