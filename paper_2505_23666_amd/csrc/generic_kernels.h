@@ -609,6 +609,7 @@ struct PrefillArgs {
     float *tok_score;         // [B*Hkv][eta + T] query-dependent scores: entry window (virtual rows lam ..), then the call's tokens
     int R2;                   // keys / queries per tile of band_score_kernel
     int32_t *spc_in;          // [B*Hkv] pairs in the sparse cache at the call's entry
+    int piece;                // number of the state-evolution launch within the pass
     int fill_closed;          // 1: prefix_kernel does the call's filling chunks (below), the state-evolution kernels start at the first
                               // scored chunk; 0: the shape-generic evolution does every chunk
 };

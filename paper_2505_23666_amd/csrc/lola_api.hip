@@ -388,8 +388,12 @@ constexpr int SCAN_RT128 = LOLA_SCAN_RT128;   // row tiles of H^T per wavefront 
 constexpr int CHIP_CUS = 256;                 // compute units of the MI355X
 constexpr size_t OVERLAP_MAX_STREAMS = 128;   // beyond this many streams the serial evolution fills the chip by itself
 constexpr int OVERLAP_MIN_PIECE = 8;          // chunks per piece on average at least
-constexpr size_t OVERLAP_MIN_WORK = 4096;     // output workgroups (in units of 64 head columns) per piece at least: below
-                                              // this the restart of the evolution costs more than the overlap hides
+constexpr size_t OVERLAP_MIN_WORK = 2048;     // output workgroups (in units of 64 head columns) per piece at least: below
+                                              // this the restart of the evolution costs more than the overlap hides (4096
+                                              // while every piece began with a feature kernel of its own; 4 x 2048 tokens at
+                                              // eta = lambda = 256 1.04 -> 1.00 ms, 1024 measures the same)
+constexpr int SHARE_MAX_WGS = 128;            // evolution workgroups at most where helpers are used
+constexpr int SHARE_MAX_HELPERS = 7;          // helpers per stream at most
 
 std::mutex side_init_mu;   // creation of the per-device entries
 std::mutex side_use_mu;    // held by a call from its first fork to its join: the events are shared
@@ -587,16 +591,34 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
             const bool wide = wide_scan_ok(c);   // (run-time window / budget kernels; else the compile-time shapes)
             if (wide || fast_attend_ok(c)) {
                 // The serial evolution over the scored chunks of the pass; phi of the keys chunk-parallel beforehand: at the
-                // compile-time shapes of every key of the pass, at the run-time shapes (per piece) of the pairs that leave
-                // the window in each chunk and of the cache slots as they stand.
+                // compile-time shapes of every key of the pass, at the run-time shapes of the pairs that leave the window in
+                // each chunk and of the cache slots as the pass finds them (the evolution keeps those current; made again
+                // for every piece they took 24 us each).
                 // (a compile-time shape whose cache does not stay in LDS takes its features the run-time way)
                 const bool big = !wide && c->sparse_budget > 128;
+                // Few streams: further workgroups score shares of the candidates (prefill_mfma.h, WideShare).  A chunk costs a
+                // stream's workgroup about 12 us + 2 us per batch alone and an exchange of about 7 us when shared, so a helper
+                // is worth its compute unit from about six batches on, and at most half of the compute units go to the
+                // evolution, the rest to the outputs beside it: 2 x 4096 tokens at eta 512 / lambda 1024 3.70 ms alone, 2.02 with
+                // 3 helpers per stream, 1.98 with 7, 2.23 with 15; 4 x 2048 at eta = lambda = 256 1.06 ms alone, 1.00 with 1
+                // helper, 1.03 with 3, 1.16 with 7.
+                int helpers = 0;
+                if (wide && a.want_out && !a.dm.score_kind) {
+                    const int batches = (c->sparse_budget + 64) / (c->feat_dim == 256 ? 32 : 64);
+                    helpers = std::max(0, std::min({batches / 6, SHARE_MAX_WGS / (int)ns - 1, SHARE_MAX_HELPERS}));
+                }
                 if (!wide && !big) {
                     const dim3 gp((unsigned)(jend - j0), (unsigned)ns);
                     if (c->head_dim == 128) hipLaunchKernelGGL(fast::phi_k_kernel<128>, gp, dim3(256), 0, stream, a);
                     else hipLaunchKernelGGL(fast::phi_k_kernel<64>, gp, dim3(256), 0, stream, a);
-                    LAUNCH_CHECK();
+                } else {
+                    const dim3 gp((unsigned)(jend - j0) + (unsigned)(c->sparse_budget / 64), (unsigned)ns);
+#define LOLA_PHI(DHV, DFV) hipLaunchKernelGGL((fast::phi_wide_kernel<DHV, DFV>), gp, dim3(256), 0, stream, a)
+                    if (c->head_dim == 128) { if (c->feat_dim == 256) LOLA_PHI(128, 256); else LOLA_PHI(128, 128); }
+                    else { if (c->feat_dim == 256) LOLA_PHI(64, 256); else LOLA_PHI(64, 128); }
+#undef LOLA_PHI
                 }
+                LAUNCH_CHECK();
                 // With few streams the serial evolution occupies few compute units, so the pass is cut into pieces and
                 // the outputs of a piece (chunk-parallel, from its snapshots) run on a second stream beside the
                 // evolution of the next piece.
@@ -659,22 +681,16 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                     // event) and are enqueued after its launch: the evolution's workgroups, which need a compute unit's whole
                     // register file, should be resident before the output workgroups arrive, instead of queueing for
                     // compute units behind them.
+                    a.piece = ip;
                     if (wide) {
-                        const dim3 gp((unsigned)(a.j1 - a.j0) + (unsigned)(c->sparse_budget / 64), (unsigned)ns);
-#define LOLA_WSCAN(DHV, DFV) do { hipLaunchKernelGGL((fast::phi_wide_kernel<DHV, DFV>), gp, dim3(256), 0, stream, a); \
-                                  if (side && ip > 0 && hipEventRecord(side->fork[ip - 1], stream) != hipSuccess) return LOLA_ERR_HIP; \
+#define LOLA_WSCAN(DHV, DFV) do { if (side && ip > 0 && hipEventRecord(side->fork[ip - 1], stream) != hipSuccess) return LOLA_ERR_HIP; \
                                   if (a.dm.score_kind) hipLaunchKernelGGL((fast::scan_wide_kernel<DHV, DFV, true>), gs, dim3(DHV * 4), 0, stream, a); \
+                                  else if (helpers > 0) hipLaunchKernelGGL((fast::scan_wide_kernel<DHV, DFV, false, true>), dim3((unsigned)(ns * (1 + helpers))), dim3(DHV * 4), 0, stream, a); \
                                   else hipLaunchKernelGGL((fast::scan_wide_kernel<DHV, DFV, false>), gs, dim3(DHV * 4), 0, stream, a); } while (0)
                         if (c->head_dim == 128) { if (c->feat_dim == 256) LOLA_WSCAN(128, 256); else LOLA_WSCAN(128, 128); }
                         else { if (c->feat_dim == 256) LOLA_WSCAN(64, 256); else LOLA_WSCAN(64, 128); }
 #undef LOLA_WSCAN
                     } else {
-                    if (big) {
-                        const dim3 gp((unsigned)(a.j1 - a.j0) + (unsigned)(c->sparse_budget / 64), (unsigned)ns);
-                        if (c->head_dim == 128) hipLaunchKernelGGL((fast::phi_wide_kernel<128, 128>), gp, dim3(256), 0, stream, a);
-                        else hipLaunchKernelGGL((fast::phi_wide_kernel<64, 128>), gp, dim3(256), 0, stream, a);
-                        LAUNCH_CHECK();
-                    }
                     if (side && ip > 0 && hipEventRecord(side->fork[ip - 1], stream) != hipSuccess) return LOLA_ERR_HIP;
 #define LOLA_SCAN(LAMV) do { if (c->head_dim == 128) hipLaunchKernelGGL((fast::scan_fast_kernel<LAMV, 128, SCAN_RT128>), gs, dim3(512 / SCAN_RT128), 0, stream, a); \
                              else hipLaunchKernelGGL((fast::scan_fast_kernel<LAMV, 64, 1>), gs, dim3(256), 0, stream, a); } while (0)

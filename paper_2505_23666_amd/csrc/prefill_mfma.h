@@ -1345,11 +1345,15 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
 // phi_wide_kernel: phi of the rows the evolution kernel reads (Sec. 2.3 eq. feature_map), 64 rows per workgroup, bf16
 // high + low parts in operand order: blocks [0, j1 - j0) the pairs that leave the window in chunk j0 + block (virtual
 // rows lam + j C + 0..63) -> phiK[j - jb]; the lam / 64 blocks behind them the cache slots -> phiE[slot].
+constexpr int WIDE_SHARE_CLEAR = 768;   // words of a WideShare ahead of its scores
 template <int DH, int DF>
 __global__ __launch_bounds__(256) void phi_wide_kernel(generic::PrefillArgs<bf16_t> a) {
     constexpr int M = DF / 2, C = 64, KS = DH / 32, NZT = M / 16, FR = 2 * DF;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
     const int si = blockIdx.y, h = si % a.dm.Hkv, LAM = a.dm.lam, P = LAM + a.dm.eta;
+    // the exchange of the evolution's workgroups (struct WideShare, behind the slots' rows) starts cleared
+    if (blockIdx.x == 0)
+        for (int x = tid; x < WIDE_SHARE_CLEAR; x += 256) reinterpret_cast<int *>(a.phiE + ((size_t)si * (LAM + C) + LAM) * DF)[x] = 0;
     const int nch = a.j1 - a.j0, row = 16 * w + r16;
     const bf16_t *Wk = a.Wk + (size_t)h * M * DH;
     const bf16_t *kr;
@@ -1394,19 +1398,168 @@ __global__ __launch_bounds__(256) void phi_wide_kernel(generic::PrefillArgs<bf16
     }
 }
 
+// Recall errors of the candidate batches [b0, b1) (b0 < b1): |P|^2, P.v, |v|^2 over all value columns -> tot, phi(k).s ->
+// dn_l.  phirow(e), vrow(e): feature and value row of candidate e.  Ahi, Alo: this wavefront's 16 rows of H^T.
+template <int DH, int DF>
+struct WideScan {
+    static constexpr int C = 64, NW = DH / 16, NTH = 64 * NW, KF = DF / 32, NMT = DF / 16, PR = DH / 8, FR = 2 * DF, PP = DF / 8;
+    static constexpr int RB = DF == 256 ? 32 : 64, TB = RB / 16;  // candidates per batch (32 KB of features)
+    static constexpr int NBUF = DF == 256 ? 3 : 2;                // batch buffers in LDS: requests run NBUF - 1 batches ahead
+    static constexpr int VPB = RB * DH / 512 / NW;                // direct loads per wavefront and batch: values ...
+    static constexpr int LPB = RB * FR / 512 / NW + VPB;          // ... and features + values
+    static_assert(VPB >= 1 && VPB * NW * 512 == RB * DH, "the wavefronts share the values of a batch evenly");
+    static constexpr int NEMAX = 1024 + C, NKMAX = NEMAX / 64;
+    static constexpr int BUF = RB * FR + RB * DH;                 // 16-bit elements of one batch buffer: features, then values
+};
+template <int DH, int DF, typename FPhi, typename FVal>
+__device__ __forceinline__ void wide_score_batches(uint16_t *pool, const float *s_l, float *dn_l, float (*tot)[WideScan<DH, DF>::NEMAX],
+                                                   float (*part)[3][DH / 16][WideScan<DH, DF>::RB], const bf16x8 (&Ahi)[DF / 32],
+                                                   const bf16x8 (&Alo)[DF / 32], int b0, int b1, int tid, FPhi phirow, FVal vrow) {
+    using L = WideScan<DH, DF>;
+    constexpr int NW = L::NW, NTH = L::NTH, KF = L::KF, PR = L::PR, FR = L::FR, PP = L::PP, RB = L::RB, TB = L::TB, NBUF = L::NBUF,
+                  VPB = L::VPB, LPB = L::LPB, BUF = L::BUF;
+    const int lane = tid & 63, r16 = lane & 15, g4 = lane >> 4, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // requests of batch b into buffer buf: 1 KB per instruction, lane l fills bytes 16 l ..; a row's 16-byte pieces are
+    // XOR-swizzled with the row number, so a lane fetches the piece that belongs in its position
+    auto issue = [&](int b, int buf) {
+        uint16_t *PBb = pool + buf * BUF, *VBb = PBb + RB * FR;
+        const int e0 = b * RB;
+#pragma unroll
+        for (int it = 0; it < RB * FR / 512 / NW; it++) {
+            const int i = w + NW * it, g = 512 * i + 8 * lane, row = g / FR, pt = (g % FR) / DF, slot = (g % DF) >> 3;
+            const uint16_t *src = phirow(e0 + row) + pt * DF + ((slot ^ (row & 15)) << 3);
+            lds_dma16(src, PBb + 512 * i);
+        }
+#pragma unroll
+        for (int it = 0; it < VPB; it++) {
+            const int i = w + NW * it, g = 512 * i + 8 * lane, row = g / DH, slot = (g % DH) >> 3;
+            const bf16_t *src = vrow(e0 + row) + ((slot ^ (row & (PR - 1))) << 3);
+            lds_dma16(src, VBb + 512 * i);
+        }
+    };
+#pragma unroll
+    for (int b = 0; b < NBUF - 1; b++) if (b0 + b < b1) issue(b0 + b, b);
+
+    // ---- 2. recall error of the candidates, batch by batch
+    int buf = 0;
+#pragma unroll 1
+    for (int b = b0; b < b1; b++) {
+        // this wavefront's share of batch b has landed: all but the requests of the batches behind it
+        const int ahead = min(NBUF - 2, b1 - 1 - b);
+        if (NBUF >= 4 && ahead >= 2) __builtin_amdgcn_s_waitcnt(0x0F70 | ((2 * LPB) & 15) | (((2 * LPB) >> 4) << 14));
+        else if (NBUF >= 3 && ahead == 1) __builtin_amdgcn_s_waitcnt(0x0F70 | (LPB & 15) | ((LPB >> 4) << 14));
+        else __builtin_amdgcn_s_waitcnt(0x0F70);
+        lds_barrier();                        // ... and everybody's; the readers of batch b - 1's buffer are done
+        if (b + NBUF - 1 < b1) issue(b + NBUF - 1, buf == 0 ? NBUF - 1 : buf - 1);
+        const uint16_t *PBb = pool + buf * BUF, *VBb = PBb + RB * FR;
+        const int pb = b & 1;
+        if (b > b0 && tid < 3 * RB) {          // batch b - 1: the wavefronts' sums over their columns, added in a fixed order
+            const int k = tid / RB, r = tid % RB;
+            float sum = 0.f;
+#pragma unroll
+            for (int x = 0; x < NW; x++) sum += part[pb ^ 1][k][x][r];
+            tot[k][(b - 1) * RB + r] = sum;
+        }
+        {   // phi(k).s of the batch's rows: TPR neighbouring lanes share a row
+            constexpr int TPR = NTH / RB, NPC = PP / TPR;
+            const int r = tid / TPR, sub = tid % TPR;
+            float dsum = 0.f;
+#pragma unroll
+            for (int x = 0; x < NPC; x++) {
+                const int pc = sub + TPR * x, addr = r * FR + ((pc ^ (r & 15)) << 3);
+                const uint4 hi = *reinterpret_cast<const uint4 *>(&PBb[addr]), lo = *reinterpret_cast<const uint4 *>(&PBb[addr + DF]);
+                const float4 s0 = *reinterpret_cast<const float4 *>(&s_l[32 * (pc >> 2) + 4 * (pc & 3)]);
+                const float4 s1 = *reinterpret_cast<const float4 *>(&s_l[32 * (pc >> 2) + 16 + 4 * (pc & 3)]);
+                dsum = fmaf(bf_lo(hi.x) + bf_lo(lo.x), s0.x, dsum); dsum = fmaf(bf_hi(hi.x) + bf_hi(lo.x), s0.y, dsum);
+                dsum = fmaf(bf_lo(hi.y) + bf_lo(lo.y), s0.z, dsum); dsum = fmaf(bf_hi(hi.y) + bf_hi(lo.y), s0.w, dsum);
+                dsum = fmaf(bf_lo(hi.z) + bf_lo(lo.z), s1.x, dsum); dsum = fmaf(bf_hi(hi.z) + bf_hi(lo.z), s1.y, dsum);
+                dsum = fmaf(bf_lo(hi.w) + bf_lo(lo.w), s1.z, dsum); dsum = fmaf(bf_hi(hi.w) + bf_hi(lo.w), s1.w, dsum);
+            }
+            dsum += dpp_f<0xB1>(dsum); dsum += dpp_f<0x4E>(dsum);
+            if (TPR >= 8) dsum += dpp_f<0x141>(dsum);
+            if (TPR >= 16) dsum += dpp_f<0x140>(dsum);
+            if (sub == 0) dn_l[b * RB + r] = dsum;
+        }
+        // recall GEMM: A = this wavefront's 16 rows of H^T, B = phi of 16 candidates from LDS; lane (candidate r16,
+        // group g4) holds the recall at columns 16 w + 4 g4 + i and pairs it with the candidate's values there
+#pragma unroll
+        for (int u = 0; u < TB; u++) {
+            const uint16_t *rowp = PBb + (16 * u + r16) * FR;
+            bf16x8 Bh[KF], Bl[KF];
+#pragma unroll
+            for (int ks = 0; ks < KF; ks++) {
+                const int addr = ((4 * ks + g4) ^ r16) << 3;
+                Bh[ks] = as_bf16x8(*reinterpret_cast<const uint4 *>(rowp + addr));
+                Bl[ks] = as_bf16x8(*reinterpret_cast<const uint4 *>(rowp + DF + addr));
+            }
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};   // the three products of a k-step go into one accumulator: the large one first
+#pragma unroll
+            for (int ks = 0; ks < KF; ks++) acc = mfma16(Ahi[ks], Bh[ks], acc);
+#pragma unroll
+            for (int ks = 0; ks < KF; ks++) acc = mfma16(Ahi[ks], Bl[ks], acc);
+#pragma unroll
+            for (int ks = 0; ks < KF; ks++) acc = mfma16(Alo[ks], Bh[ks], acc);
+            const uint2 vv = *reinterpret_cast<const uint2 *>(&VBb[(16 * u + r16) * DH + (((2 * w + (g4 >> 1)) ^ (r16 & (PR - 1))) << 3) + 4 * (g4 & 1)]);
+            const float v0 = bf_lo(vv.x), v1 = bf_hi(vv.x), v2 = bf_lo(vv.y), v3 = bf_hi(vv.y);
+            float sa = 0.f, sb = 0.f, sc = 0.f;
+            sa = fmaf(acc[0], acc[0], sa); sa = fmaf(acc[1], acc[1], sa); sa = fmaf(acc[2], acc[2], sa); sa = fmaf(acc[3], acc[3], sa);
+            sb = fmaf(acc[0], v0, sb); sb = fmaf(acc[1], v1, sb); sb = fmaf(acc[2], v2, sb); sb = fmaf(acc[3], v3, sb);
+            sc = fmaf(v0, v0, sc); sc = fmaf(v1, v1, sc); sc = fmaf(v2, v2, sc); sc = fmaf(v3, v3, sc);
+            const float s3 = grp_sum3(sa, sb, sc);   // lane group g4 holds sum g4
+            if (g4 < 3) part[pb][g4][w][16 * u + r16] = s3;
+        }
+        buf = buf == NBUF - 1 ? 0 : buf + 1;
+    }
+    lds_barrier();
+    if (tid < 3 * RB) {
+        const int k = tid / RB, r = tid % RB;
+        float sum = 0.f;
+#pragma unroll
+        for (int x = 0; x < NW; x++) sum += part[(b1 - 1) & 1][k][x][r];
+        tot[k][(b1 - 1) * RB + r] = sum;
+    }
+    lds_barrier();
+}
+
+// The evolution shared among workgroups (SHARED).  One workgroup per stream walks the chunks; with few streams the rest of
+// the chip idles while it scores lambda + 64 candidates, so further workgroups (helpers) take shares of the
+// batches.  A chunk's exchange: the stream's workgroup stores the chunk's snapshot (whose pieces are the recall GEMM's
+// operands), publishes `go` (chunk, helpers in use, batches each), scores its own batches, and waits for `done`; a helper
+// waits for `go`, takes H^T and s from the snapshot, and leaves its candidates' squared errors in `score`.
+// No wait depends on a workgroup that may not have a compute unit: helpers join by counting themselves in `joined` after
+// `started` says that the stream's workgroup runs (they leave if that takes too long), only helpers that have joined are
+// given work, and the stream's workgroup ends by publishing GO_END.
+// A chunk at lambda = 1024 and 256 features: 85 us on one workgroup (34 batches of 2 us), 37 us with 5 - 7 helpers beside
+// the outputs.  The release and acquire fences cost less than stores and loads past the caches would (2.19 against 2.03 ms
+// for 2 x 4096 tokens at eta 512 / lambda 1024).
+constexpr int WIDE_PIECES = 8;   // launches of a pass at most
+struct WideShare {   // per stream, in the feature scratch behind the cache slots' rows
+    struct Piece {   // one per launch of the pass, each word on a cache line of its own (cleared by phi_wide_kernel)
+        int started, joined, pad0[30];
+        unsigned long long go; int pad1[30];
+        int done, pad2[31];
+    } piece[WIDE_PIECES];
+    uint32_t score[1024 + 64];
+};
+static_assert(sizeof(WideShare::Piece) * WIDE_PIECES == 4 * WIDE_SHARE_CLEAR, "phi_wide_kernel clears the pieces");
+static_assert(sizeof(WideShare) <= 64 * 128 * 4, "fits the 64 spare rows of the feature scratch");
+constexpr unsigned long long GO_END = ~0ull;
+constexpr int SHARE_LEAD = 3;        // batches scored in the time a helper takes to see `go` and to load H^T
+template <typename V> __device__ __forceinline__ V agent_load(const V *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename V> __device__ __forceinline__ void agent_store(V *p, V v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <int DF>
+__device__ __forceinline__ WideShare *wide_share(const generic::PrefillArgs<bf16_t> &a, int si) {
+    return reinterpret_cast<WideShare *>(a.phiE + ((size_t)si * (a.dm.lam + 64) + a.dm.lam) * DF);
+}
+
 // SCORED: the candidates' scores are given (the query-dependent scores of Sec. 4 / appendix "scoring ablation", summed
 // beforehand per token: tok_score for the pairs that leave the window, sp_score for the cache slots) instead of being
 // self-recall errors; step 2 is skipped, an entrant's score follows it into its slot, everything else is the same.
-template <int DH, int DF, bool SCORED>
+template <int DH, int DF, bool SCORED, bool SHARED = false>
 __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<bf16_t> a) {
-    constexpr int C = 64, NW = DH / 16, NTH = 64 * NW, KF = DF / 32, NMT = DF / 16, PR = DH / 8, FR = 2 * DF, PP = DF / 8;
-    constexpr int RB = DF == 256 ? 32 : 64, TB = RB / 16;  // candidates per batch (32 KB of features)
-    constexpr int NBUF = DF == 256 ? 3 : 2;                // batch buffers in LDS: requests run NBUF - 1 batches ahead
-    constexpr int VPB = RB * DH / 512 / NW;                // direct loads per wavefront and batch: values ...
-    constexpr int LPB = RB * FR / 512 / NW + VPB;          // ... and features + values
-    static_assert(VPB >= 1 && VPB * NW * 512 == RB * DH, "the wavefronts share the values of a batch evenly");
-    constexpr int NEMAX = 1024 + C, NKMAX = NEMAX / 64;
-    constexpr int BUF = RB * FR + RB * DH;                 // 16-bit elements of one batch buffer: features, then values
+    using L = WideScan<DH, DF>;
+    constexpr int C = L::C, NW = L::NW, NTH = L::NTH, KF = L::KF, NMT = L::NMT, PR = L::PR, FR = L::FR, RB = L::RB, NBUF = L::NBUF,
+                  NEMAX = L::NEMAX, NKMAX = L::NKMAX, BUF = L::BUF;
     constexpr int FOLD = C * FR + C * DH;                  // the folded pairs' features and values
     constexpr int POOL = NBUF * BUF > FOLD ? NBUF * BUF : FOLD;
     static_assert((DH == 64 || DH == 128) && (DF == 128 || DF == 256), "shape");
@@ -1421,7 +1574,8 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
     __shared__ int ne_s;
 
     const int tid0 = threadIdx.x, w0 = tid0 >> 6;
-    const int si = blockIdx.x;
+    const int nstreams = a.dm.B * a.dm.Hkv;
+    const int si = SHARED ? (int)blockIdx.x % nstreams : (int)blockIdx.x;
     const int LAM = a.dm.lam, ETA = a.dm.eta, P = LAM + ETA, NE = LAM + C, NBATCH = NE / RB, nk = NE / 64;
     float *Hg = a.st.H + (size_t)si * DF * DH;
     float *sg = a.st.s + (size_t)si * DF;
@@ -1431,6 +1585,70 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
     uint16_t *phiE = reinterpret_cast<uint16_t *>(a.phiE + (size_t)si * (LAM + C) * DF);   // [slot][part][DF] bf16, operand order
     const bf16_t *pK = a.prefK + (size_t)si * P * DH, *pV = a.prefV + (size_t)si * P * DH;
     const bf16_t *kc = a.k + (size_t)si * a.T_tokens * DH, *vc = a.v + (size_t)si * a.T_tokens * DH;
+    // squared recall error |P|^2 / (phi.s)^2 - 2 P.v / (phi.s) + |v|^2 of candidate e (recall = 0 while phi.s = 0), as bits
+    auto sq_bits = [&](int e) -> uint32_t {
+        const float dn = dn_l[e], rd = dn > 0.f ? __builtin_amdgcn_rcpf(dn) : 0.f;
+        return __float_as_uint(fmaxf(fmaf(rd * rd, tot[0][e], fmaf(-2.0f * rd, tot[1][e], tot[2][e])), 0.f)) & 0x7FFFFFFFu;
+    };
+    __shared__ int nh_s, bh_s;
+    __shared__ unsigned long long go_s;
+    WideShare::Piece *sh = SHARED ? &wide_share<DF>(a, si)->piece[a.piece] : nullptr;
+    uint32_t *score_x = SHARED ? wide_share<DF>(a, si)->score : nullptr;
+    int want = 0;   // shares handed out so far
+    if constexpr (SHARED) {
+        if ((int)blockIdx.x >= nstreams) {   // a helper
+            const int tid = tid0, lane = tid & 63;
+            if (tid == 0) {
+                int on = 0;
+                for (int it = 0; it < 64 && !on; it++) { on = agent_load(&sh->started); if (!on) __builtin_amdgcn_s_sleep(8); }
+                nh_s = on ? __hip_atomic_fetch_add(&sh->joined, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+            }
+            __syncthreads();
+            const int rank = nh_s;
+            if (rank < 0) return;
+            unsigned long long last = 0;
+            for (;;) {
+                if (tid == 0) {
+                    unsigned long long g;
+                    while ((g = agent_load(&sh->go)) == last) __builtin_amdgcn_s_sleep(2);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                    go_s = g;
+                }
+                __syncthreads();
+                const unsigned long long g = go_s;
+                last = g;
+                if (g == GO_END) return;
+                const int used = (int)(g & 255), bh = (int)((g >> 8) & 255), jj = (int)(g >> 16) - 1;
+                if (rank < used) {
+                    const int j = a.jb + jj, vrow_l = LAM + j * C, b1 = NBATCH - rank * bh, b0 = b1 - bh;
+                    const size_t sj = (size_t)si * a.S + jj;
+                    const uint16_t *s16 = reinterpret_cast<const uint16_t *>(a.snapH) + sj * (2 * DF * DH);
+                    bf16x8 Ahi[KF], Alo[KF];
+#pragma unroll
+                    for (int ks = 0; ks < KF; ks++) {
+                        const int off = ((w0 * KF + ks) * 64 + lane) << 3;
+                        Ahi[ks] = as_bf16x8(*reinterpret_cast<const uint4 *>(s16 + off));
+                        Alo[ks] = as_bf16x8(*reinterpret_cast<const uint4 *>(s16 + DF * DH + off));
+                    }
+                    for (int x = tid; x < DF; x += NTH) s_l[x] = a.snapS[sj * DF + x];
+                    __syncthreads();
+                    const uint16_t *phk = a.phiK + sj * C * FR;
+                    auto phirow = [&](int e) -> const uint16_t * { return e < LAM ? phiE + (size_t)e * FR : phk + (size_t)(e - LAM) * FR; };
+                    auto vrow = [&](int e) -> const bf16_t * {
+                        if (e < LAM) return sp_v + (size_t)e * DH;
+                        const int vr = vrow_l + (e - LAM);
+                        return vr < P ? pV + (size_t)vr * DH : vc + (size_t)(vr - P) * DH;
+                    };
+                    wide_score_batches<DH, DF>(pool, s_l, dn_l, tot, part, Ahi, Alo, b0, b1, tid, phirow, vrow);
+                    for (int e = b0 * RB + tid; e < b1 * RB; e += NTH) agent_store(&score_x[e], sq_bits(e));
+                    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+                }
+                __syncthreads();
+                if (rank < used && tid == 0) __hip_atomic_fetch_add(&sh->done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (tid0 == 0) agent_store(&sh->started, 1);
+    }
     const int64_t a0 = a.st.n_tokens[si];
     const int spc0 = a.spc_in[si];
     int j = a.next_j[si];   // the first chunk that is scored, or where the launch before this one stopped
@@ -1516,112 +1734,7 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
         }
         if (tid < C) cidx[LAM + tid] = (int)(aj - ETA + tid);
 
-        // requests of batch b into buffer buf: 1 KB per instruction, lane l fills bytes 16 l ..; a row's 16-byte pieces are
-        // XOR-swizzled with the row number, so a lane fetches the piece that belongs in its position
-        auto issue = [&](int b, int buf) {
-            uint16_t *PBb = pool + buf * BUF, *VBb = PBb + RB * FR;
-            const int e0 = b * RB;
-#pragma unroll
-            for (int it = 0; it < RB * FR / 512 / NW; it++) {
-                const int i = w + NW * it, g = 512 * i + 8 * lane, row = g / FR, pt = (g % FR) / DF, slot = (g % DF) >> 3;
-                const uint16_t *src = phirow(e0 + row) + pt * DF + ((slot ^ (row & 15)) << 3);
-                lds_dma16(src, PBb + 512 * i);
-            }
-#pragma unroll
-            for (int it = 0; it < VPB; it++) {
-                const int i = w + NW * it, g = 512 * i + 8 * lane, row = g / DH, slot = (g % DH) >> 3;
-                const bf16_t *src = vrow(e0 + row) + ((slot ^ (row & (PR - 1))) << 3);
-                lds_dma16(src, VBb + 512 * i);
-            }
-        };
-        if (!SCORED && LAM > 0) {
-#pragma unroll
-        for (int b = 0; b < NBUF - 1; b++) issue(b, b);   // (lambda + 64 >= 128 candidates: at least NBUF batches)
-
-        // ---- 2. recall error of the candidates, batch by batch
-        int buf = 0;
-#pragma unroll 1
-        for (int b = 0; b < NBATCH; b++) {
-            // this wavefront's share of batch b has landed: all but the requests of the batches behind it
-            const int ahead = min(NBUF - 2, NBATCH - 1 - b);
-            if (NBUF >= 4 && ahead >= 2) __builtin_amdgcn_s_waitcnt(0x0F70 | ((2 * LPB) & 15) | (((2 * LPB) >> 4) << 14));
-            else if (NBUF >= 3 && ahead == 1) __builtin_amdgcn_s_waitcnt(0x0F70 | (LPB & 15) | ((LPB >> 4) << 14));
-            else __builtin_amdgcn_s_waitcnt(0x0F70);
-            lds_barrier();                        // ... and everybody's; the readers of batch b - 1's buffer are done
-            if (b + NBUF - 1 < NBATCH) issue(b + NBUF - 1, buf == 0 ? NBUF - 1 : buf - 1);
-            const uint16_t *PBb = pool + buf * BUF, *VBb = PBb + RB * FR;
-            const int pb = b & 1;
-            if (b > 0 && tid < 3 * RB) {          // batch b - 1: the wavefronts' sums over their columns, added in a fixed order
-                const int k = tid / RB, r = tid % RB;
-                float sum = 0.f;
-#pragma unroll
-                for (int x = 0; x < NW; x++) sum += part[pb ^ 1][k][x][r];
-                tot[k][(b - 1) * RB + r] = sum;
-            }
-            {   // phi(k).s of the batch's rows: TPR neighbouring lanes share a row
-                constexpr int TPR = NTH / RB, NPC = PP / TPR;
-                const int r = tid / TPR, sub = tid % TPR;
-                float dsum = 0.f;
-#pragma unroll
-                for (int x = 0; x < NPC; x++) {
-                    const int pc = sub + TPR * x, addr = r * FR + ((pc ^ (r & 15)) << 3);
-                    const uint4 hi = *reinterpret_cast<const uint4 *>(&PBb[addr]), lo = *reinterpret_cast<const uint4 *>(&PBb[addr + DF]);
-                    const float4 s0 = *reinterpret_cast<const float4 *>(&s_l[32 * (pc >> 2) + 4 * (pc & 3)]);
-                    const float4 s1 = *reinterpret_cast<const float4 *>(&s_l[32 * (pc >> 2) + 16 + 4 * (pc & 3)]);
-                    dsum = fmaf(bf_lo(hi.x) + bf_lo(lo.x), s0.x, dsum); dsum = fmaf(bf_hi(hi.x) + bf_hi(lo.x), s0.y, dsum);
-                    dsum = fmaf(bf_lo(hi.y) + bf_lo(lo.y), s0.z, dsum); dsum = fmaf(bf_hi(hi.y) + bf_hi(lo.y), s0.w, dsum);
-                    dsum = fmaf(bf_lo(hi.z) + bf_lo(lo.z), s1.x, dsum); dsum = fmaf(bf_hi(hi.z) + bf_hi(lo.z), s1.y, dsum);
-                    dsum = fmaf(bf_lo(hi.w) + bf_lo(lo.w), s1.z, dsum); dsum = fmaf(bf_hi(hi.w) + bf_hi(lo.w), s1.w, dsum);
-                }
-                dsum += dpp_f<0xB1>(dsum); dsum += dpp_f<0x4E>(dsum);
-                if (TPR >= 8) dsum += dpp_f<0x141>(dsum);
-                if (TPR >= 16) dsum += dpp_f<0x140>(dsum);
-                if (sub == 0) dn_l[b * RB + r] = dsum;
-            }
-            // recall GEMM: A = this wavefront's 16 rows of H^T, B = phi of 16 candidates from LDS; lane (candidate r16,
-            // group g4) holds the recall at columns 16 w + 4 g4 + i and pairs it with the candidate's values there
-#pragma unroll
-            for (int u = 0; u < TB; u++) {
-                const uint16_t *rowp = PBb + (16 * u + r16) * FR;
-                bf16x8 Bh[KF], Bl[KF];
-#pragma unroll
-                for (int ks = 0; ks < KF; ks++) {
-                    const int addr = ((4 * ks + g4) ^ r16) << 3;
-                    Bh[ks] = as_bf16x8(*reinterpret_cast<const uint4 *>(rowp + addr));
-                    Bl[ks] = as_bf16x8(*reinterpret_cast<const uint4 *>(rowp + DF + addr));
-                }
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};   // the three products of a k-step go into one accumulator: the large one first
-#pragma unroll
-                for (int ks = 0; ks < KF; ks++) acc = mfma16(Ahi[ks], Bh[ks], acc);
-#pragma unroll
-                for (int ks = 0; ks < KF; ks++) acc = mfma16(Ahi[ks], Bl[ks], acc);
-#pragma unroll
-                for (int ks = 0; ks < KF; ks++) acc = mfma16(Alo[ks], Bh[ks], acc);
-                const uint2 vv = *reinterpret_cast<const uint2 *>(&VBb[(16 * u + r16) * DH + (((2 * w + (g4 >> 1)) ^ (r16 & (PR - 1))) << 3) + 4 * (g4 & 1)]);
-                const float v0 = bf_lo(vv.x), v1 = bf_hi(vv.x), v2 = bf_lo(vv.y), v3 = bf_hi(vv.y);
-                float sa = 0.f, sb = 0.f, sc = 0.f;
-                sa = fmaf(acc[0], acc[0], sa); sa = fmaf(acc[1], acc[1], sa); sa = fmaf(acc[2], acc[2], sa); sa = fmaf(acc[3], acc[3], sa);
-                sb = fmaf(acc[0], v0, sb); sb = fmaf(acc[1], v1, sb); sb = fmaf(acc[2], v2, sb); sb = fmaf(acc[3], v3, sb);
-                sc = fmaf(v0, v0, sc); sc = fmaf(v1, v1, sc); sc = fmaf(v2, v2, sc); sc = fmaf(v3, v3, sc);
-                const float s3 = grp_sum3(sa, sb, sc);   // lane group g4 holds sum g4
-                if (g4 < 3) part[pb][g4][w][16 * u + r16] = s3;
-            }
-            buf = buf == NBUF - 1 ? 0 : buf + 1;
-        }
-        lds_barrier();
-        if (tid < 3 * RB) {
-            const int k = tid / RB, r = tid % RB;
-            float sum = 0.f;
-#pragma unroll
-            for (int x = 0; x < NW; x++) sum += part[(NBATCH - 1) & 1][k][x][r];
-            tot[k][(NBATCH - 1) * RB + r] = sum;
-        }
-        lds_barrier();
-        }
-
-        // The snapshot is stored here, behind the batches: the memory counter is in order, so stores issued ahead of the
-        // batches' requests would stand between every batch and its wait; from here they drain while the selection runs.
-        if (a.want_out) {
+        auto store_snapshot = [&]() {
             const size_t sj = (size_t)si * a.S + (j - a.jb);
             uint16_t *s16 = reinterpret_cast<uint16_t *>(a.snapH) + sj * (2 * DF * DH);
 #pragma unroll
@@ -1635,7 +1748,39 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
 #pragma unroll
             for (int x = 0; x < NSP; x++)
                 if (tid + NTH * x < LAM) a.snapG[sj * LAM + tid + NTH * x] = sprow_ld[x];
+        };
+        int nown = NE;   // candidates [0, nown) are scored here, the others by helpers
+        if constexpr (SHARED) {
+            store_snapshot();
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+            __syncthreads();                      // the snapshot and the last chunk's compaction are complete
+            if (tid == 0) {
+                const int nh = agent_load(&sh->joined);
+                const int bh = max(1, (NBATCH - SHARE_LEAD + nh) / (nh + 1)), used = min(nh, (NBATCH - 1) / bh);
+                if (used > 0) {
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    agent_store(&sh->go, ((unsigned long long)(j - a.jb + 1) << 16) | (unsigned long long)(bh << 8) | (unsigned long long)used);
+                }
+                nh_s = used; bh_s = bh;
+            }
+            __syncthreads();
+            nown = NE - nh_s * bh_s * RB;
+            want += nh_s;
         }
+        if (!SCORED && LAM > 0) wide_score_batches<DH, DF>(pool, s_l, dn_l, tot, part, Ahi, Alo, 0, SHARED ? nown / RB : NBATCH, tid, phirow, vrow);
+        if constexpr (SHARED) {
+            if (nown < NE) {
+                if (tid == 0) {
+                    while (agent_load(&sh->done) != want) __builtin_amdgcn_s_sleep(1);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                }
+                __syncthreads();
+            }
+        }
+
+        // The snapshot is stored here, behind the batches: the memory counter is in order, so stores issued ahead of the
+        // batches' requests would stand between every batch and its wait; from here they drain while the selection runs.
+        if (!SHARED && a.want_out) store_snapshot();
 
         // ---- 3. selection: the nf candidates with the smallest squared error are folded (order: score descending,
         // token index ascending, the first lambda stay).  The squared error is |P|^2 / (phi.s)^2 - 2 P.v / (phi.s) + |v|^2
@@ -1657,9 +1802,8 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
             }
         } else {
         for (int e = tid; e < NE; e += NTH) {
-            const float dn = dn_l[e], rd = dn > 0.f ? __builtin_amdgcn_rcpf(dn) : 0.f;
-            const float sq = fmaxf(fmaf(rd * rd, tot[0][e], fmaf(-2.0f * rd, tot[1][e], tot[2][e])), 0.f);
-            skey[e] = (e < LAM ? e < spc : e < LAM + cl) ? __float_as_uint(sq) & 0x7FFFFFFFu : 0xFFFFFFFFu;
+            const uint32_t sq = SHARED && e >= nown ? agent_load(&score_x[e]) : sq_bits(e);
+            skey[e] = (e < LAM ? e < spc : e < LAM + cl) ? sq : 0xFFFFFFFFu;
         }
         }
         lds_barrier();
@@ -1852,7 +1996,10 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
         for (int mt = 0; mt < NMT; mt++) *reinterpret_cast<f32x4 *>(hrow + 16 * mt) = hacc[mt];
         for (int x = tid0; x < DF; x += NTH) sg[x] = s_l[x];
     }
-    if (tid0 == 0) a.next_j[si] = j;
+    if (tid0 == 0) {
+        a.next_j[si] = j;
+        if (SHARED) agent_store(&sh->go, GO_END);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------

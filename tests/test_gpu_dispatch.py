@@ -97,3 +97,25 @@ def test_step_with_sequences_at_different_stages(d, D, eta, lam, kw):
             assert P.row_rel_err(out[b:b + 1].cpu().numpy(), o1.cpu().numpy().astype(np.float64)).max() < 1e-5, (i, b)
             for nm in names:
                 assert torch.equal(getattr(batch, nm)[b], getattr(lay, nm)[0]), (i, b, nm)
+
+
+@pytest.mark.parametrize("B,Hkv,d,D,eta,lam,T,limit,kw", [
+    (1, 1, 128, 256, 64, 1024, 1600, None, {}), (1, 3, 64, 256, 128, 512, 1111, None, {}), (2, 8, 128, 128, 64, 512, 1024, None, dict(prefill_overlap=1)),
+    (4, 8, 128, 256, 64, 512, 960, None, {}), (1, 2, 64, 128, 64, 768, 1000, 0, {}), (2, 8, 128, 256, 64, 1024, 1537, 40 << 20, dict(phi_kind=1)),
+    (2, 4, 128, 256, 128, 256, 1500, None, dict(prefill_overlap=1)), (2, 32, 128, 256, 64, 512, 800, None, {})])
+def test_evolution_shared_among_workgroups(B, Hkv, d, D, eta, lam, T, limit, kw):
+    """With outputs and few streams the candidates' scores come from several workgroups per stream; an update-only call
+    stays on one. The same instructions on the same operands: the memories agree bit for bit, over several launches and
+    workspace passes, a ragged last chunk and a second call that starts with a full cache."""
+    sh = wl.Shape("shared", "bf16", B, 2 * Hkv, Hkv, d, D, T=0, eta=eta, lam=lam, C=64, seed=0)
+    q, k, v, Wq, Wk = case_inputs(90 + d + D + lam, B, 2 * Hkv, Hkv, d, D, T + 130, wscale=0.5 if kw.get("phi_kind") else 1.0)
+    dq, dk, dv, dWq, dWk = P.to_dev(q, "bf16"), P.to_dev(k, "bf16"), P.to_dev(v, "bf16"), P.w_to_dev(Wq, "bf16"), P.w_to_dev(Wk, "bf16")
+    one, many = P.make_layer(sh, **kw), P.make_layer(sh, **kw)
+    for a, b in ((0, T), (T, T + 130)):
+        q1, k1, v1 = (x[:, :, a:b].contiguous() for x in (dq, dk, dv))
+        print("shared", B, Hkv, d, D, eta, lam, a, b, flush=True)
+        _, t_many = many.prefill(q1, k1, v1, dWq, dWk, trace=True, workspace_limit=limit)
+        _, t_one = one.prefill(None, k1, v1, dWq, dWk, trace=True, workspace_limit=limit)
+        assert torch.equal(t_many, t_one)
+        for nm in FIELDS:
+            assert torch.equal(getattr(one, nm), getattr(many, nm)), (a, nm)
