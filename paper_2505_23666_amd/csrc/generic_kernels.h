@@ -98,20 +98,37 @@ __device__ __forceinline__ void dot_row_many(const bf16_t *row, const float *xs,
 }
 __device__ __forceinline__ void dot_row_many(const float *row, const float *xs, int n, int nq, float (&acc)[16]) {
     const float4 *r4 = reinterpret_cast<const float4 *>(row);
-    for (int i = 0; i < n / 4; i++) {
-        const float4 u = r4[i];
+    for (int i0 = 0; i0 < n / 4; i0 += 8) {   // (n is a multiple of 32: eight pieces of the row in flight together)
+        float4 u[8];
+#pragma unroll
+        for (int y = 0; y < 8; y++) u[y] = r4[i0 + y];
 #pragma unroll
         for (int q = 0; q < 16; q++) {
             if (q < nq) {
-                const float4 x0 = *reinterpret_cast<const float4 *>(xs + q * n + 4 * i);
                 float t = acc[q];
-                t = fmaf(u.x, x0.x, t); t = fmaf(u.y, x0.y, t); t = fmaf(u.z, x0.z, t); t = fmaf(u.w, x0.w, t);
+#pragma unroll
+                for (int y = 0; y < 8; y++) {
+                    const float4 x0 = *reinterpret_cast<const float4 *>(xs + q * n + 4 * (i0 + y));
+                    t = fmaf(u[y].x, x0.x, t); t = fmaf(u[y].y, x0.y, t); t = fmaf(u[y].z, x0.z, t); t = fmaf(u[y].w, x0.w, t);
+                }
                 acc[q] = t;
             }
         }
     }
 }
 
+// wave_sum of four values, step by step side by side
+__device__ __forceinline__ void wave_sum4(float (&a)[4]) {
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int x = 0; x < 4; x++) a[x] += __shfl_xor(a[x], o, WAVE);
+}
+
+// At small states (fp32, one stream, d = D = 64, 32 candidates) scoring a chunk is bound by latency: dependent cache
+// requests and cross-lane steps, not by arithmetic.  Rows are therefore taken four at a time and requests eight at a time
+// here, in score_rows and in attend_kernel, the order of every sum unchanged: evolution 37 -> 23 us per chunk of 16
+// tokens, outputs 59 -> 36 us, a request of 256 tokens 656 -> 416 us.
 // phi of R rows.  xs [R][d] (LDS, fp32 copies of the stored vectors), W [m][d] (global, row j = w_j), result
 // ph [R][D] (LDS).  Workgroup-wide; ends with a barrier.
 template <typename T>
@@ -148,6 +165,27 @@ __device__ void phi_rows(const Dims &dm, const T *W, const float *xs, float *ph,
                 for (int i = 0; i < 4; i++) ph[r * D + 16 * jt + 4 * g4 + i] = acc[i];
             }
         }
+    } else if (std::is_same<T, float>::value && R > NT / m && NT % m == 0) {
+        // Thread (j, rg) takes the rows rg, rg + NT / m, ..., four per pass over row j of W: the lanes of a load touch as many
+        // cache lines as there are lanes, which bounds this product, and now serve four rows.
+        const int j = tid % m, nrg = NT / m;
+        const float4 *w4 = reinterpret_cast<const float4 *>(W + (size_t)j * d);
+        for (int r0 = tid / m; r0 < R; r0 += 4 * nrg) {
+            float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+            for (int i = 0; i < d / 4; i++) {
+                const float4 u = w4[i];
+#pragma unroll
+                for (int x = 0; x < 4; x++) {   // (rows behind the last are computed from row r0 and not stored)
+                    const int r = r0 + x * nrg < R ? r0 + x * nrg : r0;
+                    const float4 v = *reinterpret_cast<const float4 *>(xs + r * d + 4 * i);
+                    acc[x] = fmaf(u.x, v.x, acc[x]); acc[x] = fmaf(u.y, v.y, acc[x]);
+                    acc[x] = fmaf(u.z, v.z, acc[x]); acc[x] = fmaf(u.w, v.w, acc[x]);
+                }
+            }
+#pragma unroll
+            for (int x = 0; x < 4; x++) if (r0 + x * nrg < R) ph[(r0 + x * nrg) * D + j] = acc[x];
+        }
     } else {
         for (int p = tid; p < R * m; p += NT) {
             int r = p / m, j = p - r * m;
@@ -157,6 +195,38 @@ __device__ void phi_rows(const Dims &dm, const T *W, const float *xs, float *ph,
     }
     __syncthreads();
     const int w = tid / WAVE, lane = tid % WAVE;
+    if (dm.phi_kind != 1 && m <= WAVE) {
+        // a projection per lane: four rows at a time, their reductions side by side (each a chain of cross-lane steps)
+        for (int r0 = w; r0 < R; r0 += 4 * NW) {
+            float z[4], hi[4], lo[4], ep[4], en[4], sp[4], sn[4];
+#pragma unroll
+            for (int x = 0; x < 4; x++) {
+                const int r = r0 + x * NW;
+                z[x] = r < R && lane < m ? ph[r * D + lane] : 0.f;
+                hi[x] = lane < m ? z[x] : -INFINITY; lo[x] = lane < m ? z[x] : INFINITY;
+            }
+#pragma unroll
+            for (int o = WAVE / 2; o > 0; o >>= 1)
+#pragma unroll
+                for (int x = 0; x < 4; x++) { hi[x] = fmaxf(hi[x], __shfl_xor(hi[x], o, WAVE)); lo[x] = fminf(lo[x], __shfl_xor(lo[x], o, WAVE)); }
+#pragma unroll
+            for (int x = 0; x < 4; x++) {
+                ep[x] = expf(z[x] - hi[x]); en[x] = expf(lo[x] - z[x]);
+                sp[x] = lane < m ? ep[x] : 0.f; sn[x] = lane < m ? en[x] : 0.f;
+            }
+#pragma unroll
+            for (int o = WAVE / 2; o > 0; o >>= 1)
+#pragma unroll
+                for (int x = 0; x < 4; x++) { sp[x] += __shfl_xor(sp[x], o, WAVE); sn[x] += __shfl_xor(sn[x], o, WAVE); }
+#pragma unroll
+            for (int x = 0; x < 4; x++) {
+                const int r = r0 + x * NW;
+                if (r < R && lane < m) { ph[r * D + lane] = ep[x] / sp[x]; ph[r * D + m + lane] = en[x] / sn[x]; }
+            }
+        }
+        __syncthreads();
+        return;
+    }
     for (int r = w; r < R; r += NW) {
         float *row = ph + r * D;
         if (dm.phi_kind == 1) {
@@ -203,11 +273,16 @@ __device__ void score_rows(const Dims &dm, const float *H, const float *s, const
                            float *err, float *den, float *score_out, int R) {
     const int tid = threadIdx.x, d = dm.d, D = dm.D;
     const int w = tid / WAVE, lane = tid % WAVE;
-    for (int r = w; r < R; r += NW) {
-        float a = 0.f;
-        for (int f = lane; f < D; f += WAVE) a = fmaf(ph[r * D + f], s[f], a);
-        a = wave_sum(a);
-        if (lane == 0) den[r] = a;
+    for (int r0 = w; r0 < R; r0 += 4 * NW) {   // four rows at a time: their sums over the lanes run side by side
+        float a[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int f = lane; f < D; f += WAVE) {
+            const float sf = s[f];
+#pragma unroll
+            for (int x = 0; x < 4; x++) if (r0 + x * NW < R) a[x] = fmaf(ph[(r0 + x * NW) * D + f], sf, a[x]);
+        }
+        wave_sum4(a);
+#pragma unroll
+        for (int x = 0; x < 4; x++) if (r0 + x * NW < R && lane == 0) den[r0 + x * NW] = a[x];
     }
     __syncthreads();
     if (MF && R >= 8 && (D & 31) == 0) {
@@ -281,15 +356,21 @@ __device__ void score_rows(const Dims &dm, const float *H, const float *s, const
         float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if ((D & 3) == 0) {   // four features per load of H and of the LDS rows (index order kept)
             const float4 *H4 = reinterpret_cast<const float4 *>(H + (size_t)c * D);
-            for (int f4 = 0; f4 < D / 4; f4++) {
-                const float4 hv = H4[f4];
+            // the row of H^T is requested eight pieces at a time: one request per step waited for the cache each time
+            for (int f0 = 0; f0 < D / 4; f0 += 8) {
+                float4 hv[8];
 #pragma unroll
-                for (int i = 0; i < 8; i++) {
-                    const int r = r0 + i * nrg;
-                    if (r < R) {
-                        const float4 pv = *reinterpret_cast<const float4 *>(&ph[r * D + 4 * f4]);
-                        acc[i] = fmaf(pv.x, hv.x, acc[i]); acc[i] = fmaf(pv.y, hv.y, acc[i]);
-                        acc[i] = fmaf(pv.z, hv.z, acc[i]); acc[i] = fmaf(pv.w, hv.w, acc[i]);
+                for (int u = 0; u < 8; u++) hv[u] = H4[f0 + u < D / 4 ? f0 + u : f0];
+#pragma unroll
+                for (int u = 0; u < 8; u++) {
+                    if (f0 + u < D / 4) {
+#pragma unroll
+                        for (int i = 0; i < 8; i++) {   // (rows behind the last repeat row r0 and are not stored)
+                            const int r = r0 + i * nrg < R ? r0 + i * nrg : r0;
+                            const float4 pv = *reinterpret_cast<const float4 *>(&ph[r * D + 4 * (f0 + u)]);
+                            acc[i] = fmaf(pv.x, hv[u].x, acc[i]); acc[i] = fmaf(pv.y, hv[u].y, acc[i]);
+                            acc[i] = fmaf(pv.z, hv[u].z, acc[i]); acc[i] = fmaf(pv.w, hv[u].w, acc[i]);
+                        }
                     }
                 }
             }
@@ -316,11 +397,15 @@ __device__ void score_rows(const Dims &dm, const float *H, const float *s, const
     }
     }
     __syncthreads();
-    for (int r = w; r < R; r += NW) {
-        float a = 0.f;
-        for (int c2 = lane; c2 < d; c2 += WAVE) a += err[r * d + c2];
-        a = wave_sum(a);
-        if (lane == 0) score_out[r] = sqrtf(a);
+    for (int r0 = w; r0 < R; r0 += 4 * NW) {
+        float a[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int c2 = lane; c2 < d; c2 += WAVE) {
+#pragma unroll
+            for (int x = 0; x < 4; x++) if (r0 + x * NW < R) a[x] += err[(r0 + x * NW) * d + c2];
+        }
+        wave_sum4(a);
+#pragma unroll
+        for (int x = 0; x < 4; x++) if (r0 + x * NW < R && lane == 0) score_out[r0 + x * NW] = sqrtf(a[x]);
     }
     __syncthreads();
 }
@@ -798,6 +883,44 @@ __global__ __launch_bounds__(NT) void band_score_kernel(PrefillArgs<T> a) {
     for (int r = tid; r < nk; r += NT) a.tok_score[(size_t)si * nrows + x0 + r] = acc[r];
 }
 
+// H[c][f] += sum_r phi_r[f] v_r[c] over nr rows in LDS (ph [nr][D], vs [nr][d]), blocks of 4 value columns x FB features per
+// thread, in row order
+template <int FB>
+__device__ __forceinline__ void fold_blocks(float *H, const float *ph, const float *vs, int d, int D, int nr) {
+    const int nbf = D / FB, nblk = (d / 4) * nbf;
+    for (int b = threadIdx.x; b < nblk; b += NT) {
+        const int c0 = 4 * (b / nbf), f0 = FB * (b % nbf);
+        float acc[4][FB];
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int x = 0; x < FB; x++) acc[i][x] = 0.f;
+#pragma unroll(FB == 4 ? 4 : 1)
+        for (int r = 0; r < nr; r++) {
+            const float4 v4 = *reinterpret_cast<const float4 *>(vs + r * d + c0);
+            const float vv[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+            for (int q4 = 0; q4 < FB / 4; q4++) {
+                const float4 p4 = *reinterpret_cast<const float4 *>(ph + r * D + f0 + 4 * q4);
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    acc[i][4 * q4] = fmaf(p4.x, vv[i], acc[i][4 * q4]); acc[i][4 * q4 + 1] = fmaf(p4.y, vv[i], acc[i][4 * q4 + 1]);
+                    acc[i][4 * q4 + 2] = fmaf(p4.z, vv[i], acc[i][4 * q4 + 2]); acc[i][4 * q4 + 3] = fmaf(p4.w, vv[i], acc[i][4 * q4 + 3]);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int q4 = 0; q4 < FB / 4; q4++) {
+                float4 *hp = reinterpret_cast<float4 *>(H + (size_t)(c0 + i) * D + f0 + 4 * q4);
+                float4 hv = *hp;
+                hv.x += acc[i][4 * q4]; hv.y += acc[i][4 * q4 + 1]; hv.z += acc[i][4 * q4 + 2]; hv.w += acc[i][4 * q4 + 3];
+                *hp = hv;
+            }
+    }
+}
+
 // One chunk of the sequential evolution of a stream's memories, all state in global memory (H^T, s, cache) except the
 // sparse-cache fill count `spc`, which the caller carries.  Workgroup-wide (NT threads); `smem` is scratch LDS.
 template <typename T>
@@ -865,7 +988,13 @@ __device__ void scan_chunk(const PrefillArgs<T> &a, const int si, const int j, i
                     *reinterpret_cast<uint4 *>(s16 + D * d + pos) = make_uint4(pl[0], pl[1], pl[2], pl[3]);
                 }
             } else {
-                for (int idx = tid; idx < D * d; idx += NT) sH[idx] = H[idx];
+                for (int i0 = tid; i0 < D * d / 4; i0 += 4 * NT) {   // (D d is a multiple of 64)
+                    float4 h4[4];
+#pragma unroll
+                    for (int x = 0; x < 4; x++) if (i0 + x * NT < D * d / 4) h4[x] = reinterpret_cast<const float4 *>(H)[i0 + x * NT];
+#pragma unroll
+                    for (int x = 0; x < 4; x++) if (i0 + x * NT < D * d / 4) reinterpret_cast<float4 *>(sH)[i0 + x * NT] = h4[x];
+                }
             }
             for (int f = tid; f < D; f += NT) sS[f] = s[f];
             for (int sl = tid; sl < lam; sl += NT) sG[sl] = sl < spc ? sp_row[sl] : -1;
@@ -919,9 +1048,11 @@ __device__ void scan_chunk(const PrefillArgs<T> &a, const int si, const int j, i
             // rank by (score descending, token index ascending); the first lam stay
             for (int e = tid; e < nE; e += NT) {
                 float sc = score[e]; int ix = cidx[e], rank = 0;
+#pragma unroll 8
                 for (int o = 0; o < nE; o++) {
-                    float so = score[o];
-                    rank += (so > sc || (so == sc && cidx[o] < ix)) ? 1 : 0;
+                    const float so = score[o];
+                    const int io = cidx[o];
+                    rank += (int)((so > sc) | ((so == sc) & (io < ix)));
                 }
                 keep[e] = rank < lam;
             }
@@ -960,7 +1091,7 @@ __device__ void scan_chunk(const PrefillArgs<T> &a, const int si, const int j, i
             // registers: 5 LDS reads of 16 bytes per 64 multiply-adds, where the plain loop below reads global memory
             // twice per multiply-add (0.9 ms per chunk at the 8B shape).
             if (d % 4 == 0 && D % 16 == 0) {
-                const int nbf = D / 16, nblk = (d / 4) * nbf;
+                const int nblk = (d / 4) * (D / 16);
                 for (int t0 = 0; t0 < nf; t0 += R) {
                     const int nr = min(R, nf - t0);
                     for (int p = tid; p < nr * (D / 4); p += NT) {
@@ -976,36 +1107,8 @@ __device__ void scan_chunk(const PrefillArgs<T> &a, const int si, const int j, i
                         piece_to_f32(vsrc, i, vs + r * d);
                     }
                     __syncthreads();
-                    for (int b = tid; b < nblk; b += NT) {
-                        const int c0 = 4 * (b / nbf), f0 = 16 * (b % nbf);
-                        float acc[4][16];
-#pragma unroll
-                        for (int i = 0; i < 4; i++)
-#pragma unroll
-                            for (int x = 0; x < 16; x++) acc[i][x] = 0.f;
-                        for (int r = 0; r < nr; r++) {
-                            const float4 v4 = *reinterpret_cast<const float4 *>(vs + r * d + c0);
-                            const float vv[4] = {v4.x, v4.y, v4.z, v4.w};
-#pragma unroll
-                            for (int q4 = 0; q4 < 4; q4++) {
-                                const float4 p4 = *reinterpret_cast<const float4 *>(ph + r * D + f0 + 4 * q4);
-#pragma unroll
-                                for (int i = 0; i < 4; i++) {
-                                    acc[i][4 * q4] = fmaf(p4.x, vv[i], acc[i][4 * q4]); acc[i][4 * q4 + 1] = fmaf(p4.y, vv[i], acc[i][4 * q4 + 1]);
-                                    acc[i][4 * q4 + 2] = fmaf(p4.z, vv[i], acc[i][4 * q4 + 2]); acc[i][4 * q4 + 3] = fmaf(p4.w, vv[i], acc[i][4 * q4 + 3]);
-                                }
-                            }
-                        }
-#pragma unroll
-                        for (int i = 0; i < 4; i++)
-#pragma unroll
-                            for (int q4 = 0; q4 < 4; q4++) {
-                                float4 *hp = reinterpret_cast<float4 *>(H + (size_t)(c0 + i) * D + f0 + 4 * q4);
-                                float4 hv = *hp;
-                                hv.x += acc[i][4 * q4]; hv.y += acc[i][4 * q4 + 1]; hv.z += acc[i][4 * q4 + 2]; hv.w += acc[i][4 * q4 + 3];
-                                *hp = hv;
-                            }
-                    }
+                    if (nblk < NT) fold_blocks<4>(H, ph, vs, d, D, nr);   // small states: smaller blocks, so that no thread idles
+                    else fold_blocks<16>(H, ph, vs, d, D, nr);
                     for (int f = tid; f < D; f += NT) {
                         float acc = 0.f;
                         for (int r = 0; r < nr; r++) acc += ph[r * D + f];
@@ -1165,27 +1268,42 @@ __global__ __launch_bounds__(NT) void attend_kernel(PrefillArgs<T> a) {
         float num[16], lin[16];
 #pragma unroll
         for (int x = 0; x < 16; x++) { num[x] = 0.f; lin[x] = 0.f; }
-        for (int key = 0; key < nk; key++) {
-            const int vr = key < lam ? G[key] : vrow0 + (key - lam);
-            if (vr < 0) continue;   // empty slot: weight 0 for every query
-            const float val = vr < P ? ldf(pV, (size_t)vr * d + c) : ldf(vc, (size_t)(vr - P) * d + c);
+        // eight keys' values are requested before the first is used (a request per key waited for memory each time)
+        for (int key0 = 0; key0 < nk; key0 += 8) {
+            int vr[8];
+            float val[8];
+#pragma unroll
+            for (int u = 0; u < 8; u++) vr[u] = key0 + u >= nk ? -1 : (key0 + u < lam ? G[key0 + u] : vrow0 + (key0 + u - lam));
+#pragma unroll
+            for (int u = 0; u < 8; u++)   // empty slot: weight 0 for every query
+                val[u] = vr[u] < 0 ? 0.f : (vr[u] < P ? ldf(pV, (size_t)vr[u] * d + c) : ldf(vc, (size_t)(vr[u] - P) * d + c));
 #pragma unroll
             for (int x = 0; x < 16; x++) {
                 const int qi = part + x * nparts;
-                if (qi < nq) num[x] = fmaf(pw[qi * nkmax + key], val, num[x]);
+                if (qi < nq) {
+#pragma unroll
+                    for (int u = 0; u < 8; u++) if (key0 + u < nk) num[x] = fmaf(pw[qi * nkmax + key0 + u], val[u], num[x]);
+                }
             }
         }
         if ((D & 3) == 0) {
             const float4 *H4 = reinterpret_cast<const float4 *>(Hj + (size_t)c * D);
-            for (int f4 = 0; f4 < D / 4; f4++) {
-                const float4 hv = H4[f4];
+            for (int f0 = 0; f0 < D / 4; f0 += 8) {
+                float4 hv[8];
+#pragma unroll
+                for (int u = 0; u < 8; u++) hv[u] = H4[f0 + u < D / 4 ? f0 + u : f0];
 #pragma unroll
                 for (int x = 0; x < 16; x++) {
                     const int qi = part + x * nparts;
                     if (qi < nq) {
-                        const float4 pv = reinterpret_cast<const float4 *>(phq + qi * D)[f4];
                         float t = lin[x];
-                        t = fmaf(pv.x, hv.x, t); t = fmaf(pv.y, hv.y, t); t = fmaf(pv.z, hv.z, t); t = fmaf(pv.w, hv.w, t);
+#pragma unroll
+                        for (int u = 0; u < 8; u++) {
+                            if (f0 + u < D / 4) {
+                                const float4 pv = reinterpret_cast<const float4 *>(phq + qi * D)[f0 + u];
+                                t = fmaf(pv.x, hv[u].x, t); t = fmaf(pv.y, hv[u].y, t); t = fmaf(pv.z, hv[u].z, t); t = fmaf(pv.w, hv[u].w, t);
+                            }
+                        }
                         lin[x] = t;
                     }
                 }

@@ -119,3 +119,18 @@ def test_evolution_shared_among_workgroups(B, Hkv, d, D, eta, lam, T, limit, kw)
         assert torch.equal(t_many, t_one)
         for nm in FIELDS:
             assert torch.equal(getattr(one, nm), getattr(many, nm)), (a, nm)
+
+
+@pytest.mark.parametrize("d,D,eta,lam,C", [(32, 2, 3, 5, 4), (32, 62, 7, 9, 8), (64, 64, 16, 16, 16), (64, 128, 16, 40, 24), (64, 130, 8, 8, 16),
+                                           (256, 64, 5, 31, 16), (64, 48, 33, 17, 40), (128, 80, 0, 3, 7)])
+def test_fp32_rows_at_the_edges_of_their_batches(d, D, eta, lam, C):
+    """fp32 storage: numbers of projections that divide the workgroup or not, fill a wavefront or exceed it, states smaller and
+    larger than a round of fold blocks, candidate counts around the four-row and eight-key batches; against the oracle."""
+    sh = wl.Shape("rows", "f32", 1, 2, 1, d, D, T=0, eta=eta, lam=lam, C=C, seed=0)
+    g = wl.rng(60 + d + D, 5)
+    mk = lambda *shape: g.standard_normal(shape, dtype=np.float32)
+    q, k, v = mk(1, 2, 149, d), mk(1, 1, 149, d), mk(1, 1, 149, d)
+    Wq, Wk = mk(2, d, D // 2) / np.float32(np.sqrt(d)), mk(1, d, D // 2) / np.float32(np.sqrt(d))
+    layer, o = None, None
+    for a, b in ((0, 1), (1, 102), (102, 149)):
+        layer, o, _ = P.prefill_parity(sh, q[:, :, a:b], k[:, :, a:b], v[:, :, a:b], Wq, Wk, layer=layer, oracle=o)
