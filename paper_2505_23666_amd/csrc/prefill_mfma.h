@@ -514,10 +514,9 @@ __global__ __launch_bounds__(256, 2) void attend_wide_kernel(generic::PrefillArg
 // Sequential state evolution of the prefill (paper Sec. 3 "Chunkwise Inference": after each chunk the
 // oldest chunk leaves the window; it and the sparse cache are scored by self-recall error, the top
 // lambda stay, the rest are folded) for the 8B head shape: one workgroup of eight wavefronts per
-// (sequence, kv head), persistent over the regular chunks of a pass (a full chunk, a full window behind
-// it, a full cache).  Chunks before the first regular one (cache still filling, first chunks of a
-// sequence) and a ragged last chunk are handled by the generic kernel in launches of their own; the
-// chunk position is handed over in a per-stream counter.
+// (sequence, kv head), persistent over the scored chunks of a pass, a first one with an incomplete cache and a ragged
+// last one included (the chunks before them, which fill window and cache, have a closed form); the chunk
+// position is handed from launch to launch in a per-stream counter.
 //
 // H^T lives in registers for the whole pass (wavefront w owns rows 16w .. 16w+15 as fp32, re-split
 // into bf16 high + low MFMA operands once per chunk); s lives in LDS.  With lambda <= 128 the features
@@ -1328,7 +1327,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
 // ---------------------------------------------------------------------------------------------
 // State evolution of the prefill for any window and sparse budget (multiples of 64, read from the arguments) and 128 or
 // 256 features: the paper's own models use twice the head dimension as feature dimension and windows / budgets of
-// 128 .. 1024 in the long-context runs (Sec. 4).  Same five steps per regular chunk as scan_fast_kernel (snapshot,
+// 128 .. 1024 in the long-context runs (Sec. 4).  Same five steps per scored chunk as scan_fast_kernel (snapshot,
 // self-recall error of the lambda + 64 candidates, selection of the 64 to fold, fold, compaction; Sec. 3.1 - 3.2), laid
 // out for a candidate set that does not fit LDS:
 //   * phi of every row is computed chunk-parallel beforehand (phi_wide_kernel): the pairs that leave the window in chunk
@@ -1398,8 +1397,6 @@ __global__ __launch_bounds__(256) void phi_wide_kernel(generic::PrefillArgs<bf16
     }
 }
 
-// Recall errors of the candidate batches [b0, b1) (b0 < b1): |P|^2, P.v, |v|^2 over all value columns -> tot, phi(k).s ->
-// dn_l.  phirow(e), vrow(e): feature and value row of candidate e.  Ahi, Alo: this wavefront's 16 rows of H^T.
 template <int DH, int DF>
 struct WideScan {
     static constexpr int C = 64, NW = DH / 16, NTH = 64 * NW, KF = DF / 32, NMT = DF / 16, PR = DH / 8, FR = 2 * DF, PP = DF / 8;
@@ -1411,7 +1408,32 @@ struct WideScan {
     static constexpr int NEMAX = 1024 + C, NKMAX = NEMAX / 64;
     static constexpr int BUF = RB * FR + RB * DH;                 // 16-bit elements of one batch buffer: features, then values
 };
+// requests of batch b into buffer buf: 1 KB per instruction, lane l fills bytes 16 l ..; a row's 16-byte pieces are
+// XOR-swizzled with the row number, so a lane fetches the piece that belongs in its position
 template <int DH, int DF, typename FPhi, typename FVal>
+__device__ __forceinline__ void wide_issue(uint16_t *pool, int b, int buf, int tid, FPhi phirow, FVal vrow) {
+    using L = WideScan<DH, DF>;
+    constexpr int NW = L::NW, PR = L::PR, FR = L::FR, RB = L::RB, VPB = L::VPB, BUF = L::BUF;
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint16_t *PBb = pool + buf * BUF, *VBb = PBb + RB * FR;
+    const int e0 = b * RB;
+#pragma unroll
+    for (int it = 0; it < RB * FR / 512 / NW; it++) {
+        const int i = w + NW * it, g = 512 * i + 8 * lane, row = g / FR, pt = (g % FR) / DF, slot = (g % DF) >> 3;
+        const uint16_t *src = phirow(e0 + row) + pt * DF + ((slot ^ (row & 15)) << 3);
+        lds_dma16(src, PBb + 512 * i);
+    }
+#pragma unroll
+    for (int it = 0; it < VPB; it++) {
+        const int i = w + NW * it, g = 512 * i + 8 * lane, row = g / DH, slot = (g % DH) >> 3;
+        const bf16_t *src = vrow(e0 + row) + ((slot ^ (row & (PR - 1))) << 3);
+        lds_dma16(src, VBb + 512 * i);
+    }
+}
+// Recall errors of the candidate batches [b0, b1) (b0 < b1): |P|^2, P.v, |v|^2 over all value columns -> tot, phi(k).s ->
+// dn_l.  phirow(e), vrow(e): feature and value row of candidate e.  Ahi, Alo: this wavefront's 16 rows of H^T.  ISSUED: the
+// first NBUF - 1 batches of [b0, b1) have been requested.
+template <int DH, int DF, bool ISSUED = false, typename FPhi, typename FVal>
 __device__ __forceinline__ void wide_score_batches(uint16_t *pool, const float *s_l, float *dn_l, float (*tot)[WideScan<DH, DF>::NEMAX],
                                                    float (*part)[3][DH / 16][WideScan<DH, DF>::RB], const bf16x8 (&Ahi)[DF / 32],
                                                    const bf16x8 (&Alo)[DF / 32], int b0, int b1, int tid, FPhi phirow, FVal vrow) {
@@ -1419,26 +1441,11 @@ __device__ __forceinline__ void wide_score_batches(uint16_t *pool, const float *
     constexpr int NW = L::NW, NTH = L::NTH, KF = L::KF, PR = L::PR, FR = L::FR, PP = L::PP, RB = L::RB, TB = L::TB, NBUF = L::NBUF,
                   VPB = L::VPB, LPB = L::LPB, BUF = L::BUF;
     const int lane = tid & 63, r16 = lane & 15, g4 = lane >> 4, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // requests of batch b into buffer buf: 1 KB per instruction, lane l fills bytes 16 l ..; a row's 16-byte pieces are
-    // XOR-swizzled with the row number, so a lane fetches the piece that belongs in its position
-    auto issue = [&](int b, int buf) {
-        uint16_t *PBb = pool + buf * BUF, *VBb = PBb + RB * FR;
-        const int e0 = b * RB;
-#pragma unroll
-        for (int it = 0; it < RB * FR / 512 / NW; it++) {
-            const int i = w + NW * it, g = 512 * i + 8 * lane, row = g / FR, pt = (g % FR) / DF, slot = (g % DF) >> 3;
-            const uint16_t *src = phirow(e0 + row) + pt * DF + ((slot ^ (row & 15)) << 3);
-            lds_dma16(src, PBb + 512 * i);
-        }
-#pragma unroll
-        for (int it = 0; it < VPB; it++) {
-            const int i = w + NW * it, g = 512 * i + 8 * lane, row = g / DH, slot = (g % DH) >> 3;
-            const bf16_t *src = vrow(e0 + row) + ((slot ^ (row & (PR - 1))) << 3);
-            lds_dma16(src, VBb + 512 * i);
-        }
-    };
+    auto issue = [&](int b, int buf) { wide_issue<DH, DF>(pool, b, buf, tid, phirow, vrow); };
+    if (!ISSUED) {
 #pragma unroll
     for (int b = 0; b < NBUF - 1; b++) if (b0 + b < b1) issue(b0 + b, b);
+    }
 
     // ---- 2. recall error of the candidates, batch by batch
     int buf = 0;
@@ -1751,6 +1758,10 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
         };
         int nown = NE;   // candidates [0, nown) are scored here, the others by helpers
         if constexpr (SHARED) {
+            // the first batches travel while the snapshot drains (lambda + 64 candidates are at least NBUF batches): 1.93 ->
+            // 1.87 ms for 2 x 4096 tokens at eta 512 / lambda 1024, 1.01 -> 0.99 for 4 x 2048 at eta = lambda = 256
+#pragma unroll
+            for (int b = 0; b < NBUF - 1; b++) wide_issue<DH, DF>(pool, b, b, tid, phirow, vrow);
             store_snapshot();
             __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
             __syncthreads();                      // the snapshot and the last chunk's compaction are complete
@@ -1767,7 +1778,7 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
             nown = NE - nh_s * bh_s * RB;
             want += nh_s;
         }
-        if (!SCORED && LAM > 0) wide_score_batches<DH, DF>(pool, s_l, dn_l, tot, part, Ahi, Alo, 0, SHARED ? nown / RB : NBATCH, tid, phirow, vrow);
+        if (!SCORED && LAM > 0) wide_score_batches<DH, DF, SHARED>(pool, s_l, dn_l, tot, part, Ahi, Alo, 0, SHARED ? nown / RB : NBATCH, tid, phirow, vrow);
         if constexpr (SHARED) {
             if (nown < NE) {
                 if (tid == 0) {
