@@ -597,10 +597,10 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                 // (a compile-time shape whose cache does not stay in LDS takes its features the run-time way)
                 const bool big = !wide && c->sparse_budget > 128;
                 // Few streams: further workgroups score shares of the candidates (prefill_mfma.h, WideShare).  A chunk costs a
-                // stream's workgroup about 12 us + 2 us per batch alone and an exchange of about 7 us when shared, so a helper
+                // stream's workgroup about 12 us + 2 us per batch alone and an exchange of about 7 us (by difference) when shared, so a helper
                 // is worth its compute unit from about six batches on, and at most half of the compute units go to the
                 // evolution, the rest to the outputs beside it: 2 x 4096 tokens at eta 512 / lambda 1024 3.70 ms alone, 2.02 with
-                // 3 helpers per stream, 1.98 with 7, 2.23 with 15; 4 x 2048 at eta = lambda = 256 1.06 ms alone, 1.00 with 1
+                // 3 helpers per stream, 1.93 with 5, 1.98 with 7, 2.23 with 15; 4 x 2048 at eta = lambda = 256 1.06 ms alone, 1.00 with 1
                 // helper, 1.03 with 3, 1.16 with 7.
                 int helpers = 0;
                 if (wide && a.want_out && !a.dm.score_kind) {

@@ -1536,8 +1536,8 @@ __device__ __forceinline__ void wide_score_batches(uint16_t *pool, const float *
 // No wait depends on a workgroup that may not have a compute unit: helpers join by counting themselves in `joined` after
 // `started` says that the stream's workgroup runs (they leave if that takes too long), only helpers that have joined are
 // given work, and the stream's workgroup ends by publishing GO_END.
-// A chunk at lambda = 1024 and 256 features: 85 us on one workgroup (34 batches of 2 us), 37 us with 5 - 7 helpers beside
-// the outputs.  The release and acquire fences cost less than stores and loads past the caches would (2.19 against 2.03 ms
+// A chunk at lambda = 1024 and 256 features: 85 us on one workgroup (34 batches of 2 us), 37 - 41 us with 5 - 7 helpers
+// beside the outputs.  The release and acquire fences cost less than stores and loads past the caches would (2.19 against 2.03 ms
 // for 2 x 4096 tokens at eta 512 / lambda 1024).
 constexpr int WIDE_PIECES = 8;   // launches of a pass at most
 struct WideShare {   // per stream, in the feature scratch behind the cache slots' rows

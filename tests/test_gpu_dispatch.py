@@ -134,3 +134,31 @@ def test_fp32_rows_at_the_edges_of_their_batches(d, D, eta, lam, C):
     layer, o = None, None
     for a, b in ((0, 1), (1, 102), (102, 149)):
         layer, o, _ = P.prefill_parity(sh, q[:, :, a:b], k[:, :, a:b], v[:, :, a:b], Wq, Wk, layer=layer, oracle=o)
+
+
+def test_shared_evolution_replayed_from_a_graph():
+    """A captured prefill (emptied memories, 700 + 300 tokens) whose evolution is shared among workgroups: every replay, with
+    eager work and a synchronization between, gives the eager call's outputs and memories."""
+    sh = wl.Shape("shared_graph", "bf16", 1, 4, 2, 128, 256, T=0, eta=64, lam=512, C=64, seed=0)
+    q, k, v, Wq, Wk = case_inputs(17, 1, 4, 2, 128, 256, 1000)
+    dq, dk, dv, dWq, dWk = P.to_dev(q, "bf16"), P.to_dev(k, "bf16"), P.to_dev(v, "bf16"), P.w_to_dev(Wq, "bf16"), P.w_to_dev(Wk, "bf16")
+    parts = [[x[:, :, a:b].contiguous() for x in (dq, dk, dv)] for a, b in ((0, 700), (700, 1000))]
+    eager, lay = P.make_layer(sh), P.make_layer(sh)
+    want = [eager.prefill(*p, dWq, dWk) for p in parts]
+    outs = [torch.zeros_like(w) for w in want]
+    lay.prefill(*parts[0], dWq, dWk, out=outs[0])   # (the workspace is made outside of the capture)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        lay.reset()
+        for p, o in zip(parts, outs):
+            lay.prefill(*p, dWq, dWk, out=o)
+    for i in range(4):
+        for o in outs:
+            o.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for o, w in zip(outs, want):
+            assert torch.equal(o, w), i
+        for nm in FIELDS:
+            assert torch.equal(getattr(lay, nm), getattr(eager, nm)), (i, nm)
