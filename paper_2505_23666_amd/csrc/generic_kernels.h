@@ -693,7 +693,6 @@ struct PrefillArgs {
     int32_t *next_j;          // [B*Hkv] hand-over of the chunk position between the kernels of a pass
     float *tok_score;         // [B*Hkv][eta + T] query-dependent scores: entry window (virtual rows lam ..), then the call's tokens
     int R2;                   // keys / queries per tile of band_score_kernel
-    int32_t *spc_in;          // [B*Hkv] pairs in the sparse cache at the call's entry
     int piece;                // number of the state-evolution launch within the pass
     int fill_closed;          // 1: prefix_kernel does the call's filling chunks (below), the state-evolution kernels start at the first
                               // scored chunk; 0: the shape-generic evolution does every chunk
@@ -701,7 +700,8 @@ struct PrefillArgs {
 
 // While the eligible pairs number at most lambda nothing is scored and H, s stay as they are, so the filling chunks of a
 // call have a closed form: pair i that leaves the window (counted from the call's entry) is token L0 + i, L0 = max(0,
-// a0 - eta), sits in virtual row P + L0 - a0 + i and takes slot spc_in + i.  The copies are made by prefix_kernel, a
+// a0 - eta), sits in virtual row P + L0 - a0 + i and takes slot spc_in + i, spc_in = the pairs in the cache at the call's
+// entry (the state's sp_count, which finalize_kernel alone writes).  The copies are made by prefix_kernel, a
 // filling chunk's cache rows are computed where its outputs are, and all filling chunks share the entry's snapshot of H
 // and s.  Evolved chunk by chunk on the shape-generic kernel, each snapshot written anew, a filling chunk took 9 - 12 us and
 // a ragged last one (which the MFMA kernels now do as well) 45 - 150 us; a request (8B shape) of 8 x 333 tokens 313 -> 138 us,
@@ -782,7 +782,7 @@ __global__ __launch_bounds__(NT) void prefix_kernel(PrefillArgs<T> a) {
                 tr[p] = s < spc ? sp_idx[s] : (s < held ? (int32_t)(L0 + (s - spc)) : -1);
             }
         }
-        if (tid == 0) { a.spc_in[si] = spc; a.next_j[si] = js; }
+        if (tid == 0) a.next_j[si] = js;
     }
 }
 
@@ -813,7 +813,7 @@ __global__ __launch_bounds__(NT) void finalize_kernel(PrefillArgs<T> a) {
     }
     __syncthreads();
     if (tid == 0) {
-        if (a.fill_closed) a.st.sp_count[si] = min(dm.lam, a.spc_in[si] + left_after(a, a0, Tn));
+        if (a.fill_closed) a.st.sp_count[si] = min(dm.lam, a.st.sp_count[si] + left_after(a, a0, Tn));
         a.st.n_tokens[si] = a0 + Tn;
     }
 }

@@ -214,7 +214,7 @@ bool wide_scan_ok(const lola_config *c) {
 }
 
 struct PrefillPlan {
-    size_t off_prefK, off_prefV, off_sp_row, off_phiE, off_next, off_spc, off_score, off_snap;   // byte offsets
+    size_t off_prefK, off_prefV, off_sp_row, off_phiE, off_next, off_score, off_snap;   // byte offsets
     size_t snap_bytes_per_chunk;                                    // all streams, one chunk (snapshots + phi of its keys)
     size_t phik_bytes_per_chunk;
     size_t fixed_bytes;
@@ -229,7 +229,6 @@ PrefillPlan plan_prefill(const lola_config *c, int with_outputs, size_t Tn) {
     p.off_sp_row = off; off += up(ns * lam * 4);
     p.off_phiE = off; off += up(ns * (lam + c->chunk) * D * 4);
     p.off_next = off; off += up(ns * 4);
-    p.off_spc = off; off += up(ns * 4);
     p.off_score = off; if (c->score_kind != LOLA_SCORE_SRE) off += up(ns * ((size_t)c->window + Tn) * 4);
     p.off_snap = off;
     p.fixed_bytes = off;
@@ -488,7 +487,6 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
     a.sp_row = (int32_t *)(ws + p.off_sp_row);
     a.phiE = (float *)(ws + p.off_phiE);
     a.next_j = (int32_t *)(ws + p.off_next);
-    a.spc_in = (int32_t *)(ws + p.off_spc);
     a.scan_mode = 0;
     int S = a.n_chunks > 0 ? a.n_chunks : 1;
     if (p.snap_bytes_per_chunk > 0) {

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256, 2) void attend_fast_kernel(generic::PrefillArg
     const int64_t aj = a0 + (int64_t)j * C;         // token index of the chunk's first query
     const size_t sj = (size_t)si * a.S + jj;
     // filling chunks share one snapshot of H and s, that of the launch's first chunk, and have their rows in closed form
-    const int spc_in = a.fill_closed ? a.spc_in[si] : 0;
+    const int spc_in = a.fill_closed ? a.st.sp_count[si] : 0;
     const bool filling = a.fill_closed && j < generic::first_scored_chunk(a, a0, spc_in);
     const size_t sh = filling ? (size_t)si * a.S + (a.j0 - a.jb) : sj;
     const uint16_t *Hsnap = reinterpret_cast<const uint16_t *>(a.snapH) + sh * (2 * DH * D);
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(256, 2) void attend_wide_kernel(generic::PrefillArg
     const int64_t aj = a0 + (int64_t)j * C;         // token index of the chunk's first query
     const size_t sj = (size_t)si * a.S + jj;
     // filling chunks share one snapshot of H and s, that of the launch's first chunk, and have their rows in closed form
-    const int spc_in = a.fill_closed ? a.spc_in[si] : 0;
+    const int spc_in = a.fill_closed ? a.st.sp_count[si] : 0;
     const bool filling = a.fill_closed && j < generic::first_scored_chunk(a, a0, spc_in);
     const size_t sh = filling ? (size_t)si * a.S + (a.j0 - a.jb) : sj;
     const uint16_t *Hsnap = reinterpret_cast<const uint16_t *>(a.snapH) + sh * (2 * DH * DF);
@@ -647,7 +647,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
     const bf16_t *pK = a.prefK + (size_t)si * P * DH, *pV = a.prefV + (size_t)si * P * DH;
     const bf16_t *kc = a.k + (size_t)si * a.T_tokens * DH, *vc = a.v + (size_t)si * a.T_tokens * DH;
     const int64_t a0 = a.st.n_tokens[si];
-    const int spc0 = a.spc_in[si];
+    const int spc0 = a.st.sp_count[si];
     int j = a.next_j[si];                    // the first chunk that is scored, or where the launch before this one stopped
     const bool fill_snap = a.want_out && a.j0 < generic::first_scored_chunk(a, a0, spc0);   // filling chunks: one snapshot for all
 
@@ -1657,7 +1657,7 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
         if (tid0 == 0) agent_store(&sh->started, 1);
     }
     const int64_t a0 = a.st.n_tokens[si];
-    const int spc0 = a.spc_in[si];
+    const int spc0 = a.st.sp_count[si];
     int j = a.next_j[si];   // the first chunk that is scored, or where the launch before this one stopped
     const bool fill_snap = a.want_out && a.j0 < generic::first_scored_chunk(a, a0, spc0);   // filling chunks: one snapshot for all
 

@@ -83,6 +83,30 @@ def test_workspace_bytes_monotone(L):
     assert updg == mnug > 0
 
 
+@pytest.mark.parametrize("kw", [{}, dict(dtype=lb.LOLA_F32, window=16, sparse_budget=16, chunk=16), dict(feat_dim=256, window=256, sparse_budget=256),
+                                dict(window=100, sparse_budget=200, chunk=32), dict(batch=9, n_q_heads=7, n_kv_heads=7, sparse_budget=64, score_kind=1)])
+def test_smallest_workspace_is_what_its_parts_need(L, kw):
+    """The smallest accepted workspace is kept by callers: prefix rows of cache and window, the slots' row list, the features of
+    the eligible pairs, a chunk counter per stream, with query-dependent scores one sum per token, and one chunk's snapshot and
+    key features; every part rounded up to 256 bytes and nothing else."""
+    c, T = cfg(**kw), 500
+    up = lambda x: (x + 255) // 256 * 256
+    ns, es, d, D, lam = c.batch * c.n_kv_heads, 2 if c.dtype == lb.LOLA_BF16 else 4, c.head_dim, c.feat_dim, c.sparse_budget
+    fixed = 2 * up(ns * (lam + c.window) * d * es) + up(ns * lam * 4) + up(ns * (lam + c.chunk) * D * 4) + up(ns * 4)
+    if c.score_kind:
+        fixed += up(ns * (c.window + T) * 4)
+    phik = up(ns * c.chunk * D * 4) if lb.lola_kernel_path(c, 0) == "mfma" else 0
+    snap = up(ns * D * d * 4) + up(ns * D * 4) + up(ns * lam * 4)
+    assert lb.lola_prefill_workspace_bytes(c, T, True)[1] == fixed + phik + snap
+    assert lb.lola_prefill_workspace_bytes(c, T, False)[1] == fixed + phik
+
+
+def test_largest_call_without_allocation(L):
+    """A call whose parts fill the static scratch of lola_prefill_noalloc to the last 256 bytes fits it."""
+    c = cfg(batch=36, n_q_heads=1, n_kv_heads=1, head_dim=64, feat_dim=512, window=391, sparse_budget=240, chunk=512, dtype=lb.LOLA_F32)
+    assert lb.lola_prefill_workspace_bytes(c, 64, False)[1] == 64 << 20 == L.lola_noalloc_scratch_bytes()
+
+
 def test_status_strings(L):
     for code in range(-7, 1):
         assert L.lola_status_str(code)
