@@ -704,8 +704,11 @@ struct PrefillArgs {
 // entry (the state's sp_count, which finalize_kernel alone writes).  The copies are made by prefix_kernel, a
 // filling chunk's cache rows are computed where its outputs are, and all filling chunks share the entry's snapshot of H
 // and s.  Evolved chunk by chunk on the shape-generic kernel, each snapshot written anew, a filling chunk took 9 - 12 us and
-// a ragged last one (which the MFMA kernels now do as well) 45 - 150 us; a request (8B shape) of 8 x 333 tokens 313 -> 138 us,
-// of 16 x 1513 tokens in two calls 1.21 -> 0.86 ms, of 4 x 2048 at eta = lambda = 256 1.18 -> 1.08 ms.
+// a ragged last one (which the MFMA kernels now do as well) 45 - 150 us; a request (8B shape) of 8 x 333 tokens 313 -> 151 us,
+// of 16 x 1513 tokens in two calls 1.21 -> 0.88 ms, of 4 x 2048 at eta = lambda = 256 1.18 -> 1.08 ms.
+// The first scored chunk and a ragged last one keep the precision that they had on the shape-generic kernel (features folded
+// in fp32, scores column by column): against fp64, H after 24 calls of 1 .. 63 tokens on a full cache is off by 1.5e-7 to
+// 1.8e-7 (2-norm; 1.7e-7 to 2.0e-7 there), s by 1.0e-7 (0.9e-7 to 1.1e-7 there).
 // pairs that have left the window, counted from the call's entry, once `tok` of its tokens have joined it
 template <typename T>
 __device__ __forceinline__ int left_after(const PrefillArgs<T> &a, int64_t a0, int tok) {

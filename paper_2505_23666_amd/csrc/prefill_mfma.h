@@ -281,6 +281,27 @@ __device__ __forceinline__ void phi_from_z_tiles(const f32x4 (&zt)[NT], int phi_
     for (int x = 0; x < 4 * NT; x++) { pp[x] *= ip; pn[x] *= in_; }
 }
 
+// The same features where registers are short, one at a time: 2^(LOG2E z + cp) ip and 2^(-LOG2E z + cn) in.
+struct PhiNorm { float cp, cn, ip, in; };
+template <int NT>
+__device__ __forceinline__ PhiNorm phi_norm(const f32x4 (&zt)[NT], int phi_kind) {
+    PhiNorm n = {0.f, 0.f, 1.f, 1.f};
+    if (phi_kind == 1) return n;
+    float zmax = zt[0][0], zmin = zt[0][0];
+#pragma unroll
+    for (int x = 1; x < 4 * NT; x++) { zmax = fmaxf(zmax, zt[x >> 2][x & 3]); zmin = fminf(zmin, zt[x >> 2][x & 3]); }
+    zmax = grp_max(zmax); zmin = grp_min(zmin);
+    n.cp = -zmax * LOG2E; n.cn = zmin * LOG2E;
+    float sp = 0.f, sn = 0.f;
+#pragma unroll
+    for (int x = 0; x < 4 * NT; x++) {
+        const float zz = zt[x >> 2][x & 3];
+        sp += fexp2(fmaf(zz, LOG2E, n.cp)); sn += fexp2(fmaf(zz, -LOG2E, n.cn));
+    }
+    n.ip = frcp(grp_sum(sp)); n.in = frcp(grp_sum(sn));
+    return n;
+}
+
 // The output kernel for any window and sparse budget (read from the arguments) and for 128 or 256 features: the
 // paper's own models use twice the head dimension as feature dimension and windows / budgets of 128 .. 1024 in the
 // long-context runs (Sec. 4).  Same computation and layouts as attend_fast_kernel (chunks of 64 queries, key blocks of
@@ -658,6 +679,8 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
 #define LOLA_SDECL(rt, ks, hf) f32x4 hreg##rt##ks##hf = {0.f, 0.f, 0.f, 0.f};
 #define LOLA_SLOAD(rt, ks, hf) if (rt < RT) hreg##rt##ks##hf = *reinterpret_cast<const f32x4 *>(Hg + LOLA_SADDR(rt, ks, hf));
 #define LOLA_SSTORE(rt, ks, hf) if (rt < RT) *reinterpret_cast<f32x4 *>(Hg + LOLA_SADDR(rt, ks, hf)) = hreg##rt##ks##hf;
+#define LOLA_SZERO(rt, ks, hf) if (rt < RT) hreg##rt##ks##hf = (f32x4){0.f, 0.f, 0.f, 0.f};
+#define LOLA_SADD(rt, ks, hf) if (rt < RT) hreg##rt##ks##hf += *reinterpret_cast<const f32x4 *>(Hg + LOLA_SADDR(rt, ks, hf));
     LOLA_SREP(LOLA_SDECL)
     const bool started = j < a.j1;
     bool idx_valid = false;     // rows [0, LAM) of cidx hold the cache slots' token indices
@@ -668,22 +691,16 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
     // pairs that leave the window in chunk j
     constexpr int PHN = C * 32 / NTH;   // 16-byte pieces of a chunk's features per thread
     uint4 PHn[PHN];             // this thread's pieces of phi of the pairs that leave the window in the next chunk
-    uint2 vvn[4][RT];           // their values at this wavefront's columns
+    struct Vals { uint2 v[4][RT]; } vvn;   // their values at this wavefront's columns
 #pragma unroll
     for (int x = 0; x < 4; x++)
 #pragma unroll
-        for (int rt = 0; rt < RT; rt++) vvn[x][rt] = make_uint2(0, 0);
+        for (int rt = 0; rt < RT; rt++) vvn.v[x][rt] = make_uint2(0, 0);
 #pragma unroll
     for (int x = 0; x < PHN; x++) PHn[x] = make_uint4(0, 0, 0, 0);
 
-    if (started || fill_snap) {
-        LOLA_SREP(LOLA_SLOAD)
-        if (tid0 < D) s_l[tid0] = sg[tid0];
-        // The state is waited for here, once: left to the first use, the wait would stand in the loop body behind the
-        // chunk's own requests (the counter is in order) and hold every chunk until half of those had arrived.
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-        __syncthreads();
-    }
+    if (tid0 < D) s_l[tid0] = sg[tid0];
+    __syncthreads();
     // the snapshot's pieces of row tile rt, k-step ks (bf16 high + low parts): one contiguous 1 KB piece per store
 #define LOLA_SSNAP(rt, ks) if (rt < RT) { float sv[8]; \
         _Pragma("unroll") for (int x = 0; x < 4; x++) { sv[x] = hreg##rt##ks##0[x]; sv[4 + x] = hreg##rt##ks##1[x]; } \
@@ -694,6 +711,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
 #define LOLA_SSNAP_ALL LOLA_SSNAP(0, 0) LOLA_SSNAP(0, 1) LOLA_SSNAP(0, 2) LOLA_SSNAP(0, 3) \
                        LOLA_SSNAP(1, 0) LOLA_SSNAP(1, 1) LOLA_SSNAP(1, 2) LOLA_SSNAP(1, 3)
     if (fill_snap) {
+        LOLA_SREP(LOLA_SLOAD)
         const int w = w0, lane = tid0 & 63;
         const size_t sj = (size_t)si * a.S + (a.j0 - a.jb);
         uint16_t *s16 = reinterpret_cast<uint16_t *>(a.snapH) + sj * (2 * D * DH);
@@ -701,13 +719,18 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
         if (tid0 < D) a.snapS[sj * D + tid0] = s_l[tid0];
     }
 
-    for (; j < a.j1; j++) {
-        // A scored chunk has a full window behind it.  Its candidates: the cache slots [0, spc), and the first cl of the 64
-        // rows before the chunk, which leave the window (cl < 64: a ragged last chunk); nf of them are folded.  The
-        // positions of missing candidates are computed along and kept out of the selection by a score above all others.
-        const int cl = min(C, a.T_tokens - j * C);
+    // One scored chunk.  It has a full window behind it.  A regular one finds a full cache and lets 64 pairs leave the
+    // window.  An irregular one (IRR: the first scored chunk of a call, a ragged last one) has fewer candidates, the cache
+    // slots [0, spc) and the first cl of the 64 rows before the chunk, and folds nf < 64 of them; the positions of missing
+    // candidates are computed along and kept out of the selection by a score above all others.  Its scores and its fold keep
+    // the precision of the shape-generic evolution; it takes 21 us where a regular one takes 10 (8B shape, lambda = 128).
+    // Two copies of the body: with the irregular case in the regular chunks' loop those took up to 4 % longer.
+    // (vvc: vvn by value, so that it stays in registers)
+    auto chunk = [&](auto irr_, Vals vvc) __attribute__((always_inline)) {
+        constexpr bool IRR = decltype(irr_)::value;
+        const int cl = IRR ? min(C, a.T_tokens - j * C) : C;
         const int64_t aj = a0 + (int64_t)j * C;
-        const int spc = min(LAM, spc0 + generic::left_after(a, a0, j * C)), nf = spc + cl - LAM;
+        const int spc = IRR ? min(LAM, spc0 + generic::left_after(a, a0, j * C)) : LAM, nf = IRR ? spc + cl - LAM : C;
         // The lane coordinates are made opaque once per chunk: everything derived from them (LDS and global
         // addresses of every phase) is then recomputed inside the loop instead of being hoisted out of it as
         // hundreds of loop-invariant registers, which the register file cannot hold next to H^T.
@@ -751,7 +774,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                 lds_dma16(src, &dstbuf[pt * RB * D + rl0 * D]);
             }
 #pragma unroll
-            for (int u = 0; u < (PERSIST ? 1 : TB); u++)
+            for (int u = 0; u < (PERSIST || IRR ? 0 : TB); u++)
 #pragma unroll
                 for (int rt = 0; rt < RT; rt++)
                     vvq[u][rt] = *reinterpret_cast<const uint2 *>(vrow(16 * (tb0 + u) + r16) + 16 * (RT * w + rt) + 4 * g4);
@@ -805,17 +828,17 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                 // into the other buffer, whose readers passed the barrier that ended the batch before this one.
                 __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
 #pragma unroll
-                for (int u = 0; u < TB; u++)
+                for (int u = 0; u < (IRR ? 0 : TB); u++)
 #pragma unroll
                     for (int rt = 0; rt < RT; rt++) vv[u][rt] = vvq[PERSIST ? 0 : u][rt];
                 if (t0 + TB < NTILE) request_batch(t0 + TB, PBn);
             } else {
 #pragma unroll
-            for (int u = 0; u < TB; u++) {
+            for (int u = 0; u < (IRR ? 0 : TB); u++) {
 #pragma unroll
                 for (int rt = 0; rt < RT; rt++) {
                     if (PERSIST && u >= TC && have_phi) {
-                        vv[u][rt] = vvn[u >= TC ? u - TC : 0][rt];
+                        vv[u][rt] = vvc.v[u >= TC ? u - TC : 0][rt];
                     } else if (t0 + u < t1) {
                         vv[u][rt] = *reinterpret_cast<const uint2 *>(vrow(16 * (t0 + u) + r16) + 16 * (RT * w + rt) + 4 * g4);
                     }
@@ -866,6 +889,73 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                 if (tid < LAM) a.snapG[sj * LAM + tid] = sprow_ld;
             }
             lds_barrier();
+            if constexpr (IRR) {
+                // An irregular chunk's scores are taken as the shape-generic evolution takes them, column by column,
+                // |P / (phi.s) - v|^2 with phi.s in fp32: the expanded form below loses 2^-23 |v|^2, which decides where
+                // recalls come close to their values (values of a large common mean: pairs were folded in the wrong order
+                // by more than 1e-4).  A short loop, because its code is fetched for one chunk.
+                // First 1 / (phi.s) of the tiles t0 + w, t0 + w + NW, ...
+#pragma unroll 1
+                for (int t = t0 + w; t < t1; t += NW) {
+                    const uint16_t *rp = &PBb[(16 * (t - t0) + r16) * D];
+                    float dn = 0.f;
+#pragma unroll
+                    for (int ks = 0; ks < 4; ks++) {
+                        const uint4 hi = *reinterpret_cast<const uint4 *>(rp + (((4 * ks + g4) ^ r16) << 3));
+                        const uint4 lo = *reinterpret_cast<const uint4 *>(rp + RB * D + (((4 * ks + g4) ^ r16) << 3));
+                        const float4 sv0 = *reinterpret_cast<const float4 *>(&s_l[32 * ks + 4 * g4]);
+                        const float4 sv1 = *reinterpret_cast<const float4 *>(&s_l[32 * ks + 16 + 4 * g4]);
+                        dn = fmaf(bf_lo(hi.x) + bf_lo(lo.x), sv0.x, dn); dn = fmaf(bf_hi(hi.x) + bf_hi(lo.x), sv0.y, dn);
+                        dn = fmaf(bf_lo(hi.y) + bf_lo(lo.y), sv0.z, dn); dn = fmaf(bf_hi(hi.y) + bf_hi(lo.y), sv0.w, dn);
+                        dn = fmaf(bf_lo(hi.z) + bf_lo(lo.z), sv1.x, dn); dn = fmaf(bf_hi(hi.z) + bf_hi(lo.z), sv1.y, dn);
+                        dn = fmaf(bf_lo(hi.w) + bf_lo(lo.w), sv1.z, dn); dn = fmaf(bf_hi(hi.w) + bf_hi(lo.w), sv1.w, dn);
+                    }
+                    dn = grp_sum(dn);
+                    if (g4 == 0) dn_l[16 * t + r16] = dn > 0.f ? 1.0f / dn : 0.f;
+                }
+                constexpr int TG = PERSIST ? 4 : TB;   // tiles whose values are requested together
+                uint2 vx[TG][RT];
+                auto request_values = [&](int tg) {
+#pragma unroll
+                    for (int u = 0; u < TG; u++)
+#pragma unroll
+                        for (int rt = 0; rt < RT; rt++) vx[u][rt] = *reinterpret_cast<const uint2 *>(vrow(16 * (tg + u) + r16) + 16 * (RT * w + rt) + 4 * g4);
+                };
+                request_values(t0);
+                lds_barrier();
+#pragma unroll 1
+                for (int tg = t0; tg < t1; tg += TG) {
+#pragma unroll
+                    for (int u = 0; u < TG; u++) {
+                        const int e = 16 * (tg + u) + r16;
+                        const uint16_t *rp = &PBb[(e - 16 * t0) * D];
+                        bf16x8 B[8];
+#pragma unroll
+                        for (int ks = 0; ks < 4; ks++) {
+                            B[ks] = as_bf16x8(*reinterpret_cast<const uint4 *>(rp + (((4 * ks + g4) ^ r16) << 3)));
+                            B[4 + ks] = as_bf16x8(*reinterpret_cast<const uint4 *>(rp + RB * D + (((4 * ks + g4) ^ r16) << 3)));
+                        }
+                        const float rd = dn_l[e];
+                        float err = 0.f;
+#pragma unroll
+                        for (int rt = 0; rt < RT; rt++) {
+                            f32x4 p0 = {0.f, 0.f, 0.f, 0.f}, p1 = p0, p2 = p0;
+#pragma unroll
+                            for (int ks = 0; ks < 4; ks++) {
+                                p0 = mfma16(Ahi[rt][ks], B[ks], p0);
+                                p1 = mfma16(Ahi[rt][ks], B[4 + ks], p1);
+                                p2 = mfma16(Alo[rt][ks], B[ks], p2);
+                            }
+                            const float v4[4] = {bf_lo(vx[u][rt].x), bf_hi(vx[u][rt].x), bf_lo(vx[u][rt].y), bf_hi(vx[u][rt].y)};
+#pragma unroll
+                            for (int i = 0; i < 4; i++) { const float d = fmaf(p0[i] + (p1[i] + p2[i]), rd, -v4[i]); err = fmaf(d, d, err); }
+                        }
+                        err = grp_sum(err);
+                        if (g4 == 0) part[0][w][e] = err;
+                    }
+                    if (tg + TG < t1) request_values(tg + TG);
+                }
+            } else {
             // recall GEMM for the batch: A = this wavefront's 16 rows of H^T, B = phi from LDS; lane (candidate r16,
             // group g4) holds rows c = 16w + 4 g4 + i and pairs them with the candidate's values at those columns.
             // Tile t's denominators come from wavefront t % 8 (A = s in row 0, zeros below).  Operands of the next
@@ -991,12 +1081,13 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                 }
             }
             }
+            }
             // Requests that nothing in this chunk waits for - the rows wanted by the next chunk and the snapshot of
             // H^T - are issued where a wavefront would otherwise idle: by wavefront 0 here, behind its share of the
             // recall GEMM (it waits for the other wavefront of its SIMD anyway), by the others while wavefront 0 runs the
             // selection.  Issued by all wavefronts ahead of the recall GEMM they cost 1.3 us per chunk.
             if (w == 0 && t0 + TB >= NTILE) {
-                if (PERSIST && cl == C) {   // this chunk's own pairs leave the window in the next chunk
+                if (PERSIST && !IRR) {   // this chunk's own pairs leave the window in the next chunk
                     const uint4 *ph = reinterpret_cast<const uint4 *>(a.phiK + ((size_t)si * a.S + (j - a.jb)) * C * 2 * D);
 #pragma unroll
                     for (int it = 0; it < PHN; it++) PHn[it] = ph[tid + NTH * it];
@@ -1004,7 +1095,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                     for (int u = 0; u < 4; u++)
 #pragma unroll
                         for (int rt = 0; rt < RT; rt++)
-                            vvn[u][rt] = *reinterpret_cast<const uint2 *>(vc + (size_t)(j * C + 16 * u + r16) * DH + 16 * (RT * w + rt) + 4 * g4);
+                            vvn.v[u][rt] = *reinterpret_cast<const uint2 *>(vc + (size_t)(j * C + 16 * u + r16) * DH + 16 * (RT * w + rt) + 4 * g4);
                 }
                 if (a.want_out) {
                     uint16_t *s16 = reinterpret_cast<uint16_t *>(a.snapH) + ((size_t)si * a.S + (j - a.jb)) * (2 * D * DH);
@@ -1027,12 +1118,18 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
         // token index ascending, the first LAM stay).  The squared error is |P|^2 / (phi.s)^2 - 2 P.v / (phi.s) + |v|^2
         // (recall = 0 while phi.s = 0, i.e. nothing folded yet); the bit pattern of a float >= 0 orders like an integer.
         for (int e = tid; e < NE; e += NTH) {
-            const float dn = dn_l[e], rd = dn > 0.f ? __builtin_amdgcn_rcpf(dn) : 0.f;
-            float sa = 0.f, sb = 0.f, sc = 0.f;
+            float sq = 0.f;
+            if constexpr (IRR) {
 #pragma unroll
-            for (int x = 0; x < NW; x++) { sa += part[0][x][e]; sb += part[1][x][e]; sc += part[2][x][e]; }
-            const float sq = fmaxf(fmaf(rd * rd, sa, fmaf(-2.0f * rd, sb, sc)), 0.f);
-            skey[e] = (e < LAM ? e < spc : e < LAM + cl) ? __float_as_uint(sq) & 0x7FFFFFFFu : 0xFFFFFFFFu;
+                for (int x = 0; x < NW; x++) sq += part[0][x][e];
+            } else {
+                const float dn = dn_l[e], rd = dn > 0.f ? __builtin_amdgcn_rcpf(dn) : 0.f;
+                float sa = 0.f, sb = 0.f, sc = 0.f;
+#pragma unroll
+                for (int x = 0; x < NW; x++) { sa += part[0][x][e]; sb += part[1][x][e]; sc += part[2][x][e]; }
+                sq = fmaxf(fmaf(rd * rd, sa, fmaf(-2.0f * rd, sb, sc)), 0.f);
+            }
+            skey[e] = !IRR || (e < LAM ? e < spc : e < LAM + cl) ? __float_as_uint(sq) & 0x7FFFFFFFu : 0xFFFFFFFFu;
         }
         lds_barrier();
         // One wavefront holds all scores (NK per lane) and finds the nf-th smallest by building it bit by bit: a trial
@@ -1041,7 +1138,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
         // over their token indices picks the largest ones.  The lists follow from the fold predicate by ballots:
         // candidates to fold; entrants paired with the slots of the leavers.
         if (w != 0) {   // the requests wavefront 0 issued before the recall GEMM (H^T is still the chunk's entry state)
-            if (PERSIST && cl == C) {
+            if (PERSIST && !IRR) {
                 const uint4 *ph = reinterpret_cast<const uint4 *>(a.phiK + ((size_t)si * a.S + (j - a.jb)) * C * 2 * D);
 #pragma unroll
                 for (int it = 0; it < PHN; it++) PHn[it] = ph[tid + NTH * it];
@@ -1049,7 +1146,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                 for (int u = 0; u < 4; u++)
 #pragma unroll
                     for (int rt = 0; rt < RT; rt++)
-                        vvn[u][rt] = *reinterpret_cast<const uint2 *>(vc + (size_t)(j * C + 16 * u + r16) * DH + 16 * (RT * w + rt) + 4 * g4);
+                        vvn.v[u][rt] = *reinterpret_cast<const uint2 *>(vc + (size_t)(j * C + 16 * u + r16) * DH + 16 * (RT * w + rt) + 4 * g4);
             }
             if (a.want_out) {
                 uint16_t *s16 = reinterpret_cast<uint16_t *>(a.snapH) + ((size_t)si * a.S + (j - a.jb)) * (2 * D * DH);
@@ -1127,8 +1224,8 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                 nfo += __popcll(mf); nen += __popcll(me); nlv += __popcll(ml);
             }
             // places left: the list of folded pairs is padded (with zeros, below), entrants beyond the leavers take unused slots
-            if (lane >= nf) flist[lane] = 0;
-            if (nlv + lane < nen) eslot[nlv + lane] = spc + lane;
+            if (IRR && lane >= nf) flist[lane] = 0;
+            if (IRR && nlv + lane < nen) eslot[nlv + lane] = spc + lane;
             if (lane == 0) ne_s = nen;
         }
         lds_barrier();
@@ -1167,7 +1264,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                 va[vit] = reinterpret_cast<const uint4 *>(vrow(flist[ep]))[vch];
                 vb[vit] = reinterpret_cast<const uint4 *>(vrow(flist[ep + 1]))[vch];
             }
-            if (nf < C) {   // fewer than 64 folded pairs: the rest of the contraction is zeros
+            if constexpr (IRR) {   // fewer than 64 folded pairs: the rest of the contraction is zeros
 #pragma unroll
                 for (int it = 0; it < PIT; it++) {
                     const int ep = 8 * ((w >> 1) + CPW * it) + 2 * pairpos;
@@ -1235,30 +1332,81 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
             bf16x8 Ac[4], An[4];
 #define LOLA_SFA(dst, mt) _Pragma("unroll") for (int x = 0; x < 4; x++) { const int f = 16 * (mt) + r16; \
                 dst[x] = as_bf16x8(*reinterpret_cast<const uint4 *>(&PT[(x >> 1) * D * C + f * C + (((4 * (x & 1) + g4) ^ tswz(f)) << 3)])); }
-            LOLA_SFA(Ac, 0)
             // s += sum of the folded features: a feature tile's operands times a vector of ones (tile mt by wavefront mt % NW)
             const bf16x8 ones = as_bf16x8(make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
             f32x4 sacc[8 / NW];
-#pragma unroll
-            for (int x = 0; x < 8 / NW; x++) sacc[x] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #define LOLA_SFOLD2(ks, hf) { if (2 * ks + hf + 1 < 8) { LOLA_SFA(An, 2 * ks + hf + 1) } \
             _Pragma("unroll") for (int x = 0; x < 4; x++) { hreg0##ks##hf = mfma16(Ac[x], Bv[0][x & 1], hreg0##ks##hf); \
                                                             if (RT > 1) hreg1##ks##hf = mfma16(Ac[x], Bv[RT - 1][x & 1], hreg1##ks##hf); } \
             if (((2 * ks + hf) & (NW - 1)) == w) { _Pragma("unroll") for (int x = 0; x < 4; x++) sacc[(2 * ks + hf) / NW] = mfma16(Ac[x], ones, sacc[(2 * ks + hf) / NW]); } \
             __builtin_amdgcn_sched_barrier(0); \
             _Pragma("unroll") for (int x = 0; x < 4; x++) Ac[x] = An[x]; }
-            LOLA_SFOLD2(0, 0) LOLA_SFOLD2(0, 1) LOLA_SFOLD2(1, 0) LOLA_SFOLD2(1, 1) LOLA_SFOLD2(2, 0) LOLA_SFOLD2(2, 1) LOLA_SFOLD2(3, 0) LOLA_SFOLD2(3, 1)
-#undef LOLA_SFOLD2
-#undef LOLA_SFA
-            if (r16 == 0) {   // column 0 of the result tiles: features 16 (w + NW x) + 4 g4 + 0..3
+            // (column 0 of the result tiles of s: features 16 (w + NW x) + 4 g4 + 0..3)
+#define LOLA_SFOLD LOLA_SFA(Ac, 0) \
+            _Pragma("unroll") for (int x = 0; x < 8 / NW; x++) sacc[x] = (f32x4){0.f, 0.f, 0.f, 0.f}; \
+            LOLA_SFOLD2(0, 0) LOLA_SFOLD2(0, 1) LOLA_SFOLD2(1, 0) LOLA_SFOLD2(1, 1) LOLA_SFOLD2(2, 0) LOLA_SFOLD2(2, 1) LOLA_SFOLD2(3, 0) LOLA_SFOLD2(3, 1) \
+            if (r16 == 0) { \
+                _Pragma("unroll") for (int x = 0; x < 8 / NW; x++) { \
+                    float4 *sp = reinterpret_cast<float4 *>(&s_l[16 * (w + NW * x) + 4 * g4]); \
+                    float4 sv = *sp; \
+                    sv.x += sacc[x][0]; sv.y += sacc[x][1]; sv.z += sacc[x][2]; sv.w += sacc[x][3]; \
+                    *sp = sv; \
+                } \
+            }
+            f32x4 zt[4];   // IRR, wavefront w < 4: projections of the folded pairs 16 w ..
+            PhiNorm nm = {0.f, 0.f, 0.f, 0.f};
+            static_assert(NW >= C / 16, "a tile of 16 folded pairs per wavefront");
+            if constexpr (IRR) {
+                LOLA_SREP(LOLA_SZERO)   // the chunk's sum is taken by itself; H^T is in its place in memory
+                if (w < C / 16) {
+                    const bf16_t *kr = krow(flist[16 * w + r16]);
+                    bf16x8 BK[KS];
 #pragma unroll
-                for (int x = 0; x < 8 / NW; x++) {
-                    float4 *sp = reinterpret_cast<float4 *>(&s_l[16 * (w + NW * x) + 4 * g4]);
-                    float4 sv = *sp;
-                    sv.x += sacc[x][0]; sv.y += sacc[x][1]; sv.z += sacc[x][2]; sv.w += sacc[x][3];
-                    *sp = sv;
+                    for (int ks = 0; ks < KS; ks++) BK[ks] = ld_bf16x8(kr + 32 * ks + 8 * g4);
+#pragma unroll
+                    for (int mt = 0; mt < 4; mt++) {
+                        zt[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int ks = 0; ks < KS; ks++)
+                            zt[mt] = mfma16(ld_bf16x8(Wk + (size_t)(16 * mt + r16) * DH + 32 * ks + 8 * g4), BK[ks], zt[mt]);
+                    }
+                    nm = phi_norm<4>(zt, a.dm.phi_kind);
                 }
             }
+#pragma unroll 1
+            for (int round = 0; round < (IRR ? 2 : 1); round++) {
+                if (IRR && round) {
+                    // An irregular chunk folds with fp32 features, as the shape-generic evolution does: the features once more, and
+                    // what the two bf16 parts in the tile leave of them (2^-18 of a feature; a third part leaves 2^-26) folded in a
+                    // second round.  2-norm error of H after 24 calls of 1 .. 63 tokens 1.8e-7, with two parts 2.4e-6.
+                    lds_barrier();   // the tile has been read
+                    if (w < C / 16) {
+                        const int ep = 16 * w + r16;
+                        auto place = [&](int x) { const int f = 32 * (x >> 3) + 16 * ((x >> 2) & 1) + 4 * g4 + (x & 3);
+                                                  return &PT[f * C + (((ep >> 3) ^ tswz(f)) << 3) + (ep & 7)]; };
+#pragma unroll
+                        for (int hf = 0; hf < 2; hf++) {   // positive, negative half: all reads ahead of the writes
+                            uint16_t hi[16], lo[16];
+#pragma unroll
+                            for (int x = 0; x < 16; x++) { const uint16_t *p = place(16 * hf + x); hi[x] = p[0]; lo[x] = p[D * C]; }
+#pragma unroll
+                            for (int x = 0; x < 16; x++) {
+                                const float z = zt[x >> 2][x & 3];
+                                const float r = (hf == 0 ? fexp2(fmaf(z, LOG2E, nm.cp)) * nm.ip : fexp2(fmaf(z, -LOG2E, nm.cn)) * nm.in) - bf_lo(hi[x]) - bf_lo(lo[x]);
+                                uint16_t *p = place(16 * hf + x);
+                                p[0] = ep < nf ? __builtin_bit_cast(uint16_t, (__bf16)r) : (uint16_t)0;
+                                p[D * C] = 0;
+                            }
+                        }
+                    }
+                    lds_barrier();
+                }
+                LOLA_SFOLD
+            }
+            if constexpr (IRR) { LOLA_SREP(LOLA_SADD) }
+#undef LOLA_SFOLD
+#undef LOLA_SFOLD2
+#undef LOLA_SFA
             // ---- 5. compaction, second half: entrants take the leavers' slots, in the state and (their features) in LDS
 #pragma unroll
             for (int it = 0; it < CIT; it++) {
@@ -1308,11 +1456,41 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
             int32_t *tr = a.sel_trace + ((size_t)si * a.n_chunks + j) * LAM;
             for (int sl = tid; sl < LAM; sl += NTH) tr[sl] = sp_idx[sl];
         }
-    }
-    if (started) {
+    };
+    // Between the copies H^T passes through memory and the rows of the next chunk are requested anew, so that nothing but the
+    // copy's own values occupies registers.
+    auto ahead = [&]() __attribute__((always_inline)) {   // the rows of the pairs that leave in chunk j, the tokens of chunk j - 1
+        if (PERSIST && phi_valid) {
+            const uint4 *ph = reinterpret_cast<const uint4 *>(a.phiK + ((size_t)si * a.S + (j - 1 - a.jb)) * C * 2 * D);
+#pragma unroll
+            for (int it = 0; it < PHN; it++) PHn[it] = ph[tid0 + NTH * it];
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+#pragma unroll
+                for (int rt = 0; rt < RT; rt++)
+                    vvn.v[u][rt] = *reinterpret_cast<const uint2 *>(vc + (size_t)((j - 1) * C + 16 * u + (tid0 & 15)) * DH + 16 * (RT * w0 + rt) + 4 * ((tid0 & 63) >> 4));
+        }
+    };
+    const int jr1 = min(a.j1, a.T_tokens / C);   // behind the last full chunk
+    bool irr = started && spc0 + generic::left_after(a, a0, j * C) < LAM;   // the cache is complete from the second scored chunk on
+#pragma unroll 1
+    for (;; irr = false) {
+        if (!irr && j < jr1) {
+            LOLA_SREP(LOLA_SLOAD)
+            ahead();
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), once (see above)
+#pragma unroll 1
+            for (; j < jr1; j++) chunk(std::false_type{}, vvn);
+            LOLA_SREP(LOLA_SSTORE)
+        }
+        if (j >= a.j1) break;
+        LOLA_SREP(LOLA_SLOAD)
+        ahead();
+        chunk(std::true_type{}, vvn);
         LOLA_SREP(LOLA_SSTORE)
-        if (tid0 < D) sg[tid0] = s_l[tid0];
+        j++;
     }
+    if (started && tid0 < D) sg[tid0] = s_l[tid0];
     if (tid0 == 0) a.next_j[si] = j;
 #undef LOLA_SREP
 #undef LOLA_SREP1
@@ -1320,6 +1498,8 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
 #undef LOLA_SDECL
 #undef LOLA_SLOAD
 #undef LOLA_SSTORE
+#undef LOLA_SZERO
+#undef LOLA_SADD
 #undef LOLA_SSNAP
 #undef LOLA_SSNAP_ALL
 }
@@ -1432,14 +1612,15 @@ __device__ __forceinline__ void wide_issue(uint16_t *pool, int b, int buf, int t
 }
 // Recall errors of the candidate batches [b0, b1) (b0 < b1): |P|^2, P.v, |v|^2 over all value columns -> tot, phi(k).s ->
 // dn_l.  phirow(e), vrow(e): feature and value row of candidate e.  Ahi, Alo: this wavefront's 16 rows of H^T.  ISSUED: the
-// first NBUF - 1 batches of [b0, b1) have been requested.
-template <int DH, int DF, bool ISSUED = false, typename FPhi, typename FVal>
+// first NBUF - 1 batches of [b0, b1) have been requested.  EXACT: |P / (phi.s) - v|^2 itself -> tot[0], column by column
+// (see scan_fast_kernel, IRR); phi.s is then wanted before the products are used, one barrier more per batch.
+template <int DH, int DF, bool ISSUED = false, bool EXACT = false, typename FPhi, typename FVal>
 __device__ __forceinline__ void wide_score_batches(uint16_t *pool, const float *s_l, float *dn_l, float (*tot)[WideScan<DH, DF>::NEMAX],
                                                    float (*part)[3][DH / 16][WideScan<DH, DF>::RB], const bf16x8 (&Ahi)[DF / 32],
                                                    const bf16x8 (&Alo)[DF / 32], int b0, int b1, int tid, FPhi phirow, FVal vrow) {
     using L = WideScan<DH, DF>;
     constexpr int NW = L::NW, NTH = L::NTH, KF = L::KF, PR = L::PR, FR = L::FR, PP = L::PP, RB = L::RB, TB = L::TB, NBUF = L::NBUF,
-                  VPB = L::VPB, LPB = L::LPB, BUF = L::BUF;
+                  LPB = L::LPB, BUF = L::BUF;
     const int lane = tid & 63, r16 = lane & 15, g4 = lane >> 4, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     auto issue = [&](int b, int buf) { wide_issue<DH, DF>(pool, b, buf, tid, phirow, vrow); };
     if (!ISSUED) {
@@ -1460,7 +1641,7 @@ __device__ __forceinline__ void wide_score_batches(uint16_t *pool, const float *
         if (b + NBUF - 1 < b1) issue(b + NBUF - 1, buf == 0 ? NBUF - 1 : buf - 1);
         const uint16_t *PBb = pool + buf * BUF, *VBb = PBb + RB * FR;
         const int pb = b & 1;
-        if (b > b0 && tid < 3 * RB) {          // batch b - 1: the wavefronts' sums over their columns, added in a fixed order
+        if (b > b0 && tid < (EXACT ? 1 : 3) * RB) {          // batch b - 1: the wavefronts' sums over their columns, added in a fixed order
             const int k = tid / RB, r = tid % RB;
             float sum = 0.f;
 #pragma unroll
@@ -1487,6 +1668,7 @@ __device__ __forceinline__ void wide_score_batches(uint16_t *pool, const float *
             if (TPR >= 16) dsum += dpp_f<0x140>(dsum);
             if (sub == 0) dn_l[b * RB + r] = dsum;
         }
+        if (EXACT) lds_barrier();
         // recall GEMM: A = this wavefront's 16 rows of H^T, B = phi of 16 candidates from LDS; lane (candidate r16,
         // group g4) holds the recall at columns 16 w + 4 g4 + i and pairs it with the candidate's values there
 #pragma unroll
@@ -1508,17 +1690,26 @@ __device__ __forceinline__ void wide_score_batches(uint16_t *pool, const float *
             for (int ks = 0; ks < KF; ks++) acc = mfma16(Alo[ks], Bh[ks], acc);
             const uint2 vv = *reinterpret_cast<const uint2 *>(&VBb[(16 * u + r16) * DH + (((2 * w + (g4 >> 1)) ^ (r16 & (PR - 1))) << 3) + 4 * (g4 & 1)]);
             const float v0 = bf_lo(vv.x), v1 = bf_hi(vv.x), v2 = bf_lo(vv.y), v3 = bf_hi(vv.y);
+            if constexpr (EXACT) {
+                const float dn = dn_l[b * RB + 16 * u + r16], rd = dn > 0.f ? 1.0f / dn : 0.f, v4[4] = {v0, v1, v2, v3};
+                float err = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; i++) { const float d = fmaf(acc[i], rd, -v4[i]); err = fmaf(d, d, err); }
+                err = grp_sum(err);
+                if (g4 == 0) part[pb][0][w][16 * u + r16] = err;
+            } else {
             float sa = 0.f, sb = 0.f, sc = 0.f;
             sa = fmaf(acc[0], acc[0], sa); sa = fmaf(acc[1], acc[1], sa); sa = fmaf(acc[2], acc[2], sa); sa = fmaf(acc[3], acc[3], sa);
             sb = fmaf(acc[0], v0, sb); sb = fmaf(acc[1], v1, sb); sb = fmaf(acc[2], v2, sb); sb = fmaf(acc[3], v3, sb);
             sc = fmaf(v0, v0, sc); sc = fmaf(v1, v1, sc); sc = fmaf(v2, v2, sc); sc = fmaf(v3, v3, sc);
             const float s3 = grp_sum3(sa, sb, sc);   // lane group g4 holds sum g4
             if (g4 < 3) part[pb][g4][w][16 * u + r16] = s3;
+            }
         }
         buf = buf == NBUF - 1 ? 0 : buf + 1;
     }
     lds_barrier();
-    if (tid < 3 * RB) {
+    if (tid < (EXACT ? 1 : 3) * RB) {
         const int k = tid / RB, r = tid % RB;
         float sum = 0.f;
 #pragma unroll
@@ -1531,7 +1722,7 @@ __device__ __forceinline__ void wide_score_batches(uint16_t *pool, const float *
 // The evolution shared among workgroups (SHARED).  One workgroup per stream walks the chunks; with few streams the rest of
 // the chip idles while it scores lambda + 64 candidates, so further workgroups (helpers) take shares of the
 // batches.  A chunk's exchange: the stream's workgroup stores the chunk's snapshot (whose pieces are the recall GEMM's
-// operands), publishes `go` (chunk, helpers in use, batches each), scores its own batches, and waits for `done`; a helper
+// operands), publishes `go` (chunk, form of the scores, batches each, helpers in use), scores its own batches, and waits for `done`; a helper
 // waits for `go`, takes H^T and s from the snapshot, and leaves its candidates' squared errors in `score`.
 // No wait depends on a workgroup that may not have a compute unit: helpers join by counting themselves in `joined` after
 // `started` says that the stream's workgroup runs (they leave if that takes too long), only helpers that have joined are
@@ -1590,12 +1781,14 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
     int32_t *sp_idx = a.st.sp_idx + (size_t)si * LAM;
     int32_t *sp_row = a.sp_row + (size_t)si * LAM;
     uint16_t *phiE = reinterpret_cast<uint16_t *>(a.phiE + (size_t)si * (LAM + C) * DF);   // [slot][part][DF] bf16, operand order
+    const bf16_t *Wk = a.Wk + (size_t)(si % a.dm.Hkv) * (DF / 2) * DH;
     const bf16_t *pK = a.prefK + (size_t)si * P * DH, *pV = a.prefV + (size_t)si * P * DH;
     const bf16_t *kc = a.k + (size_t)si * a.T_tokens * DH, *vc = a.v + (size_t)si * a.T_tokens * DH;
     // squared recall error |P|^2 / (phi.s)^2 - 2 P.v / (phi.s) + |v|^2 of candidate e (recall = 0 while phi.s = 0), as bits
-    auto sq_bits = [&](int e) -> uint32_t {
+    auto sq_bits = [&](int e, bool exact) -> uint32_t {
         const float dn = dn_l[e], rd = dn > 0.f ? __builtin_amdgcn_rcpf(dn) : 0.f;
-        return __float_as_uint(fmaxf(fmaf(rd * rd, tot[0][e], fmaf(-2.0f * rd, tot[1][e], tot[2][e])), 0.f)) & 0x7FFFFFFFu;
+        const float sq = exact ? tot[0][e] : fmaxf(fmaf(rd * rd, tot[0][e], fmaf(-2.0f * rd, tot[1][e], tot[2][e])), 0.f);
+        return __float_as_uint(sq) & 0x7FFFFFFFu;
     };
     __shared__ int nh_s, bh_s;
     __shared__ unsigned long long go_s;
@@ -1625,7 +1818,8 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
                 const unsigned long long g = go_s;
                 last = g;
                 if (g == GO_END) return;
-                const int used = (int)(g & 255), bh = (int)((g >> 8) & 255), jj = (int)(g >> 16) - 1;
+                const int used = (int)(g & 255), bh = (int)((g >> 8) & 127), jj = (int)(g >> 16) - 1;
+                const bool exact = (g >> 15) & 1;
                 if (rank < used) {
                     const int j = a.jb + jj, vrow_l = LAM + j * C, b1 = NBATCH - rank * bh, b0 = b1 - bh;
                     const size_t sj = (size_t)si * a.S + jj;
@@ -1646,8 +1840,9 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
                         const int vr = vrow_l + (e - LAM);
                         return vr < P ? pV + (size_t)vr * DH : vc + (size_t)(vr - P) * DH;
                     };
-                    wide_score_batches<DH, DF>(pool, s_l, dn_l, tot, part, Ahi, Alo, b0, b1, tid, phirow, vrow);
-                    for (int e = b0 * RB + tid; e < b1 * RB; e += NTH) agent_store(&score_x[e], sq_bits(e));
+                    if (exact) wide_score_batches<DH, DF, false, true>(pool, s_l, dn_l, tot, part, Ahi, Alo, b0, b1, tid, phirow, vrow);
+                    else wide_score_batches<DH, DF>(pool, s_l, dn_l, tot, part, Ahi, Alo, b0, b1, tid, phirow, vrow);
+                    for (int e = b0 * RB + tid; e < b1 * RB; e += NTH) agent_store(&score_x[e], sq_bits(e, exact));
                     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
                 }
                 __syncthreads();
@@ -1770,7 +1965,7 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
                 const int bh = max(1, (NBATCH - SHARE_LEAD + nh) / (nh + 1)), used = min(nh, (NBATCH - 1) / bh);
                 if (used > 0) {
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-                    agent_store(&sh->go, ((unsigned long long)(j - a.jb + 1) << 16) | (unsigned long long)(bh << 8) | (unsigned long long)used);
+                    agent_store(&sh->go, ((unsigned long long)(j - a.jb + 1) << 16) | (unsigned long long)((nf < C ? 1 << 15 : 0) | (bh << 8) | used));
                 }
                 nh_s = used; bh_s = bh;
             }
@@ -1778,7 +1973,10 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
             nown = NE - nh_s * bh_s * RB;
             want += nh_s;
         }
-        if (!SCORED && LAM > 0) wide_score_batches<DH, DF, SHARED>(pool, s_l, dn_l, tot, part, Ahi, Alo, 0, SHARED ? nown / RB : NBATCH, tid, phirow, vrow);
+        if (!SCORED && LAM > 0) {
+            if (nf < C) wide_score_batches<DH, DF, SHARED, true>(pool, s_l, dn_l, tot, part, Ahi, Alo, 0, SHARED ? nown / RB : NBATCH, tid, phirow, vrow);
+            else wide_score_batches<DH, DF, SHARED>(pool, s_l, dn_l, tot, part, Ahi, Alo, 0, SHARED ? nown / RB : NBATCH, tid, phirow, vrow);
+        }
         if constexpr (SHARED) {
             if (nown < NE) {
                 if (tid == 0) {
@@ -1813,7 +2011,7 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
             }
         } else {
         for (int e = tid; e < NE; e += NTH) {
-            const uint32_t sq = SHARED && e >= nown ? agent_load(&score_x[e]) : sq_bits(e);
+            const uint32_t sq = SHARED && e >= nown ? agent_load(&score_x[e]) : sq_bits(e, nf < C);
             skey[e] = (e < LAM ? e < spc : e < LAM + cl) ? sq : 0xFFFFFFFFu;
         }
         }
@@ -1895,45 +2093,14 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
         // gathered into LDS ([pair][part][position] and [pair][column], 16-byte pieces XOR-swizzled with bits of the pair number: fswz, vswz2)
         uint16_t *FP = pool, *FV = pool + C * FR;
 #pragma unroll
-        for (int it = 0; it < C * FR / 512 / NW; it++) {
-            const int i = w + NW * it, g = 512 * i + 8 * lane, row = g / FR, pt = (g % FR) / DF, slot = (g % DF) >> 3;
-            const uint16_t *src = phirow(flist[row]) + pt * DF + ((slot ^ fswz(row)) << 3);
-            lds_dma16(src, FP + 512 * i);
-        }
-#pragma unroll
         for (int it = 0; it < C * DH / 512 / NW; it++) {
             const int i = w + NW * it, g = 512 * i + 8 * lane, row = g / DH, slot = (g % DH) >> 3;
             const bf16_t *src = vrow(flist[row]) + ((slot ^ vswz2<PR>(row)) << 3);
             lds_dma16(src, FV + 512 * i);
         }
-        // compaction, first half: the entrants' rows (keys, values, features) are requested now and stored after the fold
-        constexpr int CIT = C * 2 * PR / NTH, PIT = C * (FR / 8) / NTH;
-        uint4 cp[CIT], fe[PIT];
-#pragma unroll
-        for (int it = 0; it < CIT; it++) {
-            const int o = tid + NTH * it;
-            cp[it] = make_uint4(0, 0, 0, 0);
-            if (o < ne * 2 * PR) {
-                const int x = o / (2 * PR), rem = o % (2 * PR), e = ecand[x];
-                cp[it] = reinterpret_cast<const uint4 *>((rem >= PR) ? vrow(e) : krow(e))[rem % PR];
-            }
-        }
-#pragma unroll
-        for (int it = 0; it < PIT; it++) {
-            const int o = tid + NTH * it;
-            fe[it] = make_uint4(0, 0, 0, 0);
-            if (o < ne * (FR / 8)) fe[it] = reinterpret_cast<const uint4 *>(phirow(ecand[o / (FR / 8)]))[o % (FR / 8)];
-        }
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-        lds_barrier();
-        if (nf < C) {   // fewer than 64 folded pairs: the rest of the contraction is zeros
-            uint4 *fp0 = reinterpret_cast<uint4 *>(FP + nf * FR), *fv0 = reinterpret_cast<uint4 *>(FV + nf * DH);
-            for (int x = tid; x < (C - nf) * (FR / 8); x += NTH) fp0[x] = make_uint4(0, 0, 0, 0);
-            for (int x = tid; x < (C - nf) * PR; x += NTH) fv0[x] = make_uint4(0, 0, 0, 0);
-            lds_barrier();
-        }
         // contraction slots of lane group g4 in k-step kst: pairs 32 kst + 4 g4 + 0..3, then + 16 (the order in which the
         // transposing read delivers them, the same for both operands)
+        auto fold = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int kst = 0; kst < 2; kst++) {
             const int t0 = 32 * kst + 4 * g4 + (r16 >> 2), t15 = fswz(t0);
@@ -1981,6 +2148,95 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
                     *sp = sv;
                 }
             }
+        }
+        };
+        if (nf < C) {
+            // A chunk that folds fewer than 64 pairs (the first scored one of a call, a ragged last one) folds with fp32
+            // features, as the shape-generic evolution does: what the two bf16 parts leave of them (see scan_fast_kernel) is
+            // folded ahead of the parts.
+#pragma unroll 1
+            for (int t = w; t < C / 16; t += NW) {
+                const int ep = 16 * t + r16, ef = flist[ep];
+                const bf16_t *kr = krow(ef);
+                bf16x8 BK[DH / 32];
+#pragma unroll
+                for (int ks = 0; ks < DH / 32; ks++) BK[ks] = ld_bf16x8(kr + 32 * ks + 8 * g4);
+                f32x4 zt[NMT / 2];
+#pragma unroll
+                for (int mt = 0; mt < NMT / 2; mt++) {
+                    zt[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < DH / 32; ks++)
+                        zt[mt] = mfma16(ld_bf16x8(Wk + (size_t)(16 * mt + r16) * DH + 32 * ks + 8 * g4), BK[ks], zt[mt]);
+                    __builtin_amdgcn_sched_barrier(0);   // (the loads of all tiles at once would not fit the registers)
+                }
+                const PhiNorm nm = phi_norm<NMT / 2>(zt, a.dm.phi_kind);
+#pragma unroll
+                for (int ks = 0; ks < KF; ks++) {   // piece 4 ks + g4 of the pair's row (operand order, see phi_wide_kernel)
+                    const uint16_t *q = phirow(ef) + ((4 * ks + g4) << 3);
+                    const uint4 hi = *reinterpret_cast<const uint4 *>(q), lo = *reinterpret_cast<const uint4 *>(q + DF);
+                    bf16x8 r;
+#pragma unroll
+                    for (int x = 0; x < 8; x++) {
+                        const uint32_t uh = (&hi.x)[x >> 1], ul = (&lo.x)[x >> 1];
+                        const float z = zt[2 * (ks % (KF / 2)) + (x >> 2)][x & 3];
+                        const float f = ks < KF / 2 ? fexp2(fmaf(z, LOG2E, nm.cp)) * nm.ip : fexp2(fmaf(z, -LOG2E, nm.cn)) * nm.in;
+                        r[x] = (__bf16)(f - ((x & 1) ? bf_hi(uh) : bf_lo(uh)) - ((x & 1) ? bf_hi(ul) : bf_lo(ul)));
+                    }
+                    uint16_t *p = FP + ep * FR + (((4 * ks + g4) ^ fswz(ep)) << 3);
+                    *reinterpret_cast<uint4 *>(p) = ep < nf ? __builtin_bit_cast(uint4, r) : make_uint4(0, 0, 0, 0);
+                    *reinterpret_cast<uint4 *>(p + DF) = make_uint4(0, 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the values
+            lds_barrier();
+            uint4 *fv0 = reinterpret_cast<uint4 *>(FV + nf * DH);   // (the rest of the contraction is zeros)
+            for (int x = tid; x < (C - nf) * PR; x += NTH) fv0[x] = make_uint4(0, 0, 0, 0);
+            lds_barrier();
+            // the chunk's sum is taken by itself; H^T waits in its place in memory
+            float *hrow = Hg + (size_t)(16 * w0 + (tid0 & 15)) * DF + 4 * ((tid0 & 63) >> 4);
+#pragma unroll
+            for (int mt = 0; mt < NMT; mt++) { *reinterpret_cast<f32x4 *>(hrow + 16 * mt) = hacc[mt]; hacc[mt] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+            fold();
+            lds_barrier();
+        }
+#pragma unroll
+        for (int it = 0; it < C * FR / 512 / NW; it++) {
+            const int i = w + NW * it, g = 512 * i + 8 * lane, row = g / FR, pt = (g % FR) / DF, slot = (g % DF) >> 3;
+            const uint16_t *src = phirow(flist[row]) + pt * DF + ((slot ^ fswz(row)) << 3);
+            lds_dma16(src, FP + 512 * i);
+        }
+        // compaction, first half: the entrants' rows (keys, values, features) are requested now and stored after the fold
+        constexpr int CIT = C * 2 * PR / NTH, PIT = C * (FR / 8) / NTH;
+        uint4 cp[CIT], fe[PIT];
+#pragma unroll
+        for (int it = 0; it < CIT; it++) {
+            const int o = tid + NTH * it;
+            cp[it] = make_uint4(0, 0, 0, 0);
+            if (o < ne * 2 * PR) {
+                const int x = o / (2 * PR), rem = o % (2 * PR), e = ecand[x];
+                cp[it] = reinterpret_cast<const uint4 *>((rem >= PR) ? vrow(e) : krow(e))[rem % PR];
+            }
+        }
+#pragma unroll
+        for (int it = 0; it < PIT; it++) {
+            const int o = tid + NTH * it;
+            fe[it] = make_uint4(0, 0, 0, 0);
+            if (o < ne * (FR / 8)) fe[it] = reinterpret_cast<const uint4 *>(phirow(ecand[o / (FR / 8)]))[o % (FR / 8)];
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+        lds_barrier();
+        if (nf < C) {   // fewer than 64 folded pairs: the rest of the contraction is zeros
+            uint4 *fp0 = reinterpret_cast<uint4 *>(FP + nf * FR);
+            for (int x = tid; x < (C - nf) * (FR / 8); x += NTH) fp0[x] = make_uint4(0, 0, 0, 0);
+            lds_barrier();
+        }
+        fold();
+        if (nf < C) {
+            const float *hrow = Hg + (size_t)(16 * w0 + (tid0 & 15)) * DF + 4 * ((tid0 & 63) >> 4);
+#pragma unroll
+            for (int mt = 0; mt < NMT; mt++) hacc[mt] += *reinterpret_cast<const f32x4 *>(hrow + 16 * mt);
         }
         // ---- 5. compaction, second half: entrants take the leavers' slots (rows of the state, features, indices)
 #pragma unroll

@@ -70,6 +70,50 @@ def test_calls_that_end_while_window_and_cache_fill(d, D, eta, lam, kw):
         P.prefill_parity(sh, q[:, :, :T], k[:, :, :T], v[:, :, :T], Wq, Wk, layer_kw=kw, workspace_limit=0)
 
 
+IRREGULAR = [(128, 128, 64, 128, {}), (64, 128, 64, 64, {}), (128, 128, 64, 64, {}), (128, 128, 64, 256, {}), (64, 128, 64, 256, {}), (128, 256, 128, 128, {}),
+             (64, 256, 64, 512, {}), (128, 128, 128, 64, {}), (64, 128, 128, 192, {}), (128, 128, 64, 128, dict(phi_kind=1)), (128, 256, 128, 192, dict(phi_kind=1))]
+
+
+def irregular_calls(eta, lam):
+    """(first and last token of each call): one that ends 40 tokens behind the full cache, or that fills it and then 24 short ones"""
+    short = [int(x) for x in wl.rng(eta + lam, 7).integers(1, 64, 24)]
+    for lens in ([eta + lam + 40], [eta + lam] + short):
+        cuts = np.concatenate([[0], np.cumsum(lens)])
+        yield [(int(a), int(b)) for a, b in zip(cuts, cuts[1:])]
+
+
+@pytest.mark.parametrize("d,D,eta,lam,kw", IRREGULAR + [(64, 256, 128, 0, {}), (128, 128, 64, 128, dict(score_kind=1))])
+def test_irregular_chunks_fold_in_fp32(d, D, eta, lam, kw):
+    """Chunks that fold fewer than 64 pairs (the first scored one, ragged last ones) fold fp32 features as the shape-generic
+    kernels do: H and s stay within 2^-20 of the oracle, sixteen roundings of 2^-24 for the feature and the sums; features in
+    two bf16 parts leave 2^-18 of each product (H off by more than 2.5e-6)."""
+    sh = wl.Shape("irr", "bf16", 2, 4, 2, d, D, T=0, eta=eta, lam=lam, C=64, seed=0)
+    for calls in irregular_calls(eta, lam):
+        q, k, v, Wq, Wk = case_inputs(11 + d + D + lam, 2, 4, 2, d, D, calls[-1][1], wscale=0.5 if kw.get("phi_kind") else 1.0)
+        layer, o = None, None
+        for a, b in calls:
+            print("irregular", d, D, eta, lam, kw, a, b, flush=True)
+            layer, o, rep = P.prefill_parity(sh, q[:, :, a:b], k[:, :, a:b], v[:, :, a:b], Wq, Wk, layer=layer, oracle=o, layer_kw=kw)
+        assert layer.lola_path[0] == "mfma" and rep["scored"] > 0 or lam == 0
+        assert rep["H_err"] < 2.0 ** -20 and rep["s_err"] < 2.0 ** -20, (rep["H_err"], rep["s_err"])
+
+
+@pytest.mark.parametrize("d,D,eta,lam,kw", IRREGULAR)
+def test_irregular_chunks_rank_close_recalls(d, D, eta, lam, kw):
+    """Values of a large common mean (4 and steps of its bf16 spacing): the recalls come within a percent of them, and the
+    differences that rank the pairs are lost in |P|^2 - 2 P.v + |v|^2 (2^-23 |v|^2 = 2e-4 against squared errors of 0.03).
+    Selections outside the tie band must be the oracle's."""
+    sh = wl.Shape("close", "bf16", 2, 4, 2, d, D, T=0, eta=eta, lam=lam, C=64, seed=0)
+    for calls in irregular_calls(eta, lam):
+        N = calls[-1][1]
+        q, k, v, Wq, Wk = case_inputs(21 + d + D + lam, 2, 4, 2, d, D, N, wscale=0.5 if kw.get("phi_kind") else 1.0)
+        v = (4.0 + 2.0 ** -5 * wl.rng(d + lam, 9).integers(-2, 3, v.shape)).astype(np.float32)
+        layer, o = None, None
+        for a, b in calls:
+            print("close", d, D, eta, lam, kw, a, b, flush=True)
+            layer, o, _ = P.prefill_parity(sh, q[:, :, a:b], k[:, :, a:b], v[:, :, a:b], Wq, Wk, layer=layer, oracle=o, layer_kw=kw)
+
+
 @pytest.mark.parametrize("d,D,eta,lam,kw", [(128, 256, 64, 512, {}), (64, 128, 128, 64, {}), (64, 256, 1, 128, {}), (128, 128, 64, 64, dict(score_kind=2))])
 def test_step_with_sequences_at_different_stages(d, D, eta, lam, kw):
     """One batch holds an empty sequence, sequences that fill their window or cache at different steps, and one in steady
