@@ -694,6 +694,8 @@ struct PrefillArgs {
     float *tok_score;         // [B*Hkv][eta + T] query-dependent scores: entry window (virtual rows lam ..), then the call's tokens
     int R2;                   // keys / queries per tile of band_score_kernel
     int piece;                // number of the state-evolution launch within the pass
+    int j_end;                // end of the pass
+    float chunk_us, beside_us;   // estimates for the shared evolution: a scored chunk on one workgroup, the outputs beside this launch
     int fill_closed;          // 1: prefix_kernel does the call's filling chunks (below), the state-evolution kernels start at the first
                               // scored chunk; 0: the shape-generic evolution does every chunk
 };

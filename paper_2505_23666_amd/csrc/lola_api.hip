@@ -393,6 +393,18 @@ constexpr size_t OVERLAP_MIN_WORK = 2048;     // output workgroups (in units of 
                                               // eta = lambda = 256 1.04 -> 1.00 ms, 1024 measures the same)
 constexpr int SHARE_MAX_WGS = 128;            // evolution workgroups at most where helpers are used
 constexpr int SHARE_MAX_HELPERS = 7;          // helpers per stream at most
+constexpr float SHARE_BESIDE = 0.77f;         // a piece beside outputs has helpers while its chain takes longer than this share of
+                                              // them: where the outputs take 1.2 times the chain helpers still pay (3 x 2048 tokens at
+                                              // eta = lambda = 512 0.95 ms without, 0.89 with), where they take 1.4 times no longer (4 x
+                                              // 2048: 1.00 ms without, 1.10 with)
+
+// us of the whole chip per output workgroup at the run-time shapes (64 queries of one head): key blocks of 128 and the rest.  By
+// kernel trace at head_dim 128: 0.096 (5 blocks) and 0.149 (9) with 128 features, 0.120, 0.171 and 0.218 (5, 9, 13) with 256;
+// at 64: 0.042 (5, 128 features), 0.056 and 0.101 (5, 11; 256).
+float output_wg_us(const lola_config *c) {
+    const float blocks = (float)((c->sparse_budget + c->window + 64 + 127) / 128);
+    return (float)c->head_dim / 128.f * (0.0133f * blocks + (c->feat_dim == 256 ? 0.052f : 0.028f));
+}
 
 std::mutex side_init_mu;   // creation of the per-device entries
 std::mutex side_use_mu;    // held by a call from its first fork to its join: the events are shared
@@ -595,16 +607,19 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                 // (a compile-time shape whose cache does not stay in LDS takes its features the run-time way)
                 const bool big = !wide && c->sparse_budget > 128;
                 // Few streams: further workgroups score shares of the candidates (prefill_mfma.h, WideShare).  A chunk costs a
-                // stream's workgroup about 12 us + 2 us per batch alone and an exchange of about 7 us (by difference) when shared, so a helper
-                // is worth its compute unit from about six batches on, and at most half of the compute units go to the
-                // evolution, the rest to the outputs beside it: 2 x 4096 tokens at eta 512 / lambda 1024 3.70 ms alone, 2.02 with
-                // 3 helpers per stream, 1.93 with 5, 1.98 with 7, 2.23 with 15; 4 x 2048 at eta = lambda = 256 1.06 ms alone, 1.00 with 1
-                // helper, 1.03 with 3, 1.16 with 7.
+                // stream's workgroup about 12 us + 2 us per batch alone and an exchange of about 7 us (by difference) when shared, so a
+                // helper is worth its compute unit from about six batches on, and at most half of the compute units go to the
+                // evolution: 2 x 4096 tokens at eta 512 / lambda 1024 3.70 ms alone, 2.02 with 3 helpers per stream, 1.93 with 5, 1.98
+                // with 7, 2.23 with 15; 4 x 2048 at eta = lambda = 256 1.06 ms alone, 1.00 with 1 helper, 1.03 with 3, 1.16 with 7.
+                // A piece that runs beside outputs (below) gets them only if its chain is what the call waits for: 8 x 2048 tokens (64
+                // streams) at eta = lambda = 256 1.53 ms without helpers, 1.55 with one in every piece, 1.48 by this rule; at 512 1.81,
+                // 1.85 and 1.79; at eta 64 / lambda 512, 128 features 1.26, 1.28 and 1.21.
                 int helpers = 0;
-                if (wide && a.want_out && !a.dm.score_kind) {
-                    const int batches = (c->sparse_budget + 64) / (c->feat_dim == 256 ? 32 : 64);
+                const int batches = (c->sparse_budget + 64) / (c->feat_dim == 256 ? 32 : 64);
+                if (wide && a.want_out && !a.dm.score_kind)
                     helpers = std::max(0, std::min({batches / 6, SHARE_MAX_WGS / (int)ns - 1, SHARE_MAX_HELPERS}));
-                }
+                a.chunk_us = 12.f + 2.f * batches;
+                a.j_end = jend;
                 if (!wide && !big) {
                     const dim3 gp((unsigned)(jend - j0), (unsigned)ns);
                     if (c->head_dim == 128) hipLaunchKernelGGL(fast::phi_k_kernel<128>, gp, dim3(256), 0, stream, a);
@@ -680,10 +695,15 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                     // register file, should be resident before the output workgroups arrive, instead of queueing for
                     // compute units behind them.
                     a.piece = ip;
+                    // What runs beside this piece: the outputs from the piece before it on, on the compute units that the evolution
+                    // leaves.  While they take longer than the chain from here on, a helper's compute unit is theirs (the chain
+                    // as if every chunk were scored; the kernel, which knows, looks again).
+                    a.beside_us = side && ip > 0 ? SHARE_BESIDE * output_wg_us(c) * (float)(jend - prev0) * a.dm.Hq * a.dm.B * CHIP_CUS / (float)(CHIP_CUS - (int)ns) : 0.f;
+                    const bool shared = helpers > 0 && a.chunk_us * (float)(jend - p0) > a.beside_us;
                     if (wide) {
 #define LOLA_WSCAN(DHV, DFV) do { if (side && ip > 0 && hipEventRecord(side->fork[ip - 1], stream) != hipSuccess) return LOLA_ERR_HIP; \
                                   if (a.dm.score_kind) hipLaunchKernelGGL((fast::scan_wide_kernel<DHV, DFV, true>), gs, dim3(DHV * 4), 0, stream, a); \
-                                  else if (helpers > 0) hipLaunchKernelGGL((fast::scan_wide_kernel<DHV, DFV, false, true>), dim3((unsigned)(ns * (1 + helpers))), dim3(DHV * 4), 0, stream, a); \
+                                  else if (shared) hipLaunchKernelGGL((fast::scan_wide_kernel<DHV, DFV, false, true>), dim3((unsigned)(ns * (1 + helpers))), dim3(DHV * 4), 0, stream, a); \
                                   else hipLaunchKernelGGL((fast::scan_wide_kernel<DHV, DFV, false>), gs, dim3(DHV * 4), 0, stream, a); } while (0)
                         if (c->head_dim == 128) { if (c->feat_dim == 256) LOLA_WSCAN(128, 256); else LOLA_WSCAN(128, 128); }
                         else { if (c->feat_dim == 256) LOLA_WSCAN(64, 256); else LOLA_WSCAN(64, 128); }

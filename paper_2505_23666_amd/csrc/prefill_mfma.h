@@ -1798,6 +1798,8 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
     if constexpr (SHARED) {
         if ((int)blockIdx.x >= nstreams) {   // a helper
             const int tid = tid0, lane = tid & 63;
+            // (the outputs beside this launch take longer than the scored chunks from here on: the compute unit is theirs)
+            if (a.beside_us > 0.f && a.chunk_us * (float)(a.j_end - max(a.j0, generic::first_scored_chunk(a, a.st.n_tokens[si], a.st.sp_count[si]))) <= a.beside_us) return;
             if (tid == 0) {
                 int on = 0;
                 for (int it = 0; it < 64 && !on; it++) { on = agent_load(&sh->started); if (!on) __builtin_amdgcn_s_sleep(8); }

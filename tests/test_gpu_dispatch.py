@@ -143,6 +143,39 @@ def test_step_with_sequences_at_different_stages(d, D, eta, lam, kw):
                 assert torch.equal(getattr(batch, nm)[b], getattr(lay, nm)[0]), (i, b, nm)
 
 
+PIECES = 8   # launches of the state evolution in a pass at most
+
+
+def shares(layer, T, with_outputs=True):
+    """What the helpers of the shared evolution did in the last pass of the layer's last call, from the exchange words behind the
+    cache slots' features in its workspace: per piece and stream, the helpers that joined and the shares they finished."""
+    up = lambda x: (x + 255) // 256 * 256
+    ns, rows = layer.B * layer.Hkv, layer.lam + layer.eta
+    off = 2 * up(ns * rows * layer.d * 2) + up(ns * layer.lam * 4)
+    words = layer.workspace[off:off + ns * (layer.lam + 64) * layer.D * 4].view(torch.int32).view(ns, (layer.lam + 64) * layer.D)
+    words = words[:, layer.lam * layer.D:layer.lam * layer.D + PIECES * 96].reshape(ns, PIECES, 96).cpu().numpy()
+    return words[:, :, 1].T, words[:, :, 64].T
+
+
+@pytest.mark.parametrize("B,Hq,d,D,eta,lam,T,first,second", [(8, 32, 128, 256, 128, 256, 2048, True, False), (8, 32, 128, 128, 64, 512, 2048, True, False),
+                                                           (2, 32, 128, 256, 64, 1024, 2100, True, True), (4, 32, 128, 256, 512, 1024, 2048, False, False)])
+def test_helpers_beside_outputs(B, Hq, d, D, eta, lam, T, first, second):
+    """Outputs on the second stream: the first piece, with nothing beside it, has its helpers (if any of its chunks is scored);
+    the second piece only where the chain of scored chunks, not the outputs beside it, is what the call waits for."""
+    sh = wl.Shape("rule", "bf16", B, Hq, 8, d, D, T=0, eta=eta, lam=lam, C=64, seed=0)
+    g = torch.Generator(device=P.DEV).manual_seed(B + lam)
+    mk = lambda *shape: torch.randn(shape, generator=g, device=P.DEV).to(torch.bfloat16)
+    Wq, Wk = mk(Hq, D // 2, d) / d ** 0.5, mk(8, D // 2, d) / d ** 0.5
+    q, k, v = mk(B, Hq, T, d), mk(B, 8, T, d), mk(B, 8, T, d)
+    layer = P.make_layer(sh, prefill_overlap=1)
+    layer.prefill(q, k, v, Wq, Wk)
+    torch.cuda.synchronize()
+    joined, done = shares(layer, T)
+    print("helpers", B, Hq, d, D, eta, lam, T, joined.max(1), done.max(1), flush=True)
+    assert bool((joined[0] > 0).all()) and bool((done[0] > 0).all()) == first
+    assert bool((joined[1] > 0).all()) == bool(joined[1].any()) == second
+
+
 @pytest.mark.parametrize("B,Hkv,d,D,eta,lam,T,limit,kw", [
     (1, 1, 128, 256, 64, 1024, 1600, None, {}), (1, 3, 64, 256, 128, 512, 1111, None, {}), (2, 8, 128, 128, 64, 512, 1024, None, dict(prefill_overlap=1)),
     (4, 8, 128, 256, 64, 512, 960, None, {}), (1, 2, 64, 128, 64, 768, 1000, 0, {}), (2, 8, 128, 256, 64, 1024, 1537, 40 << 20, dict(phi_kind=1)),
