@@ -388,9 +388,12 @@ constexpr int CHIP_CUS = 256;                 // compute units of the MI355X
 constexpr size_t OVERLAP_MAX_STREAMS = 128;   // beyond this many streams the serial evolution fills the chip by itself
 constexpr int OVERLAP_MIN_PIECE = 8;          // chunks per piece on average at least
 constexpr size_t OVERLAP_MIN_WORK = 2048;     // output workgroups (in units of 64 head columns) per piece at least: below
-                                              // this the restart of the evolution costs more than the overlap hides (4096
-                                              // while every piece began with a feature kernel of its own; 4 x 2048 tokens at
-                                              // eta = lambda = 256 1.04 -> 1.00 ms, 1024 measures the same)
+                                              // this the restart of the evolution costs more than the overlap hides (4 x 2048
+                                              // tokens at eta = lambda = 256 1.04 ms with 4096, 1.00 with 2048 and with 1024)
+constexpr size_t OVERLAP_RESTART_WORK = 4096; // the same for the third piece and on at lambda <= 128 and head_dim 64, where a restart
+                                              // recomputes the cached keys' features on four wavefronts: 8 x 2048 tokens at the 1B
+                                              // shape 371 us in two pieces, 379 in four, 8 x 4096 667 and 677; but 4 x 3000 444 in
+                                              // one and 422 in two (at head_dim 128 4 x 2048 tokens 457 in two, 450 in four)
 constexpr int SHARE_MAX_WGS = 128;            // evolution workgroups at most where helpers are used
 constexpr int SHARE_MAX_HELPERS = 7;          // helpers per stream at most
 constexpr float SHARE_BESIDE = 0.77f;         // a piece beside outputs has helpers while its chain takes longer than this share of
@@ -639,7 +642,8 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                 SideStream *side = nullptr;
                 int np = piece / OVERLAP_MIN_PIECE;
                 const size_t work = (size_t)piece * a.dm.Hq * a.dm.B * (size_t)(c->head_dim / 64);
-                if ((size_t)np > work / OVERLAP_MIN_WORK) np = (int)(work / OVERLAP_MIN_WORK);
+                const size_t fed = wide || big || c->head_dim > 64 ? work / OVERLAP_MIN_WORK : std::max(work / OVERLAP_RESTART_WORK, std::min<size_t>(2, work / OVERLAP_MIN_WORK));
+                if ((size_t)np > fed) np = (int)fed;
                 if (np > SideStream::NEV) np = SideStream::NEV;
                 if (allow_side_stream && c->prefill_overlap && a.want_out && ns <= OVERLAP_MAX_STREAMS && np >= 2) side = side_stream(stream);
                 std::unique_lock<std::mutex> side_lock(side_use_mu, std::defer_lock);
