@@ -409,6 +409,8 @@ float output_wg_us(const lola_config *c) {
     return (float)c->head_dim / 128.f * (0.0133f * blocks + (c->feat_dim == 256 ? 0.052f : 0.028f));
 }
 
+static_assert(SideStream::NEV <= fast::WIDE_PIECES, "every piece of a pass has exchange words of its own, cleared ahead of it");
+
 std::mutex side_init_mu;   // creation of the per-device entries
 std::mutex side_use_mu;    // held by a call from its first fork to its join: the events are shared
 
