@@ -423,8 +423,9 @@ __device__ __forceinline__ float query_term(int kind, float logit, float a) {
 // ---------------------------------------------------------------------------------------------
 // state init
 // ---------------------------------------------------------------------------------------------
-// All fields of the memories in one launch: a block fills FILL_WORDS 32-bit words of one field, 16 bytes per lane and store.
-// Bound by launch latency at few streams, by the write bandwidth at many.  One launch per field before: emptying the
+// All fields of the memories in one launch: a block fills `words` 32-bit words of one field, 16 bytes per lane and store:
+// FILL_WORDS, or as many times more as keep the launch below 2^24 blocks (a grid holds fewer than 2^32 threads: states of 256 GiB
+// and more).  Bound by launch latency at few streams, by the write bandwidth at many.  One launch per field before: emptying the
 // memories and a prefill of 8 x 333 tokens at the 8B shape took 327 us, now 313; of 4 x 4096 tokens 854 and 831.
 constexpr int FILL_FIELDS = 14;
 constexpr int FILL_WORDS = 4096;
@@ -433,15 +434,15 @@ struct FillArgs {
     size_t n[FILL_FIELDS];           // words
     uint32_t val[FILL_FIELDS];
     uint32_t end[FILL_FIELDS];       // blocks of the fields up to and including this one
-    int fields;
+    int words;                       // per block, a multiple of 4
 };
 __global__ __launch_bounds__(256) void fill_fields_kernel(FillArgs a) {
     int f = 0;
-    while (blockIdx.x >= a.end[f]) f++;   // (the grid has end[fields - 1] blocks)
-    const size_t w0 = (size_t)(blockIdx.x - (f ? a.end[f - 1] : 0u)) * FILL_WORDS;
+    while (blockIdx.x >= a.end[f]) f++;   // (the grid has as many blocks as the last field's end)
+    const size_t w0 = (size_t)(blockIdx.x - (f ? a.end[f - 1] : 0u)) * a.words;
     const uint32_t val = a.val[f];
     uint32_t *p = a.p[f] + w0;
-    const int n = (int)min((size_t)FILL_WORDS, a.n[f] - w0);
+    const int n = (int)min((size_t)a.words, a.n[f] - w0);
     const uint4 v4 = make_uint4(val, val, val, val);
     for (int i = threadIdx.x; i < n / 4; i += 256) reinterpret_cast<uint4 *>(p)[i] = v4;
     for (int i = (n & ~3) + (int)threadIdx.x; i < n; i += 256) p[i] = val;

@@ -815,14 +815,17 @@ lola_status lola_state_init(const lola_config *c, const lola_state *st, void *st
                       c->fold_defer ? st->pend_count : nullptr, sk ? st->win_score : nullptr, sk ? st->sp_score : nullptr};
     static_assert(generic::FILL_FIELDS == 14, "one fill per field");
     generic::FillArgs fa;
-    fa.fields = 0;
+    fa.words = generic::FILL_WORDS;
+    auto share = [&](size_t bytes) { return (bytes / 4 + fa.words - 1) / fa.words; };   // every field is a multiple of 4 bytes (head_dim is even)
+    auto total = [&]() { size_t n = 0; for (int i = 0; i < 14; i++) if (ptrs[i]) n += share(fb[i]); return n; };
+    while (total() >= (size_t)1 << 24) fa.words *= 2;
+    int fields = 0;
     uint32_t blocks = 0;
     for (int i = 0; i < 14; i++) {
         if (!ptrs[i] || fb[i] == 0) continue;
-        const size_t n = fb[i] / 4;   // every field is a multiple of 4 bytes (head_dim is even)
-        blocks += (uint32_t)((n + generic::FILL_WORDS - 1) / generic::FILL_WORDS);
-        fa.p[fa.fields] = (uint32_t *)ptrs[i]; fa.n[fa.fields] = n;
-        fa.val[fa.fields] = i == 6 ? 0xFFFFFFFFu : 0u; fa.end[fa.fields++] = blocks;
+        blocks += (uint32_t)share(fb[i]);
+        fa.p[fields] = (uint32_t *)ptrs[i]; fa.n[fields] = fb[i] / 4;
+        fa.val[fields] = i == 6 ? 0xFFFFFFFFu : 0u; fa.end[fields++] = blocks;
     }
     hipLaunchKernelGGL(generic::fill_fields_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, fa);
     LAUNCH_CHECK();

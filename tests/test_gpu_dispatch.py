@@ -34,6 +34,29 @@ def test_reset_empties_every_field(B, Hkv, d, D, eta, lam, kw):
         assert bool((raw[nb:] == 0x5A).all()), n
 
 
+def test_reset_of_more_memories_than_a_grid_of_blocks():
+    """Fields that together pass 256 GiB need more than one launch grid of the usual blocks.  The four K / V fields (64 GiB each)
+    share one buffer here."""
+    from paper_2505_23666_amd import binding as lb
+    ns, d, D, rows = 16400, 256, 2, 4096
+    cfg = lb.LolaConfig(ns, 1, 1, d, D, rows, rows, 16, lb.LOLA_F32, lb.LOLA_F32, 0, 0.0, 0, 0, 0, 0)
+    tot, fb = lb.lola_state_bytes(cfg)
+    assert tot >> 38 and fb[2] == fb[3] == fb[4] == fb[5]
+    torch.cuda.empty_cache()
+    size = {0: fb[0], 1: fb[1], 2: fb[2], 6: fb[6], 7: fb[7], 8: fb[8]}
+    bufs = {i: torch.full((n + 64,), 0x5A, dtype=torch.uint8, device=P.DEV) for i, n in size.items()}
+    st = lb.LolaState(*[bufs[2 if 2 <= i <= 5 else i].data_ptr() if i < 9 else None for i in range(14)])
+    lb.lola_state_init(cfg, st)
+    torch.cuda.synchronize()
+    for i, n in size.items():
+        raw, want = bufs[i], 0xFF if i == 6 else 0
+        for a in range(0, n, 1 << 30):
+            assert bool((raw[a:min(n, a + (1 << 30))] == want).all()), (i, a)
+        assert bool((raw[n:] == 0x5A).all()), i
+    del bufs, raw
+    torch.cuda.empty_cache()
+
+
 def case_inputs(seed, B, Hq, Hkv, d, D, N, wscale=1.0):
     g = wl.rng(seed, 5)
     mk = lambda *shape: wl.store(g.standard_normal(shape, dtype=np.float32), "bf16")
