@@ -64,7 +64,7 @@ def case_inputs(seed, B, Hq, Hkv, d, D, N, wscale=1.0):
     return mk(B, Hq, N, d), mk(B, Hkv, N, d), mk(B, Hkv, N, d), w(Hq), w(Hkv)
 
 
-@pytest.mark.parametrize("d,D,eta,lam,kw", [(128, 128, 64, 128, {}), (64, 128, 64, 64, {}), (128, 128, 64, 256, dict(prefill_overlap=1)),
+@pytest.mark.parametrize("d,D,eta,lam,kw", [(128, 128, 64, 128, {}), (64, 128, 64, 64, {}), (128, 128, 64, 256, {}),
                                             (64, 128, 64, 256, {}), (128, 256, 128, 192, {}), (64, 256, 192, 64, dict(phi_kind=1)),
                                             (128, 128, 128, 0, {}), (64, 256, 192, 0, {}), (128, 128, 64, 128, dict(score_kind=4)),
                                             (128, 256, 64, 128, dict(score_kind=1))])
@@ -169,7 +169,7 @@ def test_step_with_sequences_at_different_stages(d, D, eta, lam, kw):
 PIECES = 8   # launches of the state evolution in a pass at most
 
 
-def shares(layer, T, with_outputs=True):
+def shares(layer):
     """What the helpers of the shared evolution did in the last pass of the layer's last call, from the exchange words behind the
     cache slots' features in its workspace: per piece and stream, the helpers that joined and the shares they finished."""
     up = lambda x: (x + 255) // 256 * 256
@@ -193,20 +193,21 @@ def test_helpers_beside_outputs(B, Hq, d, D, eta, lam, T, first, second):
     layer = P.make_layer(sh, prefill_overlap=1)
     layer.prefill(q, k, v, Wq, Wk)
     torch.cuda.synchronize()
-    joined, done = shares(layer, T)
+    joined, done = shares(layer)
     print("helpers", B, Hq, d, D, eta, lam, T, joined.max(1), done.max(1), flush=True)
     assert bool((joined[0] > 0).all()) and bool((done[0] > 0).all()) == first
     assert bool((joined[1] > 0).all()) == bool(joined[1].any()) == second
 
 
 @pytest.mark.parametrize("B,Hkv,d,D,eta,lam,T,limit,kw", [
-    (1, 1, 128, 256, 64, 1024, 1600, None, {}), (1, 3, 64, 256, 128, 512, 1111, None, {}), (2, 8, 128, 128, 64, 512, 1024, None, dict(prefill_overlap=1)),
+    (1, 1, 128, 256, 64, 1024, 1600, None, {}), (1, 3, 64, 256, 128, 512, 1111, None, {}), (4, 8, 128, 128, 64, 512, 2100, None, dict(prefill_overlap=1)),
     (4, 8, 128, 256, 64, 512, 960, None, {}), (1, 2, 64, 128, 64, 768, 1000, 0, {}), (2, 8, 128, 256, 64, 1024, 1537, 40 << 20, dict(phi_kind=1)),
-    (2, 4, 128, 256, 128, 256, 1500, None, dict(prefill_overlap=1)), (2, 32, 128, 256, 64, 512, 800, None, {})])
+    (2, 8, 128, 256, 64, 1024, 4200, None, dict(prefill_overlap=1)), (4, 4, 128, 256, 128, 256, 4130, None, dict(prefill_overlap=1)), (2, 32, 128, 256, 64, 512, 800, None, {})])
 def test_evolution_shared_among_workgroups(B, Hkv, d, D, eta, lam, T, limit, kw):
     """With outputs and few streams the candidates' scores come from several workgroups per stream; an update-only call
     stays on one. The same instructions on the same operands: the memories agree bit for bit, over several launches and
-    workspace passes, a ragged last chunk and a second call that starts with a full cache."""
+    workspace passes, a ragged last chunk and a second call that starts with a full cache.  With the outputs beside it the
+    evolution runs in pieces of its own, one or several helpers per stream in the first and the second."""
     sh = wl.Shape("shared", "bf16", B, 2 * Hkv, Hkv, d, D, T=0, eta=eta, lam=lam, C=64, seed=0)
     q, k, v, Wq, Wk = case_inputs(90 + d + D + lam, B, 2 * Hkv, Hkv, d, D, T + 130, wscale=0.5 if kw.get("phi_kind") else 1.0)
     dq, dk, dv, dWq, dWk = P.to_dev(q, "bf16"), P.to_dev(k, "bf16"), P.to_dev(v, "bf16"), P.w_to_dev(Wq, "bf16"), P.w_to_dev(Wk, "bf16")
@@ -214,11 +215,79 @@ def test_evolution_shared_among_workgroups(B, Hkv, d, D, eta, lam, T, limit, kw)
     for a, b in ((0, T), (T, T + 130)):
         q1, k1, v1 = (x[:, :, a:b].contiguous() for x in (dq, dk, dv))
         print("shared", B, Hkv, d, D, eta, lam, a, b, flush=True)
-        _, t_many = many.prefill(q1, k1, v1, dWq, dWk, trace=True, workspace_limit=limit)
+        out, t_many = many.prefill(q1, k1, v1, dWq, dWk, trace=True, workspace_limit=limit)
+        torch.cuda.synchronize()
+        joined, done = shares(many)
+        print("   helpers", joined.max(1), "shares", done.max(1), flush=True)
+        if limit is None:   # (a pass of one chunk may be over before a helper has joined)
+            assert bool((joined[0] > 0).all()) and bool((done > 0).any(0).all())
+        if kw.get("prefill_overlap") and a == 0:   # (the second call is too short for pieces)
+            assert bool((joined[1] > 0).all()) and bool((done[1] > 0).all())
+            apart = P.make_layer(sh)
+            assert torch.equal(apart.prefill(q1, k1, v1, dWq, dWk), out)
         _, t_one = one.prefill(None, k1, v1, dWq, dWk, trace=True, workspace_limit=limit)
+        torch.cuda.synchronize()
+        assert not shares(one)[0].any()
         assert torch.equal(t_many, t_one)
         for nm in FIELDS:
             assert torch.equal(getattr(one, nm), getattr(many, nm)), (a, nm)
+
+
+def test_filling_chunks_in_a_later_piece():
+    """Outputs beside the evolution while the caches still fill in the second piece (24 filling chunks, a first piece of 20): its
+    filling chunks share the snapshot that its own launch took.  Outputs and memories as on one stream, bit for bit, then a
+    second, ragged call."""
+    sh = wl.Shape("later", "bf16", 4, 32, 8, 128, 256, T=0, eta=512, lam=1024, C=64, seed=0)
+    g = torch.Generator(device=P.DEV).manual_seed(3)
+    mk = lambda *shape: torch.randn(shape, generator=g, device=P.DEV).to(torch.bfloat16)
+    Wq, Wk = mk(32, 128, 128) / 128 ** 0.5, mk(8, 128, 128) / 128 ** 0.5
+    beside, apart = P.make_layer(sh, prefill_overlap=1), P.make_layer(sh)
+    for T in (2048, 77):
+        q, k, v = mk(4, 32, T, 128), mk(4, 8, T, 128), mk(4, 8, T, 128)
+        out, want = beside.prefill(q, k, v, Wq, Wk), apart.prefill(q, k, v, Wq, Wk)
+        torch.cuda.synchronize()
+        assert T < 2048 or (int(shares(beside)[0].any(1).sum()) >= 2 and int(shares(apart)[0].any(1).sum()) == 1)   # (pieces)
+        assert torch.equal(out, want), T
+        for nm in FIELDS:
+            assert torch.equal(getattr(beside, nm), getattr(apart, nm)), (T, nm)
+
+
+def test_shared_evolution_from_two_host_threads():
+    """Two host threads, each with a layer, a workspace and a stream of its own, run shared evolutions (48 workgroups each, and the
+    outputs beside them) at the same time: each result must be the one that the same call gives alone."""
+    import threading
+    sh = wl.Shape("threads", "bf16", 1, 16, 8, 128, 256, T=0, eta=64, lam=1024, C=64, seed=0)
+    layers, args, want = [], [], []
+    for seed in (5, 6):
+        q, k, v, Wq, Wk = case_inputs(seed, 1, 16, 8, 128, 256, 2000)
+        args.append((P.to_dev(q, "bf16"), P.to_dev(k, "bf16"), P.to_dev(v, "bf16"), P.w_to_dev(Wq, "bf16"), P.w_to_dev(Wk, "bf16")))
+        layers.append(P.make_layer(sh))
+        want.append((layers[-1].prefill(*args[-1]).clone(), [getattr(layers[-1], nm).clone() for nm in FIELDS]))
+        torch.cuda.synchronize()
+        assert bool((shares(layers[-1])[1][0] > 0).all())
+    outs, errs = [[], []], []
+
+    def run(i):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(4):
+                    layers[i].reset()
+                    outs[i].append(layers[i].prefill(*args[i]))
+                torch.cuda.current_stream().synchronize()
+        except Exception as e:   # surfaced in the main thread
+            errs.append(e)
+
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errs, errs
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert all(torch.equal(o, want[i][0]) for o in outs[i])
+        for nm, w in zip(FIELDS, want[i][1]):
+            assert torch.equal(getattr(layers[i], nm), w), (i, nm)
 
 
 @pytest.mark.parametrize("d,D,eta,lam,C", [(32, 2, 3, 5, 4), (32, 62, 7, 9, 8), (64, 64, 16, 16, 16), (64, 128, 16, 40, 24), (64, 130, 8, 8, 16),

@@ -453,8 +453,8 @@ def test_two_stream_prefill_from_two_host_threads():
             lay, dq, dk, dv, _, _ = cases[i]
             st = torch.cuda.Stream()
             for _ in range(4):
-                lay.reset()
-                with torch.cuda.stream(st):
+                with torch.cuda.stream(st):   # (the reset too: a stream of torch does not wait for the default stream)
+                    lay.reset()
                     outs[i] = lay.prefill(dq, dk, dv, dWq, dWk)
                 st.synchronize()
         except Exception as e:   # surfaced in the main thread
