@@ -62,8 +62,8 @@ enum { LOLA_HIDE_STATE = 1, LOLA_HIDE_SPARSE = 2 };
  * and over the query heads of its group, of
  *     (w - a)^2 | |w - a| | a / w | w,    w = exp(scale q_t.k_i), a = phi(q_t).phi(k_i).
  * A pair's sum is final when it leaves the window and stays with it in the sparse cache; the lambda
- * largest stay (ties: lower token index), as with the self-recall error.  These kinds run on the
- * shape-generic kernels and need queries: an update-only lola_prefill returns LOLA_ERR_UNSUPPORTED. */
+ * largest stay (ties: lower token index), as with the self-recall error.  These kinds need queries: an
+ * update-only lola_prefill returns LOLA_ERR_UNSUPPORTED. */
 enum { LOLA_SCORE_SRE = 0, LOLA_SCORE_WERR_SQ = 1, LOLA_SCORE_WERR_ABS = 2, LOLA_SCORE_OVEREST = 3, LOLA_SCORE_ATTN = 4 };
 
 typedef struct {
@@ -176,6 +176,10 @@ lola_status lola_state_flush(const lola_config *cfg, const lola_state *st, void 
  *   `stream` is under graph capture, or if the second stream cannot be created, everything stays
  *   on `stream`.  Results do not depend on which way a call ran.  Host threads may call
  *   concurrently; the second stream is shared and guarded by a lock held while a call enqueues.
+ * Waits on the device: with outputs, few streams (B * Hkv <= 64) and window / budget read at run time, several workgroups of
+ *   one launch share the scoring of a stream's candidates and wait for each other on words in the workspace.  A workgroup waits
+ *   only for ones that already run, so a call needs no free compute unit to finish: it may run beside other streams' or
+ *   processes' work and under graph capture like any other.
  * Token indices are int32: n_tokens + T must stay below 2^31.
  */
 lola_status lola_prefill(const lola_config *cfg, const lola_state *st,

@@ -901,7 +901,7 @@ __device__ __forceinline__ void fold_blocks(float *H, const float *ph, const flo
         for (int i = 0; i < 4; i++)
 #pragma unroll
             for (int x = 0; x < FB; x++) acc[i][x] = 0.f;
-#pragma unroll(FB == 4 ? 4 : 1)
+#pragma unroll FB == 4 ? 4 : 1
         for (int r = 0; r < nr; r++) {
             const float4 v4 = *reinterpret_cast<const float4 *>(vs + r * d + c0);
             const float vv[4] = {v4.x, v4.y, v4.z, v4.w};

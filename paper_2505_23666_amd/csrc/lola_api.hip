@@ -40,8 +40,8 @@ bool wide_step_out_ok(const lola_config *c) {
            c->window >= 1 && !fast_decode_ok(c) && c->n_q_heads / c->n_kv_heads <= 8 &&
            c->sparse_budget + c->window <= (c->n_q_heads / c->n_kv_heads <= 4 ? fast::STEP_OUT_NKMAX : fast::STEP_OUT_NKMAX / 2);
 }
-// ... and at which the streams in steady state are updated by the MFMA update kernel ahead of it (sparse budgets in
-// multiples of 64).
+// ... and at which the memories are updated by the MFMA update kernel ahead of it, streams that are still filling included
+// (sparse budgets in multiples of 64).
 bool wide_decode_ok(const lola_config *c) {
     return wide_step_out_ok(c) && c->sparse_budget >= 64 && c->sparse_budget % 64 == 0 && c->sparse_budget <= fast::STEP_UPDATE_LAMMAX;
 }
@@ -952,7 +952,7 @@ const char *lola_status_str(lola_status s) {
 const char *lola_kernel_path(const lola_config *c, int32_t which) {
     if (check_config(c) != LOLA_OK) return "invalid";
     if (which == 1 && fast_decode_ok(c)) return "mfma";
-    if (which == 1 && wide_decode_ok(c)) return "mfma";      // update of steady-state streams and outputs on MFMA
+    if (which == 1 && wide_decode_ok(c)) return "mfma";      // update and outputs on MFMA
     if (which == 1 && wide_step_out_ok(c)) return "mixed";   // outputs on MFMA, update shape-generic
     if (which == 0 && (fast_attend_ok(c) || wide_scan_ok(c))) return "mfma";
     if (which == 0 && (fast_output_ok(c) || wide_output_ok(c))) return "mixed";

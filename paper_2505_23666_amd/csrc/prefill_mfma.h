@@ -852,7 +852,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
                     *reinterpret_cast<uint4 *>(&PBb[pt * RB * D + (LAM + row) * D + ((pc ^ (row & 15)) << 3)]) = PHn[it];
                 }
             } else if (PERSIST) {
-                // phi of the batch's tiles (first regular chunk of a launch): wavefront w takes tiles t0 + w, t0 + w + NW, ...
+                // phi of the batch's tiles (first scored chunk of a launch): wavefront w takes tiles t0 + w, t0 + w + NW, ...
                 // (W_k is read where it is used: this path runs once per launch and must not raise the kernel's register need)
 #pragma unroll 1
                 for (int t = t0 + w; t < t1; t += NW) {
@@ -1134,7 +1134,7 @@ __global__ __launch_bounds__(DH * 4 / RT, 1) void scan_fast_kernel(generic::Pref
         lds_barrier();
         // One wavefront holds all scores (NK per lane) and finds the nf-th smallest by building it bit by bit: a trial
         // value is kept when fewer than nf scores lie below it (votes counted on the scalar unit).  Scores equal to
-        // the threshold are folded too if that makes exactly 64; otherwise (exact ties across the cut) the same search
+        // the threshold are folded too if that makes exactly nf; otherwise (exact ties across the cut) the same search
         // over their token indices picks the largest ones.  The lists follow from the fold predicate by ballots:
         // candidates to fold; entrants paired with the slots of the leavers.
         if (w != 0) {   // the requests wavefront 0 issued before the recall GEMM (H^T is still the chunk's entry state)
@@ -1732,7 +1732,8 @@ __device__ __forceinline__ void wide_score_batches(uint16_t *pool, const float *
 // for 2 x 4096 tokens at eta 512 / lambda 1024).
 constexpr int WIDE_PIECES = 8;   // launches of a pass at most
 struct WideShare {   // per stream, in the feature scratch behind the cache slots' rows
-    struct Piece {   // one per launch of the pass, each word on a cache line of its own (cleared by phi_wide_kernel)
+    struct Piece {   // one per launch of the pass, cleared by phi_wide_kernel; `started` and `joined` (used while a launch begins), `go` and
+                     // `done` on three cache lines
         int started, joined, pad0[30];
         unsigned long long go; int pad1[30];
         int done, pad2[31];

@@ -407,8 +407,8 @@ def test_8b_shape_outputs_on_the_second_stream():
 
 def test_8b_shape_budget_256_outputs_on_the_second_stream():
     """Sparse budget 256 at the 8B head shape with the outputs on the second stream: the candidates' features stream
-    through LDS in batches requested one ahead, and every piece of the pass starts with a launch of the feature kernel
-    of the run-time shapes (the pairs that leave the window in its chunks, the cache slots as it finds them).  Two calls
+    through LDS in batches requested one ahead, and the pass starts with a launch of the feature kernel of the run-time
+    shapes (the pairs that leave the window in its chunks, the cache slots as it finds them).  Two calls
     with a ragged boundary against the oracle, then the first call again on one stream: bit for bit the same outputs."""
     sh = wl.scaled(3, lam=256, T=64 * 32 + 37 + 64 * 17)
     Wq, Wk = wl.weights(sh)
