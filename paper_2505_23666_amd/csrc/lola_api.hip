@@ -5,6 +5,7 @@
 #include <mutex>
 #include "generic_kernels.h"
 #include "decode_mfma.h"
+#include "attend_mfma.h"
 #include "prefill_mfma.h"
 
 using namespace lola;
@@ -459,26 +460,24 @@ SideStream *side_stream(hipStream_t caller) {
     return state[dev] == 1 ? &table[dev] : nullptr;
 }
 
-// outputs of the chunks [r0, r1) by the MFMA output kernels: the compile-time form where the shape has one, else the
-// form with run-time window and sparse budget
+// outputs of the chunks [r0, r1) by the MFMA output kernel
 void launch_output_kernel(const lola_config *c, const generic::PrefillArgs<bf16_t> &a, int r0, int r1, hipStream_t so) {
     generic::PrefillArgs<bf16_t> ao = a;
     ao.j0 = r0; ao.j1 = r1; ao.scan_mode = 0;
-    const dim3 ga((unsigned)(r1 - r0), (unsigned)a.dm.Hq, (unsigned)a.dm.B);
+    // Heads per workgroup: with 128 features two (two workgroups per compute unit cover each other's waits: 369 us against 401 with
+    // four, 16 x 1536 tokens of the 8B shape; 18.9 against 23.4 for one sequence of 384), with 256 four (keys and snapshot read once
+    // for the group: 441 against 467 at eta 512 / lambda 1024).
+    const int nch = r1 - r0, G = c->feat_dim == 256 && a.dm.g % 4 == 0 ? 4 : (a.dm.g % 2 == 0 ? 2 : 1);
     const bool f32o = c->out_dtype == LOLA_F32;
-    if (!fast_output_ok(c)) {
-#define LOLA_WIDE(DHV, DFV) do { if (f32o) hipLaunchKernelGGL((fast::attend_wide_kernel<DHV, DFV, float>), ga, dim3(256), 0, so, ao); \
-                                 else hipLaunchKernelGGL((fast::attend_wide_kernel<DHV, DFV, bf16_t>), ga, dim3(256), 0, so, ao); } while (0)
-        if (c->head_dim == 128) { if (c->feat_dim == 256) LOLA_WIDE(128, 256); else LOLA_WIDE(128, 128); }
-        else { if (c->feat_dim == 256) LOLA_WIDE(64, 256); else LOLA_WIDE(64, 128); }
-#undef LOLA_WIDE
-        return;
-    }
-#define LOLA_ATT2(LAMV, DHV) do { if (f32o) hipLaunchKernelGGL((fast::attend_fast_kernel<LAMV, DHV, float>), ga, dim3(256), 0, so, ao); \
-                                  else hipLaunchKernelGGL((fast::attend_fast_kernel<LAMV, DHV, bf16_t>), ga, dim3(256), 0, so, ao); } while (0)
-#define LOLA_ATT(LAMV) do { if (c->head_dim == 128) LOLA_ATT2(LAMV, 128); else LOLA_ATT2(LAMV, 64); } while (0)
-    if (c->sparse_budget == 0) LOLA_ATT(0); else if (c->sparse_budget == 64) LOLA_ATT(64);
-    else if (c->sparse_budget == 128) LOLA_ATT(128); else LOLA_ATT(256);
+    // streams (and groups of G query heads) run fastest, so that a stream's chunks meet in one XCD's L2
+    const int groups = a.dm.B * a.dm.Hkv * (a.dm.g / G);
+    const int ny = std::min(nch, 32768);
+    const dim3 ga((unsigned)groups, (unsigned)ny, (unsigned)((nch + ny - 1) / ny));
+#define LOLA_ATT2(DHV, DFV, GV) do { if (f32o) hipLaunchKernelGGL((fast::attend_group_kernel<DHV, DFV, GV, float>), ga, dim3(fast::AttendShape<DHV, DFV, GV>::NTHR), (fast::AttendShape<DHV, DFV, GV>::lds(c->sparse_budget)), so, ao); \
+                                     else hipLaunchKernelGGL((fast::attend_group_kernel<DHV, DFV, GV, bf16_t>), ga, dim3(fast::AttendShape<DHV, DFV, GV>::NTHR), (fast::AttendShape<DHV, DFV, GV>::lds(c->sparse_budget)), so, ao); } while (0)
+#define LOLA_ATT(DHV, DFV) do { if (DFV == 256 && G == 4) LOLA_ATT2(DHV, 256, 4); else if (G == 2) LOLA_ATT2(DHV, DFV, 2); else LOLA_ATT2(DHV, DFV, 1); } while (0)
+    if (c->head_dim == 128) { if (c->feat_dim == 256) LOLA_ATT(128, 256); else LOLA_ATT(128, 128); }
+    else { if (c->feat_dim == 256) LOLA_ATT(64, 256); else LOLA_ATT(64, 128); }
 #undef LOLA_ATT
 #undef LOLA_ATT2
 }
@@ -664,24 +663,26 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                     ~Joiner() { (void)join(); }
                 } joiner;
                 joiner.side = side; joiner.stream = stream;
-                // Piece boundaries: each piece half as long as the one before it, so that the outputs of a piece
-                // (which take about half as long per chunk as the evolution) are hidden behind the evolution of the
-                // next; the last piece, whose outputs nothing hides, is at least one round of output workgroups on the
-                // chip (two per compute unit).
+                // Piece boundaries: each piece `shrink` times shorter than the one before it, so that the outputs of a piece are
+                // hidden behind the evolution of the next; the last piece, whose outputs nothing hides, is at least one
+                // round of output workgroups on the chip (two per compute unit).  At the compile-time shapes the outputs of a
+                // chunk take about a third of its evolution (4.4 against 12.5 us at 4 sequences of the 8B shape), at the run-time
+                // ones up to half; a piece fewer is a restart of the evolution fewer.
                 int bnd[SideStream::NEV + 1];
                 bnd[0] = j0; bnd[1] = jend;
                 int npieces = 1;
                 if (side) {
                     side_lock.lock();
                     const int per_chunk = a.dm.Hq * a.dm.B;   // output workgroups per chunk
+                    const int shrink = wide || a.dm.Hq * a.dm.B > 192 ? 2 : 3;
                     int last = (2 * CHIP_CUS + per_chunk - 1) / per_chunk;
                     if (last < 2) last = 2;
-                    while (np > 2 && piece / ((1 << np) - 1) < last) np--;
-                    int unit = piece / ((1 << np) - 1);
-                    if (unit < 1) unit = 1;
+                    auto units = [&](int n) { int u = 0, x = 1; for (int i = 0; i < n; i++, x *= shrink) u += x; return u; };
+                    while (np > 2 && piece / units(np) < last) np--;
+                    int len = std::max(piece / units(np), 1);
                     npieces = np;
                     bnd[np] = jend;
-                    for (int i = np - 1; i >= 1; i--) bnd[i] = bnd[i + 1] - (unit << (np - 1 - i));   // the first piece takes the rest
+                    for (int i = np - 1; i >= 1; i--, len *= shrink) bnd[i] = bnd[i + 1] - len;   // the first piece takes the rest
                 }
                 auto attend = [&](hipStream_t so, int r0, int r1) { launch_output_kernel(c, a, r0, r1, so); };
                 // outputs of the chunks [r0, r1) on the second stream, behind what `stream` held when fork[ev] was recorded

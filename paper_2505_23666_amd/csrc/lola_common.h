@@ -65,6 +65,12 @@ __device__ __forceinline__ void lds_dma16(const void *gsrc, void *lds_dst) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(l), "v"(gsrc) : "memory");
 }
 
+// the same with 4 bytes per lane (256 per wavefront)
+__device__ __forceinline__ void lds_dma4(const void *gsrc, void *lds_dst) {
+    const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds_dst);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" :: "s"(l), "v"(gsrc) : "memory");
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = WAVE / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);

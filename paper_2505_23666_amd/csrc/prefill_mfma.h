@@ -1,257 +1,15 @@
 // MFMA kernels of the prefill (and, further down, of the generation step at the shapes the fused kernel of
-// decode_mfma.h does not cover) for gfx950, bf16 storage.  In file order: attend_fast_kernel / attend_wide_kernel
-// (chunk-parallel outputs, compile-time / run-time window and budget), phi_k_kernel, scan_fast_kernel (state evolution,
-// compile-time shapes), phi_wide_kernel, scan_wide_kernel (run-time shapes; also with given scores and without a
-// cache), step_out_wide_kernel, step_update_wide_kernel (generation step), band_score_wide_kernel (query-dependent
-// scores of a call), scan_nocache_kernel (no sparse cache, window 64).
-//
-// The chunk-parallel output kernel for the 8B head shape:
-//
-// One workgroup (four wavefronts) per (sequence, query head, chunk); every wavefront owns 16 of the
-// chunk's 64 queries.  All GEMMs are computed transposed (queries are MFMA columns), so that
-//   - the softmax statistics of a query live in the four lanes that share l % 16,
-//   - the C layout of one GEMM is directly the B-operand layout of the next
-//     (S^T -> P^T for the value GEMM, z^T -> phi(q)^T for the linear read-out),
-// using the contraction-index permutation kappa(ks, e, grp) = 32 ks + 16 (e / 4) + 4 grp + e % 4.
-//
-// Per workgroup (paper Sec. 3, y_t equation with the chunk sharing one state, "Chunkwise Inference"):
-//   1. phi(q) for the 64 queries: z^T = W_q Q^T on MFMA, fp32 softmax halves; phi(q)^T s.
-//   2. linear part lin^T = H^T phi(q)^T with the chunk's snapshot of H^T, which the scan kernel
-//      leaves as bf16 high + low parts in operand order (three MFMAs per product).
-//   3. keys in blocks of 128: positions [0, lambda) sparse cache (gathered by virtual row),
-//      [lambda, lambda + 64) the 64 rows before the chunk, [lambda + 64, lambda + 128) the chunk
-//      itself (causal).  Per block: K and V staged in LDS (both row-major), S^T = K Q^T, running max (started at 0:
-//      the linear terms carry weight exp(-m)), P^T as bf16 high + low parts, out^T += V^T P^T with V^T taken
-//      through the transposing LDS read.
-//   4. y = (out + exp(-m) lin) / (sum p + exp(-m) phi(q)^T s).
+// decode_mfma.h does not cover) for gfx950, bf16 storage.  In file order: phi_k_kernel,
+// scan_fast_kernel (state evolution, compile-time shapes), phi_wide_kernel, scan_wide_kernel (run-time shapes; also with
+// given scores and without a cache), step_out_wide_kernel, step_update_wide_kernel (generation step),
+// band_score_wide_kernel (query-dependent scores of a call), scan_nocache_kernel (no sparse cache, window 64).  The
+// chunk-parallel output kernel is in attend_mfma.h.
 #pragma once
 #include "decode_mfma.h"
 #include "generic_kernels.h"
 
 namespace lola {
 namespace fast {
-
-template <int PR> __device__ __forceinline__ int vswz2(int row);   // (piece swizzle of row-major value tiles, defined with the other swizzles below)
-
-template <int LAM, int DH, typename TO>
-__global__ __launch_bounds__(256, 2) void attend_fast_kernel(generic::PrefillArgs<bf16_t> a) {
-    constexpr int M = 64, D = 128, C = 64, ETA = 64, KS = DH / 32, PR = DH / 8, NCT = DH / 16;
-    static_assert(DH == 64 || DH == 128, "head_dim");
-    constexpr int P = LAM + ETA;                    // rows of the virtual prefix
-    constexpr int NKEYS = LAM + ETA + C;            // key positions
-    constexpr int NB = (NKEYS + 127) / 128;         // key blocks
-    __shared__ __attribute__((aligned(16))) uint16_t L[2 * DH * D];   // 64 KB: H^T high/low parts, then K block + V block
-    __shared__ __attribute__((aligned(16))) float s_l[D];
-    __shared__ int G_l[LAM > 0 ? LAM : 1];
-    __shared__ int gneg_l[4];   // per wavefront: it saw an empty cache slot
-
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
-    const int j = a.j0 + blockIdx.x, jj = j - a.jb, hq = blockIdx.y, b = blockIdx.z;
-    const int h = hq / a.dm.g, si = b * a.dm.Hkv + h;
-    const int64_t a0 = a.st.n_tokens[si];
-    const int Tn = a.T_tokens;
-    const int cl = min(C, Tn - j * C);              // queries in this chunk
-    const int64_t aj = a0 + (int64_t)j * C;         // token index of the chunk's first query
-    const size_t sj = (size_t)si * a.S + jj;
-    // filling chunks share one snapshot of H and s, that of the launch's first chunk, and have their rows in closed form
-    const int spc_in = a.fill_closed ? a.st.sp_count[si] : 0;
-    const bool filling = a.fill_closed && j < generic::first_scored_chunk(a, a0, spc_in);
-    const size_t sh = filling ? (size_t)si * a.S + (a.j0 - a.jb) : sj;
-    const uint16_t *Hsnap = reinterpret_cast<const uint16_t *>(a.snapH) + sh * (2 * DH * D);
-    const float *ssnap = a.snapS + sh * D;
-    const int32_t *Gsnap = a.snapG + sj * LAM;
-    const bf16_t *pK = a.prefK + (size_t)si * P * DH, *pV = a.prefV + (size_t)si * P * DH;
-    const bf16_t *kc = a.k + (size_t)si * Tn * DH, *vc = a.v + (size_t)si * Tn * DH;
-    const bf16_t *qh = a.q + (((size_t)b * a.dm.Hq + hq) * Tn + (size_t)j * C) * DH;
-    TO *oh = (TO *)a.out + (((size_t)b * a.dm.Hq + hq) * Tn + (size_t)j * C) * DH;
-    const bf16_t *Wq = a.Wq + (size_t)hq * M * DH;   // [M][DH]
-    const int vrow_c = P + j * C;                     // virtual row of the chunk's first token
-    const float scale2 = a.dm.scale * LOG2E;          // logits are kept in units of log2(e)
-
-    // ---- loads: this wavefront's queries as MFMA B operand (column = query, k = input index); rows past the chunk's
-    // end are read from row 0 (their results are never stored)
-    const int qi = 16 * w + r16;
-    bf16x8 BQ[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) BQ[ks] = ld_bf16x8(qh + (size_t)(qi < cl ? qi : 0) * DH + 32 * ks + 8 * g4);
-    if (tid < D / 4) reinterpret_cast<float4 *>(s_l)[tid] = reinterpret_cast<const float4 *>(ssnap)[tid];
-    bool gneg = false;
-    for (int x = tid; x < LAM; x += 256) { const int gr = filling ? generic::fill_row(a, a0, spc_in, j, x) : Gsnap[x]; G_l[x] = gr; gneg |= gr < 0; }
-    if (lane == 0) gneg_l[w] = 0;
-    if (gneg) gneg_l[w] = 1;   // (after the store of 0 in program order; lanes of one wavefront, same value)
-    lds_barrier();
-    // Key blocks that lie in the cache and the window need no masks when every slot is in use, the window is full and the
-    // queries may read the cache: the per-element tests (an LDS read and three compares each) are skipped there.
-    const bool nomask_ok = !(gneg_l[0] | gneg_l[1] | gneg_l[2] | gneg_l[3]) && !(a.dm.hide & 2) && aj >= ETA;
-
-    // ---- softmax part over key blocks of 128 positions
-    uint16_t *Kl = L, *Vr = L + DH * 128;   // [key][input piece ^ key % pieces] and [key][piece ^ vswz2(key)] (read transposed)
-    f32x4 out[NCT];
-#pragma unroll
-    for (int mt = 0; mt < NCT; mt++) out[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    float mrun = 0.f, lsum = 0.f;   // running max (units of log2 e) and running sum of weights
-    const int64_t tq = aj + qi;     // token index of this lane's query
-#pragma unroll 1
-    for (int blk = 0; blk < NB; blk++) {
-        // position -> source row (or none).  A thread handles PR / 4 items of the block, each one 16-byte piece of two
-        // neighbouring keys; the values stay row-major (the value GEMM reads them through the transposing LDS read)
-        // (named scalars: an array held across the barrier would be sent through scratch memory).
-#define LOLA_REP8(X) X(0) X(1) X(2) X(3)   // items beyond 64 * PR / 256 compile to nothing
-#define LOLA_KVROW(pos, vr) { vr = -1; \
-            if (pos < LAM) vr = G_l[pos]; \
-            else if (pos < NKEYS) { vr = vrow_c - ETA + (pos - LAM); if (aj - ETA + (pos - LAM) < 0 || (pos - LAM - ETA) >= cl) vr = -1; } }
-#define LOLA_KVLOAD(it) uint4 kreg##it = make_uint4(0, 0, 0, 0), vreg##it = make_uint4(0, 0, 0, 0), \
-                              kreh##it = make_uint4(0, 0, 0, 0), vreh##it = make_uint4(0, 0, 0, 0); if (it < PR / 4) { \
-            const int o = tid + 256 * it, kk = 2 * (o / PR), ch = o % PR; \
-            int vr0, vr1; \
-            LOLA_KVROW((128 * blk + kk), vr0) LOLA_KVROW((128 * blk + kk + 1), vr1) \
-            if (vr0 >= 0) { \
-                kreg##it = reinterpret_cast<const uint4 *>(vr0 < P ? pK + (size_t)vr0 * DH : kc + (size_t)(vr0 - P) * DH)[ch]; \
-                vreg##it = reinterpret_cast<const uint4 *>(vr0 < P ? pV + (size_t)vr0 * DH : vc + (size_t)(vr0 - P) * DH)[ch]; \
-            } \
-            if (vr1 >= 0) { \
-                kreh##it = reinterpret_cast<const uint4 *>(vr1 < P ? pK + (size_t)vr1 * DH : kc + (size_t)(vr1 - P) * DH)[ch]; \
-                vreh##it = reinterpret_cast<const uint4 *>(vr1 < P ? pV + (size_t)vr1 * DH : vc + (size_t)(vr1 - P) * DH)[ch]; \
-            } }
-#define LOLA_KVSTORE(it) if (it < PR / 4) { \
-            const int o = tid + 256 * it, kk = 2 * (o / PR), ch = o % PR; \
-            *reinterpret_cast<uint4 *>(&Kl[kk * DH + ((ch ^ (kk & (PR - 1))) << 3)]) = kreg##it; \
-            *reinterpret_cast<uint4 *>(&Kl[(kk + 1) * DH + ((ch ^ ((kk + 1) & (PR - 1))) << 3)]) = kreh##it; \
-            *reinterpret_cast<uint4 *>(&Vr[kk * DH + ((ch ^ vswz2<PR>(kk)) << 3)]) = vreg##it; \
-            *reinterpret_cast<uint4 *>(&Vr[(kk + 1) * DH + ((ch ^ vswz2<PR>(kk + 1)) << 3)]) = vreh##it; }
-        LOLA_REP8(LOLA_KVLOAD)
-        lds_barrier();   // previous users of L (H^T, or the previous block) are done
-        LOLA_REP8(LOLA_KVSTORE)
-#undef LOLA_KVLOAD
-#undef LOLA_KVSTORE
-#undef LOLA_KVROW
-#undef LOLA_REP8
-        lds_barrier();
-        // S^T = K Q^T for the 8 key tiles of the block; lane (column = query r16, group g4) holds keys 16 mt + 4 g4 + i
-        f32x4 sc[8];
-        float bmax = mrun;
-#pragma unroll
-        for (int mt = 0; mt < 8; mt++) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KS; ks++)
-                acc = mfma16(as_bf16x8(*reinterpret_cast<const uint4 *>(&Kl[(16 * mt + r16) * DH + (((4 * ks + g4) ^ (r16 & (PR - 1))) << 3)])), BQ[ks], acc);
-            if (nomask_ok && 128 * (blk + 1) <= LAM + ETA) {
-#pragma unroll
-                for (int i = 0; i < 4; i++) { acc[i] *= scale2; bmax = fmaxf(bmax, acc[i]); }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int pos = 128 * blk + 16 * mt + 4 * g4 + i;
-                    bool ok;
-                    if (pos < LAM) ok = G_l[pos] >= 0 && !(a.dm.hide & 2);
-                    else if (pos < LAM + ETA) ok = aj - ETA + (pos - LAM) >= 0;
-                    else ok = pos < NKEYS && (aj + (pos - LAM - ETA)) <= tq;
-                    acc[i] = ok ? acc[i] * scale2 : -INFINITY;
-                    bmax = fmaxf(bmax, acc[i]);
-                }
-            }
-            sc[mt] = acc;
-        }
-        bmax = grp_max(bmax);
-        const float resc = fexp2(mrun - bmax);
-        mrun = bmax;
-        lsum *= resc;
-#pragma unroll
-        for (int mt = 0; mt < NCT; mt++) out[mt] *= resc;
-        // weights and out^T += V^T P^T, 32 keys per k-step (key tiles 2s, 2s+1)
-#pragma unroll
-        for (int s = 0; s < 4; s++) {
-            float pw[8];
-#pragma unroll
-            for (int e = 0; e < 8; e++) { pw[e] = fexp2(sc[2 * s + (e >> 2)][e & 3] - mrun); lsum += pw[e]; }
-            bf16x8 Ph, Pl;
-            split8(pw, Ph, Pl);
-            // A = V^T of keys 32 s ..: lane (column r16 of tile mt, group g4) holds keys 4 g4 + 0..3 and 16 + 4 g4 + 0..3 (the
-            // order of pw) of its column, through the transposing read of the row-major block
-            const int t0 = 4 * g4 + (r16 >> 2);
-            const uint16_t *vb = &Vr[(32 * s + t0) * DH + 4 * (r16 & 1)];
-#pragma unroll
-            for (int mt = 0; mt < NCT; mt++) {
-                const int pc = ((2 * mt + ((r16 & 3) >> 1)) ^ vswz2<PR>(t0)) << 3;
-                const bf16x4 b0 = tr_read(vb + pc), b1 = tr_read(vb + 16 * DH + pc);
-                const bf16x8 Av = __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7);
-                out[mt] = mfma16(Av, Ph, out[mt]);
-                out[mt] = mfma16(Av, Pl, out[mt]);
-            }
-        }
-    }
-    lsum = grp_sum(lsum);
-
-    // ---- linear part, after the softmax part so that its operands do not occupy registers during the key blocks:
-    // H^T snapshot -> LDS (16-byte pieces XOR-swizzled by the row so that operand reads are conflict free), phi(q),
-    // then per value tile lin^T[c][q] = sum_f H^T[c][f] phi(q)[f] and the output
-    //   y = (out + exp(-m) lin) / (sum p + exp(-m) phi(q)^T s);  the lane holds columns c = 16 mt + 4 g4 + 0..3 of query qi
-    lds_barrier();   // the last key block has been consumed
-#pragma unroll
-    for (int p4 = 0; p4 < DH / 32; p4++) {
-        uint4 hv[4];
-#pragma unroll
-        for (int it = 0; it < 4; it++) hv[it] = reinterpret_cast<const uint4 *>(Hsnap)[tid + 256 * (4 * p4 + it)];
-#pragma unroll
-        for (int it = 0; it < 4; it++) {
-            // snapshot order: [part][row tile of 16][k-step][lane = 16 (piece % 4) + row % 16]
-            const int o = tid + 256 * (4 * p4 + it), part = o / (DH * 16), op = o % (DH * 16);
-            const int c = 16 * (op >> 8) + (o & 15), ch = 4 * ((o >> 6) & 3) + ((o >> 4) & 3);
-            *reinterpret_cast<uint4 *>(&L[part * DH * D + c * D + ((ch ^ (c & 15)) << 3)]) = hv[it];
-        }
-    }
-    // phi(q): z^T = W_q Q^T (A = W_q rows from global, B = queries)
-    float pp[16], pn[16];
-    {
-        f32x4 zt[4];
-#pragma unroll
-        for (int mt = 0; mt < 4; mt++) {
-            zt[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KS; ks++)
-                zt[mt] = mfma16(ld_bf16x8(Wq + (size_t)(16 * mt + r16) * DH + 32 * ks + 8 * g4), BQ[ks], zt[mt]);
-        }
-        phi_from_z(zt, a.dm.phi_kind, pp, pn);
-    }
-    float lden = 0.f;   // phi(q)^T s
-#pragma unroll
-    for (int mt = 0; mt < 4; mt++) {
-        const float4 sp4 = *reinterpret_cast<const float4 *>(&s_l[16 * mt + 4 * g4]);
-        const float4 sn4 = *reinterpret_cast<const float4 *>(&s_l[M + 16 * mt + 4 * g4]);
-        lden = fmaf(pp[4 * mt], sp4.x, lden); lden = fmaf(pp[4 * mt + 1], sp4.y, lden);
-        lden = fmaf(pp[4 * mt + 2], sp4.z, lden); lden = fmaf(pp[4 * mt + 3], sp4.w, lden);
-        lden = fmaf(pn[4 * mt], sn4.x, lden); lden = fmaf(pn[4 * mt + 1], sn4.y, lden);
-        lden = fmaf(pn[4 * mt + 2], sn4.z, lden); lden = fmaf(pn[4 * mt + 3], sn4.w, lden);
-    }
-    lden = grp_sum(lden);
-    bf16x8 Bh[4], Bl[4];
-    split8(&pp[0], Bh[0], Bl[0]); split8(&pp[8], Bh[1], Bl[1]);
-    split8(&pn[0], Bh[2], Bl[2]); split8(&pn[8], Bh[3], Bl[3]);
-    const float el = (a.dm.hide & 1) ? 0.f : fexp2(-mrun);   // restricted query: no hidden-state terms
-    const float inv = frcp(fmaf(el, lden, lsum));
-    lds_barrier();   // H^T is in LDS
-#pragma unroll
-    for (int mt = 0; mt < NCT; mt++) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < 4; ks++) {
-            const int addr = (16 * mt + r16) * D + (((4 * ks + g4) ^ r16) << 3);
-            const bf16x8 Ahi = as_bf16x8(*reinterpret_cast<const uint4 *>(&L[addr]));
-            const bf16x8 Alo = as_bf16x8(*reinterpret_cast<const uint4 *>(&L[DH * D + addr]));
-            acc = mfma16(Ahi, Bh[ks], acc);
-            acc2 = mfma16(Ahi, Bl[ks], acc2);
-            acc2 = mfma16(Alo, Bh[ks], acc2);
-        }
-        const f32x4 lin = acc + acc2;
-        if (qi < cl) {
-            TO *dst = oh + (size_t)qi * DH + 16 * mt + 4 * g4;
-#pragma unroll
-            for (int i = 0; i < 4; i++) stf(dst, i, fmaf(el, lin[i], out[mt][i]) * inv);
-        }
-    }
-}
-
 
 // phi of 16 vectors from their NT tiles of projections in the C layout of the projection GEMM (lane (column r16, group
 // g4) holds z[16 mt + 4 g4 + i] in zt[mt][i]): the lane's 4 NT positive-half and 4 NT negative-half features, index
@@ -301,235 +59,6 @@ __device__ __forceinline__ PhiNorm phi_norm(const f32x4 (&zt)[NT], int phi_kind)
     n.ip = frcp(grp_sum(sp)); n.in = frcp(grp_sum(sn));
     return n;
 }
-
-// The output kernel for any window and sparse budget (read from the arguments) and for 128 or 256 features: the
-// paper's own models use twice the head dimension as feature dimension and windows / budgets of 128 .. 1024 in the
-// long-context runs (Sec. 4).  Same computation and layouts as attend_fast_kernel (chunks of 64 queries, key blocks of
-// 128 positions: cache slots, window, the chunk itself), with run-time trip counts; the H^T snapshot passes through LDS
-// 128 features at a time.  The snapshot's pieces are ordered [part][row tile of 16][k-step of 32 features][lane].
-template <int DH, int DF, typename TO>
-__global__ __launch_bounds__(256, 2) void attend_wide_kernel(generic::PrefillArgs<bf16_t> a) {
-    constexpr int M = DF / 2, C = 64, KS = DH / 32, PR = DH / 8, NCT = DH / 16, NZT = M / 16, KSD = DF / 32, NFH = DF / 128;
-    constexpr int MAXLAM = 1024;
-    static_assert((DH == 64 || DH == 128) && (DF == 128 || DF == 256), "shape");
-    __shared__ __attribute__((aligned(16))) uint16_t L[2 * DH * 128];   // 64 KB: K block + V block, then half of H^T (high/low parts)
-    __shared__ __attribute__((aligned(16))) float s_l[DF];
-    __shared__ int G_l[MAXLAM];
-    __shared__ int gneg_l[4];   // per wavefront: it saw an empty cache slot
-
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
-    const int LAM = a.dm.lam, ETA = a.dm.eta;
-    const int P = LAM + ETA, NKEYS = LAM + ETA + C, NB = (NKEYS + 127) / 128;
-    const int j = a.j0 + blockIdx.x, jj = j - a.jb, hq = blockIdx.y, b = blockIdx.z;
-    const int h = hq / a.dm.g, si = b * a.dm.Hkv + h;
-    const int64_t a0 = a.st.n_tokens[si];
-    const int Tn = a.T_tokens;
-    const int cl = min(C, Tn - j * C);              // queries in this chunk
-    const int64_t aj = a0 + (int64_t)j * C;         // token index of the chunk's first query
-    const size_t sj = (size_t)si * a.S + jj;
-    // filling chunks share one snapshot of H and s, that of the launch's first chunk, and have their rows in closed form
-    const int spc_in = a.fill_closed ? a.st.sp_count[si] : 0;
-    const bool filling = a.fill_closed && j < generic::first_scored_chunk(a, a0, spc_in);
-    const size_t sh = filling ? (size_t)si * a.S + (a.j0 - a.jb) : sj;
-    const uint16_t *Hsnap = reinterpret_cast<const uint16_t *>(a.snapH) + sh * (2 * DH * DF);
-    const float *ssnap = a.snapS + sh * DF;
-    const int32_t *Gsnap = a.snapG + sj * LAM;
-    const bf16_t *pK = a.prefK + (size_t)si * P * DH, *pV = a.prefV + (size_t)si * P * DH;
-    const bf16_t *kc = a.k + (size_t)si * Tn * DH, *vc = a.v + (size_t)si * Tn * DH;
-    const bf16_t *qh = a.q + (((size_t)b * a.dm.Hq + hq) * Tn + (size_t)j * C) * DH;
-    TO *oh = (TO *)a.out + (((size_t)b * a.dm.Hq + hq) * Tn + (size_t)j * C) * DH;
-    const bf16_t *Wq = a.Wq + (size_t)hq * M * DH;   // [M][DH]
-    const int vrow_c = P + j * C;                     // virtual row of the chunk's first token
-    const float scale2 = a.dm.scale * LOG2E;          // logits are kept in units of log2(e)
-
-    const int qi = 16 * w + r16;
-    bf16x8 BQ[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) BQ[ks] = ld_bf16x8(qh + (size_t)(qi < cl ? qi : 0) * DH + 32 * ks + 8 * g4);
-    for (int x = tid; x < DF / 4; x += 256) reinterpret_cast<float4 *>(s_l)[x] = reinterpret_cast<const float4 *>(ssnap)[x];
-    bool gneg = false;
-    for (int x = tid; x < LAM; x += 256) { const int gr = filling ? generic::fill_row(a, a0, spc_in, j, x) : Gsnap[x]; G_l[x] = gr; gneg |= gr < 0; }
-    if (lane == 0) gneg_l[w] = 0;
-    if (gneg) gneg_l[w] = 1;   // (after the store of 0 in program order; lanes of one wavefront, same value)
-    __syncthreads();
-    // Key blocks that lie in the cache and the window need no masks when every slot is in use, the window is full and the
-    // queries may read the cache: the per-element tests (an LDS read and three compares each) are skipped there.
-    const bool nomask_ok = !(gneg_l[0] | gneg_l[1] | gneg_l[2] | gneg_l[3]) && !(a.dm.hide & 2) && aj >= ETA;
-
-    // position -> source row of the key / value (or -1)
-    auto kv_row = [&](int pos) -> int {
-        if (pos < LAM) return G_l[pos];
-        if (pos >= NKEYS) return -1;
-        const int wpos = pos - LAM;                       // 0 .. ETA + C - 1: window, then the chunk
-        if (aj - ETA + wpos < 0 || wpos - ETA >= cl) return -1;
-        return vrow_c - ETA + wpos;
-    };
-
-    // ---- softmax part over key blocks of 128 positions
-    uint16_t *Kl = L, *Vr = L + DH * 128;   // [key][input piece ^ key % pieces] and [key][piece ^ vswz2(key)] (read transposed)
-    f32x4 out[NCT];
-#pragma unroll
-    for (int mt = 0; mt < NCT; mt++) out[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    float mrun = 0.f, lsum = 0.f;   // running max (units of log2 e) and running sum of weights
-    const int64_t tq = aj + qi;     // token index of this lane's query
-#pragma unroll 1
-    for (int blk = 0; blk < NB; blk++) {
-        // a thread stages PR / 4 items of the block, each one 16-byte piece of two neighbouring keys; the values stay
-        // row-major (the value GEMM reads them through the transposing LDS read)
-        constexpr int NIT = PR / 4;
-        uint4 kreg[NIT], kreh[NIT], vreg[NIT], vreh[NIT];
-#pragma unroll
-        for (int it = 0; it < NIT; it++) {
-            const int o = tid + 256 * it, kk = 2 * (o / PR), ch = o % PR;
-            const int vr0 = kv_row(128 * blk + kk), vr1 = kv_row(128 * blk + kk + 1);
-            kreg[it] = kreh[it] = vreg[it] = vreh[it] = make_uint4(0, 0, 0, 0);
-            if (vr0 >= 0) {
-                kreg[it] = reinterpret_cast<const uint4 *>(vr0 < P ? pK + (size_t)vr0 * DH : kc + (size_t)(vr0 - P) * DH)[ch];
-                vreg[it] = reinterpret_cast<const uint4 *>(vr0 < P ? pV + (size_t)vr0 * DH : vc + (size_t)(vr0 - P) * DH)[ch];
-            }
-            if (vr1 >= 0) {
-                kreh[it] = reinterpret_cast<const uint4 *>(vr1 < P ? pK + (size_t)vr1 * DH : kc + (size_t)(vr1 - P) * DH)[ch];
-                vreh[it] = reinterpret_cast<const uint4 *>(vr1 < P ? pV + (size_t)vr1 * DH : vc + (size_t)(vr1 - P) * DH)[ch];
-            }
-        }
-        __syncthreads();   // previous users of L (the previous block) are done
-#pragma unroll
-        for (int it = 0; it < NIT; it++) {
-            const int o = tid + 256 * it, kk = 2 * (o / PR), ch = o % PR;
-            *reinterpret_cast<uint4 *>(&Kl[kk * DH + ((ch ^ (kk & (PR - 1))) << 3)]) = kreg[it];
-            *reinterpret_cast<uint4 *>(&Kl[(kk + 1) * DH + ((ch ^ ((kk + 1) & (PR - 1))) << 3)]) = kreh[it];
-            *reinterpret_cast<uint4 *>(&Vr[kk * DH + ((ch ^ vswz2<PR>(kk)) << 3)]) = vreg[it];
-            *reinterpret_cast<uint4 *>(&Vr[(kk + 1) * DH + ((ch ^ vswz2<PR>(kk + 1)) << 3)]) = vreh[it];
-        }
-        __syncthreads();
-        // S^T = K Q^T for the 8 key tiles of the block; lane (column = query r16, group g4) holds keys 16 mt + 4 g4 + i
-        f32x4 sc[8];
-        float bmax = mrun;
-#pragma unroll
-        for (int mt = 0; mt < 8; mt++) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KS; ks++)
-                acc = mfma16(as_bf16x8(*reinterpret_cast<const uint4 *>(&Kl[(16 * mt + r16) * DH + (((4 * ks + g4) ^ (r16 & (PR - 1))) << 3)])), BQ[ks], acc);
-            if (nomask_ok && 128 * (blk + 1) <= LAM + ETA) {
-#pragma unroll
-                for (int i = 0; i < 4; i++) { acc[i] *= scale2; bmax = fmaxf(bmax, acc[i]); }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int pos = 128 * blk + 16 * mt + 4 * g4 + i;
-                    bool ok;
-                    if (pos < LAM) ok = G_l[pos] >= 0 && !(a.dm.hide & 2);
-                    else if (pos < LAM + ETA) ok = aj - ETA + (pos - LAM) >= 0;
-                    else ok = pos < NKEYS && (aj + (pos - LAM - ETA)) <= tq;
-                    acc[i] = ok ? acc[i] * scale2 : -INFINITY;
-                    bmax = fmaxf(bmax, acc[i]);
-                }
-            }
-            sc[mt] = acc;
-        }
-        bmax = grp_max(bmax);
-        const float resc = fexp2(mrun - bmax);
-        mrun = bmax;
-        lsum *= resc;
-#pragma unroll
-        for (int mt = 0; mt < NCT; mt++) out[mt] *= resc;
-#pragma unroll
-        for (int s = 0; s < 4; s++) {
-            float pw[8];
-#pragma unroll
-            for (int e = 0; e < 8; e++) { pw[e] = fexp2(sc[2 * s + (e >> 2)][e & 3] - mrun); lsum += pw[e]; }
-            bf16x8 Ph, Pl;
-            split8(pw, Ph, Pl);
-            // A = V^T of keys 32 s ..: lane (column r16 of tile mt, group g4) holds keys 4 g4 + 0..3 and 16 + 4 g4 + 0..3 (the
-            // order of pw) of its column, through the transposing read of the row-major block
-            const int t0 = 4 * g4 + (r16 >> 2);
-            const uint16_t *vb = &Vr[(32 * s + t0) * DH + 4 * (r16 & 1)];
-#pragma unroll
-            for (int mt = 0; mt < NCT; mt++) {
-                const int pc = ((2 * mt + ((r16 & 3) >> 1)) ^ vswz2<PR>(t0)) << 3;
-                const bf16x4 b0 = tr_read(vb + pc), b1 = tr_read(vb + 16 * DH + pc);
-                const bf16x8 Av = __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7);
-                out[mt] = mfma16(Av, Ph, out[mt]);
-                out[mt] = mfma16(Av, Pl, out[mt]);
-            }
-        }
-    }
-    lsum = grp_sum(lsum);
-
-    // ---- linear part: phi(q), phi(q)^T s, then lin^T = H^T phi(q)^T with the snapshot staged 128 features at a time
-    float pp[4 * NZT], pn[4 * NZT];
-    {
-        f32x4 zt[NZT];
-#pragma unroll
-        for (int mt = 0; mt < NZT; mt++) {
-            zt[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KS; ks++)
-                zt[mt] = mfma16(ld_bf16x8(Wq + (size_t)(16 * mt + r16) * DH + 32 * ks + 8 * g4), BQ[ks], zt[mt]);
-        }
-        phi_from_z_tiles<NZT>(zt, a.dm.phi_kind, pp, pn);
-    }
-    float lden = 0.f;   // phi(q)^T s
-#pragma unroll
-    for (int mt = 0; mt < NZT; mt++) {
-        const float4 sp4 = *reinterpret_cast<const float4 *>(&s_l[16 * mt + 4 * g4]);
-        const float4 sn4 = *reinterpret_cast<const float4 *>(&s_l[M + 16 * mt + 4 * g4]);
-        lden = fmaf(pp[4 * mt], sp4.x, lden); lden = fmaf(pp[4 * mt + 1], sp4.y, lden);
-        lden = fmaf(pp[4 * mt + 2], sp4.z, lden); lden = fmaf(pp[4 * mt + 3], sp4.w, lden);
-        lden = fmaf(pn[4 * mt], sn4.x, lden); lden = fmaf(pn[4 * mt + 1], sn4.y, lden);
-        lden = fmaf(pn[4 * mt + 2], sn4.z, lden); lden = fmaf(pn[4 * mt + 3], sn4.w, lden);
-    }
-    lden = grp_sum(lden);
-    // B operands of the read-out: k-step ks covers features 32 ks ..: the first KSD / 2 k-steps the positive half
-    bf16x8 Bh[KSD], Bl[KSD];
-#pragma unroll
-    for (int ks = 0; ks < KSD / 2; ks++) {
-        split8(&pp[8 * ks], Bh[ks], Bl[ks]);
-        split8(&pn[8 * ks], Bh[KSD / 2 + ks], Bl[KSD / 2 + ks]);
-    }
-    const float el = (a.dm.hide & 1) ? 0.f : fexp2(-mrun);   // restricted query: no hidden-state terms
-    const float inv = frcp(fmaf(el, lden, lsum));
-    f32x4 lin[NCT], lin2[NCT];
-#pragma unroll
-    for (int mt = 0; mt < NCT; mt++) { lin[mt] = (f32x4){0.f, 0.f, 0.f, 0.f}; lin2[mt] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
-#pragma unroll 1
-    for (int fh = 0; fh < NFH; fh++) {
-        __syncthreads();   // the last key block (or the previous half) has been consumed
-        // snapshot order: [part][row tile of 16][k-step][lane = 16 (piece % 4) + row % 16]; this half: k-steps 4 fh .. 4 fh + 3
-        for (int o = tid; o < 2 * DH * 16; o += 256) {
-            const int part = o / (DH * 16), op = o % (DH * 16);
-            const int ct = op >> 8, ksl = (op >> 6) & 3, ln = op & 63;
-            const uint4 hv = reinterpret_cast<const uint4 *>(Hsnap)[(size_t)part * (DH * DF / 8) + (ct * KSD + 4 * fh + ksl) * 64 + ln];
-            const int c = 16 * ct + (ln & 15), ch = 4 * ksl + (ln >> 4);
-            *reinterpret_cast<uint4 *>(&L[part * DH * 128 + c * 128 + ((ch ^ (c & 15)) << 3)]) = hv;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int mt = 0; mt < NCT; mt++) {
-#pragma unroll
-            for (int ks = 0; ks < 4; ks++) {
-                const int addr = (16 * mt + r16) * 128 + (((4 * ks + g4) ^ r16) << 3);
-                const bf16x8 Ahi = as_bf16x8(*reinterpret_cast<const uint4 *>(&L[addr]));
-                const bf16x8 Alo = as_bf16x8(*reinterpret_cast<const uint4 *>(&L[DH * 128 + addr]));
-                const bf16x8 bh = fh == 0 ? Bh[ks] : Bh[(KSD > 4 ? 4 : 0) + ks], bl = fh == 0 ? Bl[ks] : Bl[(KSD > 4 ? 4 : 0) + ks];
-                lin[mt] = mfma16(Ahi, bh, lin[mt]);
-                lin2[mt] = mfma16(Ahi, bl, lin2[mt]);
-                lin2[mt] = mfma16(Alo, bh, lin2[mt]);
-            }
-        }
-    }
-    if (qi < cl) {
-#pragma unroll
-        for (int mt = 0; mt < NCT; mt++) {
-            const f32x4 ln4 = lin[mt] + lin2[mt];
-            TO *dst = oh + (size_t)qi * DH + 16 * mt + 4 * g4;
-#pragma unroll
-            for (int i = 0; i < 4; i++) stf(dst, i, fmaf(el, ln4[i], out[mt][i]) * inv);
-        }
-    }
-}
-
 
 // ---------------------------------------------------------------------------------------------
 // Sequential state evolution of the prefill (paper Sec. 3 "Chunkwise Inference": after each chunk the
