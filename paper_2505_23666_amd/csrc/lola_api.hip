@@ -25,6 +25,8 @@ inline size_t esize(int dtype) { return dtype == LOLA_BF16 ? 2 : 4; }
 
 constexpr size_t LDS_LIMIT = 64 * 1024 - 256;   // static workgroup limit minus the kernels' few static words
 
+constexpr int CHIP_CUS = 256;   // compute units of the MI355X
+
 constexpr int DEFER_R = 8;   // pairs a stream may list before the generation step writes its state back
 
 // The fused MFMA generation step covers the Llama-8B head shape with bf16 storage.
@@ -301,27 +303,36 @@ lola_status run_decode(const lola_config *c, const lola_state *st, const void *q
             ua.st = a.st; ua.k = a.k; ua.v = a.v; ua.Wk = a.Wk;
             ua.Hkv = a.dm.Hkv; ua.lam = a.dm.lam; ua.eta = a.dm.eta; ua.phi_kind = a.dm.phi_kind;
             ua.scr_stride = (int)step_scratch_floats(c);
-            // Few streams and several passes over the cached pairs: the scoring is split over `parts` workgroups per
-            // stream (each at least one pass of 256 pairs, all of them resident at once), a second launch does the rest.
-            // The scores travel through sp_score, which a self-recall-error state may carry as scratch.
-            // Where the compute units suffice for one tile of 16 pairs per wavefront (lambda / 128 workgroups per stream),
-            // the parts take single tiles instead of pairs of tiles.
-            const int ns = a.dm.B * a.dm.Hkv, npass = a.dm.lam / 256;
+            // At most 64 streams (and the scratch for the scores, sp_score, which a self-recall-error state may carry): groups
+            // of 32 candidates dealt to several workgroups per stream, then arg-min and fold, the rows of H^T dealt likewise.  128
+            // workgroups read the state less often than 256 would and are faster up to 4 groups each (eta = lambda = 256, batch 4:
+            // 34.2 us a step against 39.3; eta 512, lambda 1024: 51.5 against 48.1 with 8 groups each); the leaving pair has a
+            // workgroup of its own where one is left.
+            const int ns = a.dm.B * a.dm.Hkv, npass = a.dm.lam / 256, ngroups = a.dm.lam / 32;
+            // (At head_dim 64 the kernel with one workgroup per stream has less to read: from 8 groups per workgroup on it stays,
+            // 31.6 us against 32.8 at eta 64, lambda 1024, batch 8.)
+            const bool split = !a.dm.score_kind && st->sp_score && ns <= 64 && (c->head_dim == 128 || ngroups * ns <= 6 * CHIP_CUS);
+            ua.nparts = std::max(1, std::min(ngroups, CHIP_CUS / 2 / ns));
+            if (ngroups > 4 * ua.nparts) ua.nparts = std::min(ngroups, CHIP_CUS / ns);
+            const dim3 grids(ns, ua.nparts + (ns * (ua.nparts + 1) <= CHIP_CUS ? 1 : 0));
+            const int fp = ns <= 32 ? 8 : 4;   // parts of H^T in the fold
+            // Up to 128 streams and several passes over the cached pairs: the scoring is split over two workgroups per stream, a
+            // second launch does the rest (batch 16 at lambda = 512: 69.5 us a step, 78.5 in one launch, 72.9 as above).
             int parts = 1;
-            bool single = false;
-            if (!a.dm.score_kind && st->sp_score && npass >= 2 && 2 * ns <= 256) {
-                single = a.dm.lam % 128 == 0 && ns * (a.dm.lam / 128) <= 256;
-                parts = single ? a.dm.lam / 128 : std::min(npass, 256 / ns);
-            }
+            if (!a.dm.score_kind && st->sp_score && npass >= 2 && 2 * ns <= CHIP_CUS) parts = std::min(npass, CHIP_CUS / ns);
             const dim3 grid1(ns, parts);
+#define LOLA_FOLD(DHV, DFV, FPV) hipLaunchKernelGGL((fast::step_fold_kernel<DHV, DFV, FPV>), dim3(ns, FPV), dim3(512), 0, stream, ua)
 #define LOLA_UPD(DHV, DFV) do { if (a.dm.score_kind) hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, true>), grid, dim3(512), 0, stream, ua); \
-                                else if (parts == 1) hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, false>), grid, dim3(512), 0, stream, ua); \
-                                else { if (single) hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, false, 1, 1>), grid1, dim3(512), 0, stream, ua); \
-                                       else hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, false, 1>), grid1, dim3(512), 0, stream, ua); \
+                                else if (split) { \
+                                    hipLaunchKernelGGL((fast::step_score_kernel<DHV, DFV>), grids, dim3(512), 0, stream, ua); \
+                                    if (fp == 8 && DHV * DFV > 64 * 128) LOLA_FOLD(DHV, DFV, (DHV * DFV > 64 * 128 ? 8 : 4)); else LOLA_FOLD(DHV, DFV, 4); \
+                                } else if (parts == 1) hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, false>), grid, dim3(512), 0, stream, ua); \
+                                else { hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, false, 1>), grid1, dim3(512), 0, stream, ua); \
                                        hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, false, 2>), grid, dim3(512), 0, stream, ua); } } while (0)
             if (c->head_dim == 128) { if (c->feat_dim == 256) LOLA_UPD(128, 256); else LOLA_UPD(128, 128); }
             else { if (c->feat_dim == 256) LOLA_UPD(64, 256); else LOLA_UPD(64, 128); }
 #undef LOLA_UPD
+#undef LOLA_FOLD
             LAUNCH_CHECK();
             updated = true;
         }
@@ -385,7 +396,6 @@ struct SideStream {
 #define LOLA_SCAN_RT128 1
 #endif
 constexpr int SCAN_RT128 = LOLA_SCAN_RT128;   // row tiles of H^T per wavefront in the MFMA scan at head_dim 128
-constexpr int CHIP_CUS = 256;                 // compute units of the MI355X
 constexpr size_t OVERLAP_MAX_STREAMS = 128;   // beyond this many streams the serial evolution fills the chip by itself
 constexpr int OVERLAP_MIN_PIECE = 8;          // chunks per piece on average at least
 constexpr size_t OVERLAP_MIN_WORK = 2048;     // output workgroups (in units of 64 head columns) per piece at least: below

@@ -2217,7 +2217,8 @@ struct StepUpdateArgs {
     State<bf16_t> st;
     const bf16_t *k, *v, *Wk;
     int Hkv, lam, eta, phi_kind;
-    int scr_stride;       // split forms: floats per stream in the scratch (sp_score)
+    int scr_stride;       // forms of several workgroups per stream: floats per stream in the scratch (sp_score)
+    int nparts;           // step_score_kernel: workgroups per stream that score cached pairs
 };
 
 constexpr int STEP_UPDATE_LAMMAX = 2048;
@@ -2259,14 +2260,11 @@ __device__ __forceinline__ void fill_step(const StepUpdateArgs &a, int si, int64
 // split off: MODE 1 = grid (streams, parts), workgroup (stream, part) scores the passes part, part + parts, ... into
 // sp_score (scratch in this mode) and changes nothing else; MODE 2 = one workgroup per stream reads those scores and does
 // the rest (the leaving pair's score, steps 3 and 4).  The scores are computed by the same instructions in either form.
-// NTP: tiles of 16 candidates a wavefront takes per pass (2: the operands of H^T and W_k serve both; 1 for the score
-// part when there are compute units enough to give every wavefront a single tile).
-template <int DH, int DF, bool SCORED, int MODE = 0, int NTP = 2>
+template <int DH, int DF, bool SCORED, int MODE = 0>
 __global__ __launch_bounds__(512) void step_update_wide_kernel(StepUpdateArgs a) {
     static_assert(MODE == 0 || !SCORED, "the split forms score by self-recall error");
-    static_assert(NTP == 2 || (NTP == 1 && MODE == 1), "single tiles: score part only");
     constexpr int M = DF / 2, KS = DH / 32, NZT = M / 16, KF = DF / 32, NCT = DH / 16, NP = NCT * KF / 8, PR = DH / 8;
-    constexpr int LAMMAX = STEP_UPDATE_LAMMAX;
+    constexpr int LAMMAX = STEP_UPDATE_LAMMAX, NTP = 2;   // tiles of 16 candidates per pass: the operands of H^T and W_k serve both
     __shared__ __attribute__((aligned(16))) uint4 HA[NCT * KF * 2 * 64];     // [row tile][k-step][part][lane]
     __shared__ __attribute__((aligned(16))) float s_l[DF];
     __shared__ __attribute__((aligned(16))) float phif[DF];                  // phi of the folded pair
@@ -2640,6 +2638,357 @@ __global__ __launch_bounds__(512) void step_update_wide_kernel(StepUpdateArgs a)
         if (SCORED && tid == 65) sps[drop] = score[LAM];
     }
     if (SCORED && tid == 66) wsc[0] = 0.f;
+    const bf16_t *knew = a.k + (size_t)si * DH, *vnew = a.v + (size_t)si * DH;
+    if (tid >= 128 && tid < 128 + PR) reinterpret_cast<uint4 *>(win_k)[tid - 128] = reinterpret_cast<const uint4 *>(knew)[tid - 128];
+    else if (tid >= 192 && tid < 192 + PR) reinterpret_cast<uint4 *>(win_v)[tid - 192] = reinterpret_cast<const uint4 *>(vnew)[tid - 192];
+    if (tid == 0) a.st.n_tokens[si] = tok + 1;
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same update for few streams (self-recall error, with the scratch), in two launches.  What one workgroup of the kernel
+// above is bounded by is its compute unit's intake: every wavefront reads all of W_k (from L2) for its own candidates and all
+// of the split H^T (from LDS).  Here a wavefront owns 16 rows of H^T as operands in registers and 16 projections of W_k, and the
+// workgroup takes 32 candidates at a time: projections to LDS, features to LDS as bf16 high + low operands, recall of all 32
+// against the wavefront's rows, squared errors summed over the wavefronts.  Nothing is read twice by a workgroup, and the groups
+// of 32 are dealt to several workgroups per stream.  A group takes 2.6 us with 256 features (1.9 above, where two tiles of 16 per
+// wavefront share every operand, so that many streams and large budgets stay there), the start 10 us, the fold 7.  Step at the 8B shape, 256
+// features, us before and after: eta = lambda = 256 47.7 -> 30.9 (batch 2), 48.7 -> 34.2 (4), 52.6 -> 43.3 (8); 512 49.2 -> 33.8,
+// 50.1 -> 40.2, 54.7 -> 51.4; 1024 51.0 -> 39.6, 52.7 -> 48.1, 62.0 -> 62.1.
+//
+// Scratch of a stream: the cached pairs' scores [0, lambda), the leaving pair's at lambda, then STEP_* words.
+constexpr int STEP_ARRIVED = 1, STEP_STEADY = 2;   // behind the leaving pair's score
+
+template <int DH, int DF>
+__global__ __launch_bounds__(512) void step_score_kernel(StepUpdateArgs a) {
+    constexpr int M = DF / 2, KS = DH / 32, NZT = M / 16, KF = DF / 32, NCT = DH / 16;
+    constexpr int UZ = NZT == 8 ? 2 : 1;    // candidate tiles per wavefront in the projections (8 wavefronts: NZT tiles of W_k x 2 / UZ)
+    constexpr int UR = NCT == 8 ? 2 : 1;    // ... and in the recall
+    constexpr int PL = M / 16, ZS = M + 4;  // projections per lane when features are made; row stride of the projections
+    __shared__ __attribute__((aligned(16))) float s_l[DF];
+    __shared__ __attribute__((aligned(16))) float zl[32 * ZS];                // projections of 32 candidates
+    __shared__ __attribute__((aligned(16))) uint16_t ph[2][2][KF * 512];      // [tile][part][k-step][lane]: their features
+    __shared__ __attribute__((aligned(16))) float zp[M];                      // projections of the leaving pair
+    __shared__ float rd_l[2][32], err_l[2][NCT][32], errp_l[DH], errp[2];
+
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
+    const int si = blockIdx.x, h = si % a.Hkv, LAM = a.lam, ETA = a.eta, part = blockIdx.y, nparts = a.nparts, ng = LAM / 32;
+    const bool leave = part == (int)gridDim.y - 1;   // scores the leaving pair, behind its cached pairs' loads or alone
+    const int ct = NCT == 8 ? w : w & 3, ur0 = NCT == 8 ? 0 : w >> 2;         // row tile of H^T, first candidate tile of the recall
+    const int mz = NZT == 8 ? w : w & 3, uz0 = NZT == 8 ? 0 : w >> 2;         // tile of W_k, first candidate tile of the projections
+    const float *Hg = a.st.H + (size_t)si * DF * DH, *sg = a.st.s + (size_t)si * DF;
+    const bf16_t *Wk = a.Wk + (size_t)h * M * DH;
+    const bf16_t *sp_k = a.st.sp_k + (size_t)si * LAM * DH, *sp_v = a.st.sp_v + (size_t)si * LAM * DH;
+    float *scr = a.st.sp_score + (size_t)si * a.scr_stride;
+    // ---- operands; a group's keys and values are requested one group ahead
+    bf16x8 BK[UZ][KS], W[KS];
+    uint2 vv[UR];
+    auto load_group = [&](int gi) {
+#pragma unroll
+        for (int u = 0; u < UZ; u++)
+#pragma unroll
+            for (int ks = 0; ks < KS; ks++) BK[u][ks] = ld_bf16x8(sp_k + (size_t)(32 * gi + 16 * (uz0 + u) + r16) * DH + 32 * ks + 8 * g4);
+#pragma unroll
+        for (int u = 0; u < UR; u++) vv[u] = *reinterpret_cast<const uint2 *>(sp_v + (size_t)(32 * gi + 16 * (ur0 + u) + r16) * DH + 16 * ct + 4 * g4);
+    };
+    if (part < nparts) load_group(part);
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) W[ks] = ld_bf16x8(Wk + (size_t)(16 * mz + r16) * DH + 32 * ks + 8 * g4);
+    float4 hreg[KF][2];
+#pragma unroll
+    for (int ks = 0; ks < KF; ks++) {
+        const float *hp = Hg + (size_t)(16 * ct + r16) * DF + 32 * ks + 4 * g4;
+        hreg[ks][0] = *reinterpret_cast<const float4 *>(hp);
+        hreg[ks][1] = *reinterpret_cast<const float4 *>(hp + 16);
+    }
+    for (int x = tid; x < DF; x += 512) s_l[x] = sg[x];
+    const int64_t tok = a.st.n_tokens[si];
+    const bool steady = tok >= (int64_t)ETA && a.st.sp_count[si] == LAM;
+    if (leave && tid == 0) {
+        reinterpret_cast<int *>(scr)[LAM + STEP_ARRIVED] = 0;
+        reinterpret_cast<int *>(scr)[LAM + STEP_STEADY] = steady;
+    }
+    if (!steady) return;
+    if (leave) {   // the leaving pair, from the state as fp32: same operations as in the one-launch form
+        const size_t wrow = (size_t)si * ETA + (int)(tok % ETA);
+        const bf16_t *win_k = a.st.win_k + wrow * DH, *win_v = a.st.win_v + wrow * DH;
+        bf16x8 zK[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) zK[ks] = ld_bf16x8(win_k + 32 * ks + 8 * g4);
+        const float pv = ldf(win_v, 16 * ct + r16);
+        f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) z = mfma16(W[ks], zK[ks], z);
+        if (w < NZT && r16 == 0) *reinterpret_cast<f32x4 *>(&zp[16 * mz + 4 * g4]) = z;
+        lds_barrier();
+        float pp[4 * NZT], pn[4 * NZT];
+        f32x4 zt[NZT];
+#pragma unroll
+        for (int mt = 0; mt < NZT; mt++) zt[mt] = *reinterpret_cast<const f32x4 *>(&zp[16 * mt + 4 * g4]);
+        phi_from_z_tiles<NZT>(zt, a.phi_kind, pp, pn);
+        float dn = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < NZT; mt++) {
+            const float4 sp4 = *reinterpret_cast<const float4 *>(&s_l[16 * mt + 4 * g4]);
+            const float4 sn4 = *reinterpret_cast<const float4 *>(&s_l[M + 16 * mt + 4 * g4]);
+            dn = fmaf(pp[4 * mt], sp4.x, dn); dn = fmaf(pp[4 * mt + 1], sp4.y, dn);
+            dn = fmaf(pp[4 * mt + 2], sp4.z, dn); dn = fmaf(pp[4 * mt + 3], sp4.w, dn);
+            dn = fmaf(pn[4 * mt], sn4.x, dn); dn = fmaf(pn[4 * mt + 1], sn4.y, dn);
+            dn = fmaf(pn[4 * mt + 2], sn4.z, dn); dn = fmaf(pn[4 * mt + 3], sn4.w, dn);
+        }
+        dn = grp_sum(dn);
+        const float rdp = dn > 0.f ? 1.0f / dn : 0.f;
+        float rec = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KF; ks++) {   // (features 32 ks + 4 g4 + 0..3 and + 16 .. are the lane's own)
+            const float *p = ks < KF / 2 ? &pp[8 * ks] : &pn[8 * (ks - KF / 2)];
+            float d0 = hreg[ks][0].x * p[0];
+            d0 = fmaf(hreg[ks][0].y, p[1], d0); d0 = fmaf(hreg[ks][0].z, p[2], d0); d0 = fmaf(hreg[ks][0].w, p[3], d0);
+            d0 = fmaf(hreg[ks][1].x, p[4], d0); d0 = fmaf(hreg[ks][1].y, p[5], d0); d0 = fmaf(hreg[ks][1].z, p[6], d0); d0 = fmaf(hreg[ks][1].w, p[7], d0);
+            rec += grp_sum(d0);
+        }
+        if (w < NCT && g4 == 0) errp_l[16 * ct + r16] = rec * rdp - pv;
+        lds_barrier();
+        if (tid < 128) {
+            float err = tid < DH ? errp_l[tid < DH ? tid : 0] : 0.f;
+            err = wsum(err * err);
+            if (lane == 0) errp[w] = err;
+        }
+        lds_barrier();
+        if (tid == 0) scr[LAM] = sqrtf(errp[0] + errp[1]);
+        if (part >= nparts) return;
+    } else {
+        lds_barrier();   // (s is in LDS)
+    }
+    bf16x8 Ah[KF], Al[KF];
+#pragma unroll
+    for (int ks = 0; ks < KF; ks++) {
+        const float x8[8] = {hreg[ks][0].x, hreg[ks][0].y, hreg[ks][0].z, hreg[ks][0].w, hreg[ks][1].x, hreg[ks][1].y, hreg[ks][1].z, hreg[ks][1].w};
+        split8(x8, Ah[ks], Al[ks]);
+    }
+    // the sum of a group's squared errors over the row tiles, one group behind
+    auto finish = [&](int gi, int buf) {
+        if (tid < 32) {
+            float e = 0.f;
+#pragma unroll
+            for (int c = 0; c < NCT; c++) e += err_l[buf][c][tid];
+            scr[32 * gi + tid] = sqrtf(e);
+        }
+    };
+    int buf = 0;
+#pragma unroll 1
+    for (int gi = part; gi < ng; gi += nparts, buf ^= 1) {
+        // projections: this wavefront's 16 rows of W_k
+#pragma unroll
+        for (int u = 0; u < UZ; u++) {
+            f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ks++) z = mfma16(W[ks], BK[u][ks], z);
+            *reinterpret_cast<f32x4 *>(&zl[(16 * (uz0 + u) + r16) * ZS + 16 * mz + 4 * g4]) = z;
+        }
+        uint2 vc[UR];
+#pragma unroll
+        for (int u = 0; u < UR; u++) vc[u] = vv[u];
+        if (gi + nparts < ng) load_group(gi + nparts);
+        lds_barrier();
+        if (gi != part) finish(gi - nparts, buf ^ 1);
+        {   // features: sixteen lanes per candidate, PL projections each
+            const int c = 4 * w + g4, q = r16;
+            float z[PL];
+#pragma unroll
+            for (int x = 0; x < PL; x += 4) {
+                const float4 t = *reinterpret_cast<const float4 *>(&zl[c * ZS + PL * q + x]);
+                z[x] = t.x; z[x + 1] = t.y; z[x + 2] = t.z; z[x + 3] = t.w;
+            }
+            float cp = 0.f, cn = 0.f;
+            if (a.phi_kind != 1) {
+                float zmax = z[0], zmin = z[0];
+#pragma unroll
+                for (int x = 1; x < PL; x++) { zmax = fmaxf(zmax, z[x]); zmin = fminf(zmin, z[x]); }
+                zmax = fmaxf(zmax, dpp_f<0xB1>(zmax)); zmax = fmaxf(zmax, dpp_f<0x4E>(zmax)); zmax = fmaxf(zmax, dpp_f<0x141>(zmax)); zmax = fmaxf(zmax, dpp_f<0x140>(zmax));
+                zmin = fminf(zmin, dpp_f<0xB1>(zmin)); zmin = fminf(zmin, dpp_f<0x4E>(zmin)); zmin = fminf(zmin, dpp_f<0x141>(zmin)); zmin = fminf(zmin, dpp_f<0x140>(zmin));
+                cp = -zmax * LOG2E; cn = zmin * LOG2E;
+            }
+            float p[PL], n[PL], sp = 0.f, sn = 0.f, dp = 0.f, dm = 0.f;
+#pragma unroll
+            for (int x = 0; x < PL; x++) {
+                p[x] = fexp2(fmaf(z[x], LOG2E, cp)); n[x] = fexp2(fmaf(z[x], -LOG2E, cn));
+                sp += p[x]; sn += n[x];
+                dp = fmaf(p[x], s_l[PL * q + x], dp); dm = fmaf(n[x], s_l[M + PL * q + x], dm);
+            }
+            auto row_sum = [&](float v) { v += dpp_f<0xB1>(v); v += dpp_f<0x4E>(v); v += dpp_f<0x141>(v); v += dpp_f<0x140>(v); return v; };
+            float ip = 1.f, in_ = 1.f;
+            if (a.phi_kind != 1) { ip = frcp(row_sum(sp)); in_ = frcp(row_sum(sn)); }
+            const float dn = row_sum(fmaf(dp, ip, dm * in_));
+            if (q == 0) rd_l[buf][c] = dn > 0.f ? 1.0f / dn : 0.f;   // recall = 0 while nothing was folded
+#pragma unroll
+            for (int sg_ = 0; sg_ < 2; sg_++)
+#pragma unroll
+                for (int x = 0; x < PL; x += 4) {
+                    // quad of features f .. f + 3: k-step f / 32, its half (f % 32) / 16, lane group (f % 16) / 4; the candidate's place
+                    // XOR-swizzled by the k-step, which spreads these stores over the banks
+                    const int f = PL * q + x + (sg_ ? M : 0), off = ((f >> 5) * 64 + 16 * ((f & 15) >> 2) + ((c & 15) ^ (((f >> 5) & 3) << 2))) * 8 + 4 * ((f >> 4) & 1);
+                    uint32_t hb[2], lb[2];
+#pragma unroll
+                    for (int y = 0; y < 2; y++) {
+                        const f32x2 v = {(sg_ ? n[x + 2 * y] * in_ : p[x + 2 * y] * ip), (sg_ ? n[x + 2 * y + 1] * in_ : p[x + 2 * y + 1] * ip)};
+                        hb[y] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+                        const f32x2 r = {v[0] - __uint_as_float(hb[y] << 16), v[1] - __uint_as_float(hb[y] & 0xFFFF0000u)};
+                        lb[y] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+                    }
+                    *reinterpret_cast<uint2 *>(&ph[c >> 4][0][off]) = make_uint2(hb[0], hb[1]);
+                    *reinterpret_cast<uint2 *>(&ph[c >> 4][1][off]) = make_uint2(lb[0], lb[1]);
+                }
+        }
+        lds_barrier();
+        // recall of this wavefront's rows, squared errors against the values (the operands of four k-steps are read while the four
+        // before them are multiplied: left to itself the compiler reads each just before its use)
+        bf16x8 B[2][8];
+        auto read_ops = [&](int x) {   // x: four k-steps of a tile
+            const int u = x / (KF / 4), ks0 = x % (KF / 4) * 4;
+#pragma unroll
+            for (int y = 0; y < 4; y++) {
+                const int off = ((ks0 + y) * 64 + (lane ^ (y << 2))) * 8;
+                B[x & 1][y] = as_bf16x8(*reinterpret_cast<const uint4 *>(&ph[ur0 + u][0][off]));
+                B[x & 1][4 + y] = as_bf16x8(*reinterpret_cast<const uint4 *>(&ph[ur0 + u][1][off]));
+            }
+        };
+        read_ops(0);
+#pragma unroll
+        for (int u = 0; u < UR; u++) {
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = acc, acc3 = acc;
+#pragma unroll
+            for (int k4 = 0; k4 < KF / 4; k4++) {
+                const int x = u * (KF / 4) + k4;
+                if (x + 1 < UR * KF / 4) read_ops(x + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int y = 0; y < 4; y++) {
+                    acc = mfma16(Ah[4 * k4 + y], B[x & 1][y], acc);
+                    acc2 = mfma16(Ah[4 * k4 + y], B[x & 1][4 + y], acc2);
+                    acc3 = mfma16(Al[4 * k4 + y], B[x & 1][y], acc3);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const float rd = rd_l[buf][16 * (ur0 + u) + r16];
+            const float v4[4] = {bf_lo(vc[u].x), bf_hi(vc[u].x), bf_lo(vc[u].y), bf_hi(vc[u].y)};
+            float es = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const float err = (acc[i] + (acc2[i] + acc3[i])) * rd - v4[i];
+                es = fmaf(err, err, es);
+            }
+            es = grp_sum(es);
+            if (g4 == 0) err_l[buf][ct][16 * (ur0 + u) + r16] = es;
+        }
+    }
+    lds_barrier();
+    if (part < ng) finish(part + (ng - 1 - part) / nparts * nparts, buf ^ 1);
+}
+
+// What follows the scores: arg-min (ties: the larger token index goes), phi of the folded pair, rank-1 fold, slot and ring
+// replacement; grid (stream, FP parts of the rows of H^T).  A part reads what it needs, folds its rows and counts itself; the
+// last one to do so, behind which nobody reads the live state any more, changes s, the cache and the window.
+template <int DH, int DF, int FP>
+__global__ __launch_bounds__(512) void step_fold_kernel(StepUpdateArgs a) {
+    constexpr int M = DF / 2, KS = DH / 32, NZT = M / 16, PR = DH / 8, NH = DH * DF / FP / 4 / 512;
+    static_assert(NH >= 1, "at least one piece per thread");
+    __shared__ __attribute__((aligned(16))) float phif[DF], zp[M];
+    __shared__ __attribute__((aligned(16))) uint16_t pkb[DH], pvb[DH];   // the pair that leaves the window
+    __shared__ unsigned long long key_l[8];
+    __shared__ int drop_s, last_s;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
+    const int si = blockIdx.x, part = blockIdx.y, h = si % a.Hkv, LAM = a.lam, ETA = a.eta;
+    const float *scr = a.st.sp_score + (size_t)si * a.scr_stride;
+    int *words = reinterpret_cast<int *>(a.st.sp_score + (size_t)si * a.scr_stride) + LAM;
+    // this part's rows of H^T, flat pieces of four
+    float4 *Hp = reinterpret_cast<float4 *>(a.st.H + (size_t)si * DF * DH) + (size_t)part * (NH * 512);
+    float4 hreg[NH];
+#pragma unroll
+    for (int i = 0; i < NH; i++) hreg[i] = Hp[tid + 512 * i];
+    const bf16_t *Wk = a.Wk + (size_t)h * M * DH;
+    const int mz = NZT == 8 ? w : w & 3;
+    bf16x8 W[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) W[ks] = ld_bf16x8(Wk + (size_t)(16 * mz + r16) * DH + 32 * ks + 8 * g4);
+    int32_t *sp_idx = a.st.sp_idx + (size_t)si * LAM;
+    const int64_t tok = a.st.n_tokens[si];
+    if (!words[STEP_STEADY]) {   // (as the score kernel found the stream: the counters may change under the other parts)
+        if (part == 0) fill_step<DH, false>(a, si, tok, a.st.sp_count[si]);
+        return;
+    }
+    const int slot = (int)(tok % ETA), pidx = (int)(tok - ETA);
+    bf16_t *sp_k = a.st.sp_k + (size_t)si * LAM * DH, *sp_v = a.st.sp_v + (size_t)si * LAM * DH;
+    bf16_t *win_k = a.st.win_k + ((size_t)si * ETA + slot) * DH, *win_v = a.st.win_v + ((size_t)si * ETA + slot) * DH;
+    if (tid < PR) reinterpret_cast<uint4 *>(pkb)[tid] = reinterpret_cast<const uint4 *>(win_k)[tid];
+    else if (tid < 2 * PR) reinterpret_cast<uint4 *>(pvb)[tid - PR] = reinterpret_cast<const uint4 *>(win_v)[tid - PR];
+    // smallest score, ties -> the larger token index; NaN never, slot 0 if nothing else is left
+    constexpr unsigned long long NONE = ((unsigned long long)0x7F800000u << 32) | 0x80000000u;
+    unsigned long long best = NONE;
+    int be = -1;
+    for (int e = tid; e <= LAM; e += 512) {
+        const float sc = scr[e];
+        const int ix = e < LAM ? sp_idx[e] : pidx;
+        const unsigned long long key = sc == sc ? ((unsigned long long)__float_as_uint(sc) << 32) | (0x7FFFFFFFu - (uint32_t)ix) : NONE;
+        if (key < best) { best = key; be = e; }
+    }
+    const unsigned long long wbest = wmin_u64(best);
+    if (lane == 0) key_l[w] = wbest;
+    if (tid == 0) drop_s = 0;
+    __syncthreads();
+    unsigned long long all = key_l[0];
+#pragma unroll
+    for (int x = 1; x < 8; x++) all = key_l[x] < all ? key_l[x] : all;
+    if (be >= 0 && best == all) drop_s = be;   // (token indices are unique)
+    __syncthreads();
+    const int drop = drop_s;
+    const bf16_t *kr = drop < LAM ? sp_k + (size_t)drop * DH : reinterpret_cast<const bf16_t *>(pkb);
+    const bf16_t *vr = drop < LAM ? sp_v + (size_t)drop * DH : reinterpret_cast<const bf16_t *>(pvb);
+    float vf[NH];
+#pragma unroll
+    for (int i = 0; i < NH; i++) vf[i] = ldf(vr, (part * (NH * 512) + tid + 512 * i) / (DF / 4));
+    {   // (every column holds the same key: column 0 stores)
+        f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) z = mfma16(W[ks], ld_bf16x8(kr + 32 * ks + 8 * g4), z);
+        if (w < NZT && r16 == 0) *reinterpret_cast<f32x4 *>(&zp[16 * mz + 4 * g4]) = z;
+    }
+    lds_barrier();
+    if (w == 0) {
+        float pp[4 * NZT], pn[4 * NZT];
+        f32x4 zt[NZT];
+#pragma unroll
+        for (int mt = 0; mt < NZT; mt++) zt[mt] = *reinterpret_cast<const f32x4 *>(&zp[16 * mt + 4 * g4]);
+        phi_from_z_tiles<NZT>(zt, a.phi_kind, pp, pn);
+        if (r16 == 0) {
+#pragma unroll
+            for (int mt = 0; mt < NZT; mt++) {
+                *reinterpret_cast<float4 *>(&phif[16 * mt + 4 * g4]) = make_float4(pp[4 * mt], pp[4 * mt + 1], pp[4 * mt + 2], pp[4 * mt + 3]);
+                *reinterpret_cast<float4 *>(&phif[M + 16 * mt + 4 * g4]) = make_float4(pn[4 * mt], pn[4 * mt + 1], pn[4 * mt + 2], pn[4 * mt + 3]);
+            }
+        }
+    }
+    // everything this part reads of the live state has arrived: count
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (FP > 1 && tid == 0) last_s = __hip_atomic_fetch_add(&words[STEP_ARRIVED], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == FP - 1;
+#pragma unroll
+    for (int i = 0; i < NH; i++) {
+        const float4 p = *reinterpret_cast<const float4 *>(&phif[(tid + 512 * i) % (DF / 4) * 4]);
+        float4 x = hreg[i];
+        x.x = fmaf(p.x, vf[i], x.x); x.y = fmaf(p.y, vf[i], x.y); x.z = fmaf(p.z, vf[i], x.z); x.w = fmaf(p.w, vf[i], x.w);
+        Hp[tid + 512 * i] = x;
+    }
+    if (FP > 1) {
+        lds_barrier();
+        if (!last_s) return;
+    }
+    float *sg = a.st.s + (size_t)si * DF;
+    for (int x = tid; x < DF; x += 512) sg[x] += phif[x];
+    if (drop < LAM) {   // the leaving pair takes the freed slot
+        if (tid < PR) reinterpret_cast<uint4 *>(sp_k + (size_t)drop * DH)[tid] = reinterpret_cast<const uint4 *>(pkb)[tid];
+        else if (tid < 2 * PR) reinterpret_cast<uint4 *>(sp_v + (size_t)drop * DH)[tid - PR] = reinterpret_cast<const uint4 *>(pvb)[tid - PR];
+        if (tid == 64) sp_idx[drop] = pidx;
+    }
     const bf16_t *knew = a.k + (size_t)si * DH, *vnew = a.v + (size_t)si * DH;
     if (tid >= 128 && tid < 128 + PR) reinterpret_cast<uint4 *>(win_k)[tid - 128] = reinterpret_cast<const uint4 *>(knew)[tid - 128];
     else if (tid >= 192 && tid < 192 + PR) reinterpret_cast<uint4 *>(win_v)[tid - 192] = reinterpret_cast<const uint4 *>(vnew)[tid - 192];

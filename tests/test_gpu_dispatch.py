@@ -347,3 +347,35 @@ def test_output_kernel_edges(B, Hkv, g, d, D, eta, lam, T, kw):
     print("edges", B, Hkv, g, d, D, eta, lam, T, kw, flush=True)
     layer, o, _ = P.prefill_parity(sh, q[:, :, :T], k[:, :, :T], v[:, :, :T], Wq, Wk, layer_kw=kw)
     P.prefill_parity(sh, q[:, :, T:], k[:, :, T:], v[:, :, T:], Wq, Wk, layer=layer, oracle=o)
+
+
+@pytest.mark.parametrize("B,Hkv,d,D,eta,lam,kw", [(1, 1, 128, 256, 65, 64, {}), (3, 1, 64, 128, 100, 192, {}), (33, 1, 128, 128, 64, 320, {}), (8, 8, 64, 256, 30, 128, {}),
+                                                 (16, 4, 128, 256, 64, 256, dict(phi_kind=1)), (1, 5, 64, 256, 128, 2048, {})])
+def test_generation_step_in_groups_of_candidates(B, Hkv, d, D, eta, lam, kw):
+    """The step's scores from groups of 32 candidates on several workgroups and its fold in parts of the rows of H^T, at two groups,
+    more workgroups than groups, groups that do not divide evenly, 1 to 64 streams, and streams that are still filling: against one
+    workgroup per stream (no scratch), every memory equal bit for bit at every step.  Half of the sequences start short of
+    a full cache."""
+    Hq = 2 * Hkv
+    sh = wl.Shape("groups", "bf16", B, Hq, Hkv, d, D, T=0, eta=eta, lam=lam, C=64, seed=0)
+    T, nd = eta + lam + 70, 6
+    q, k, v, Wq, Wk = case_inputs(500 + d + D + lam, B, Hq, Hkv, d, D, T + nd, wscale=0.5 if kw.get("phi_kind") else 1.0)
+    dWq, dWk = P.w_to_dev(Wq, "bf16"), P.w_to_dev(Wk, "bf16")
+    print("groups", B, Hkv, d, D, eta, lam, kw, flush=True)
+    full, short = P.make_layer(sh, step_scratch=False, **kw), P.make_layer(sh, step_scratch=False, **kw)
+    for lay, n in ((full, T), (short, eta + lam - 3)):
+        lay.prefill(None, P.to_dev(k[:, :, :n], "bf16"), P.to_dev(v[:, :, :n], "bf16"), None, dWk)
+    lays = [P.make_layer(sh, step_scratch=x, **kw) for x in (True, False)]
+    assert lays[0].step_scratch is not None
+    lays[0].step_scratch.fill_(float("nan"))   # (nothing is read before it is written)
+    for lay in lays:
+        for nm in FIELDS:
+            for b in range(B):
+                getattr(lay, nm)[b].copy_(getattr(short if b % 2 else full, nm)[b])
+    for i in range(nd):
+        sq, sk, sv = (P.to_dev(np.ascontiguousarray(x[:, :, T + i]), "bf16") for x in (q, k, v))
+        outs = [lay.decode_step(sq, sk, sv, dWq, dWk) for lay in lays]
+        torch.cuda.synchronize()
+        assert torch.allclose(outs[0], outs[1], rtol=1e-5, atol=2e-6), i
+        for nm in FIELDS:
+            assert torch.equal(getattr(lays[0], nm), getattr(lays[1], nm)), (i, nm)
