@@ -405,8 +405,8 @@ constexpr size_t OVERLAP_RESTART_WORK = 4096; // the same for the third piece an
                                               // recomputes the cached keys' features on four wavefronts: 8 x 2048 tokens at the 1B
                                               // shape 371 us in two pieces, 379 in four, 8 x 4096 667 and 677; but 4 x 3000 444 in
                                               // one and 422 in two (at head_dim 128 4 x 2048 tokens 457 in two, 450 in four)
-constexpr int SHARE_MAX_WGS = 128;            // evolution workgroups at most where helpers are used
-constexpr int SHARE_MAX_HELPERS = 7;          // helpers per stream at most
+constexpr int SHARE_MAX_WGS = 128;            // evolution workgroups at most where helpers run beside outputs
+constexpr int SHARE_MAX_HELPERS = 7;          // helpers per stream at most there
 constexpr float SHARE_BESIDE = 0.77f;         // a piece beside outputs has helpers while its chain takes longer than this share of
                                               // them: where the outputs take 1.2 times the chain helpers still pay (3 x 2048 tokens at
                                               // eta = lambda = 512 0.95 ms without, 0.89 with), where they take 1.4 times no longer (4 x
@@ -633,6 +633,16 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                 if (wide && a.want_out && !a.dm.score_kind)
                     helpers = std::max(0, std::min({batches / 6, SHARE_MAX_WGS / (int)ns - 1, SHARE_MAX_HELPERS}));
                 a.chunk_us = 12.f + 2.f * batches;
+                // Where nothing runs beside the launch (no overlap, or the first piece) the idle compute units are free: as many
+                // helpers as the batches keep busy.  us per call without helpers, with the count above, with this one: 4 x 2048
+                // tokens at 256 features, eta = lambda = 256 1079 / 907 / 825, 512 1241 / 875 / 842, eta 64 / lambda 128 912 / 813 / 771;
+                // 128 features, 128 / 192 668 / 668 / 598, 128 / 256 723 / 723 / 598; 4096 tokens at 256 / 256 1976 / 1530 / 1186, at
+                // 512 / 1024 3733 / 1560 / 1331.  (Four batches lose with 7: 620; 34 batches with 7 take 1479.)
+                int alone = 0;
+                if (wide && a.want_out && !a.dm.score_kind && ns <= SHARE_MAX_WGS / 2) {
+                    alone = batches < 3 ? 0 : (batches == 3 ? 1 : (batches == 4 ? 2 : (batches <= 6 ? 3 : (batches < 16 ? 7 : 15))));
+                    alone = std::min(alone, CHIP_CUS / (int)ns - 1);
+                }
                 a.j_end = jend;
                 if (!wide && !big) {
                     const dim3 gp((unsigned)(jend - j0), (unsigned)ns);
@@ -716,11 +726,11 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                     // leaves.  While they take longer than the chain from here on, a helper's compute unit is theirs (the chain
                     // as if every chunk were scored; the kernel, which knows, looks again).
                     a.beside_us = side && ip > 0 ? SHARE_BESIDE * output_wg_us(c) * (float)(jend - prev0) * a.dm.Hq * a.dm.B * CHIP_CUS / (float)(CHIP_CUS - (int)ns) : 0.f;
-                    const bool shared = helpers > 0 && a.chunk_us * (float)(jend - p0) > a.beside_us;
+                    const int nhelp = a.beside_us > 0.f ? (a.chunk_us * (float)(jend - p0) > a.beside_us ? helpers : 0) : alone;
                     if (wide) {
 #define LOLA_WSCAN(DHV, DFV) do { if (side && ip > 0 && hipEventRecord(side->fork[ip - 1], stream) != hipSuccess) return LOLA_ERR_HIP; \
                                   if (a.dm.score_kind) hipLaunchKernelGGL((fast::scan_wide_kernel<DHV, DFV, true>), gs, dim3(DHV * 4), 0, stream, a); \
-                                  else if (shared) hipLaunchKernelGGL((fast::scan_wide_kernel<DHV, DFV, false, true>), dim3((unsigned)(ns * (1 + helpers))), dim3(DHV * 4), 0, stream, a); \
+                                  else if (nhelp > 0) hipLaunchKernelGGL((fast::scan_wide_kernel<DHV, DFV, false, true>), dim3((unsigned)(ns * (1 + nhelp))), dim3(DHV * 4), 0, stream, a); \
                                   else hipLaunchKernelGGL((fast::scan_wide_kernel<DHV, DFV, false>), gs, dim3(DHV * 4), 0, stream, a); } while (0)
                         if (c->head_dim == 128) { if (c->feat_dim == 256) LOLA_WSCAN(128, 256); else LOLA_WSCAN(128, 128); }
                         else { if (c->feat_dim == 256) LOLA_WSCAN(64, 256); else LOLA_WSCAN(64, 128); }
