@@ -406,18 +406,16 @@ constexpr size_t OVERLAP_RESTART_WORK = 4096; // the same for the third piece an
                                               // shape 371 us in two pieces, 379 in four, 8 x 4096 667 and 677; but 4 x 3000 444 in
                                               // one and 422 in two (at head_dim 128 4 x 2048 tokens 457 in two, 450 in four)
 constexpr int SHARE_MAX_WGS = 128;            // evolution workgroups at most where helpers run beside outputs
-constexpr int SHARE_MAX_HELPERS = 7;          // helpers per stream at most there
-constexpr float SHARE_BESIDE = 0.77f;         // a piece beside outputs has helpers while its chain takes longer than this share of
-                                              // them: where the outputs take 1.2 times the chain helpers still pay (3 x 2048 tokens at
-                                              // eta = lambda = 512 0.95 ms without, 0.89 with), where they take 1.4 times no longer (4 x
-                                              // 2048: 1.00 ms without, 1.10 with)
+constexpr float SHARE_BESIDE = 1.2f;          // a piece beside outputs has helpers while its chain takes longer than this times the outputs:
+                                              // they take compute units from the outputs (4 x 2048 tokens, 256 features, eta = lambda =
+                                              // 256 852 us without them in the second piece, 794 with; 512 958 and 759)
 
-// us of the whole chip per output workgroup at the run-time shapes (64 queries of one head): key blocks of 128 and the rest.  By
-// kernel trace at head_dim 128: 0.096 (5 blocks) and 0.149 (9) with 128 features, 0.120, 0.171 and 0.218 (5, 9, 13) with 256;
-// at 64: 0.042 (5, 128 features), 0.056 and 0.101 (5, 11; 256).
+// us of the whole chip per output workgroup of 64 queries of one head at the run-time shapes: key blocks of 128 and the rest.  By
+// kernel trace beside the evolution, scaled to the chip: 0.031 (2 blocks, 128 features), 0.063 (5, 256), 0.119 (13, 256) at
+// head_dim 128.
 float output_wg_us(const lola_config *c) {
     const float blocks = (float)((c->sparse_budget + c->window + 64 + 127) / 128);
-    return (float)c->head_dim / 128.f * (0.0133f * blocks + (c->feat_dim == 256 ? 0.052f : 0.028f));
+    return (float)c->head_dim / 128.f * (0.007f * blocks + (c->feat_dim == 256 ? 0.0273f : 0.0165f));
 }
 
 static_assert(SideStream::NEV <= fast::WIDE_PIECES, "every piece of a pass has exchange words of its own, cleared ahead of it");
@@ -620,29 +618,23 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                 // for every piece they took 24 us each).
                 // (a compile-time shape whose cache does not stay in LDS takes its features the run-time way)
                 const bool big = !wide && c->sparse_budget > 128;
-                // Few streams: further workgroups score shares of the candidates (prefill_mfma.h, WideShare).  A chunk costs a
-                // stream's workgroup about 12 us + 2 us per batch alone and an exchange of about 7 us (by difference) when shared, so a
-                // helper is worth its compute unit from about six batches on, and at most half of the compute units go to the
-                // evolution: 2 x 4096 tokens at eta 512 / lambda 1024 3.70 ms alone, 2.02 with 3 helpers per stream, 1.93 with 5, 1.98
-                // with 7, 2.23 with 15; 4 x 2048 at eta = lambda = 256 1.06 ms alone, 1.00 with 1 helper, 1.03 with 3, 1.16 with 7.
-                // A piece that runs beside outputs (below) gets them only if its chain is what the call waits for: 8 x 2048 tokens (64
-                // streams) at eta = lambda = 256 1.53 ms without helpers, 1.55 with one in every piece, 1.48 by this rule; at 512 1.81,
-                // 1.85 and 1.79; at eta 64 / lambda 512, 128 features 1.26, 1.28 and 1.21.
-                int helpers = 0;
+                // Few streams: further workgroups score shares of the candidates (prefill_mfma.h, WideShare), as many as the batches
+                // keep busy (a chunk costs a stream's workgroup about 12 us + 2 us per batch alone and an exchange of about 7 us
+                // when shared).  us per call without overlap, for 0 / 1 / 3 / 7 / 15 helpers per stream: 4 x 2048 tokens with 256
+                // features, eta = lambda = 256 1079 / 908 / 827 / 825, 512 1241 / 1005 / 879 / 842, eta 64 / lambda 128 912 / 810 / 771 /
+                // 808; 128 features, 128 / 192 668 / 630 / 603 / 620 (598 with 2), 128 / 256 723 / 680 / 598 / 623; 1 x 4096 at 256 / 256 1977 /
+                // 1519 / 1297 / 1192 / 1230, at 512 / 1024 3733 / 2449 / 1813 / 1479 / 1331.
+                // Beside the outputs of earlier pieces (below) at most half of the compute units go to the evolution (2 x 4096 tokens at
+                // 512 / 1024 1544 us with 5 helpers per stream in those pieces, 1463 with 7), and only if its chain is what the call
+                // waits for.
                 const int batches = (c->sparse_budget + 64) / (c->feat_dim == 256 ? 32 : 64);
-                if (wide && a.want_out && !a.dm.score_kind)
-                    helpers = std::max(0, std::min({batches / 6, SHARE_MAX_WGS / (int)ns - 1, SHARE_MAX_HELPERS}));
-                a.chunk_us = 12.f + 2.f * batches;
-                // Where nothing runs beside the launch (no overlap, or the first piece) the idle compute units are free: as many
-                // helpers as the batches keep busy.  us per call without helpers, with the count above, with this one: 4 x 2048
-                // tokens at 256 features, eta = lambda = 256 1079 / 907 / 825, 512 1241 / 875 / 842, eta 64 / lambda 128 912 / 813 / 771;
-                // 128 features, 128 / 192 668 / 668 / 598, 128 / 256 723 / 723 / 598; 4096 tokens at 256 / 256 1976 / 1530 / 1186, at
-                // 512 / 1024 3733 / 1560 / 1331.  (Four batches lose with 7: 620; 34 batches with 7 take 1479.)
-                int alone = 0;
+                int helpers = 0, alone = 0;   // beside outputs, and where nothing runs beside
                 if (wide && a.want_out && !a.dm.score_kind && ns <= SHARE_MAX_WGS / 2) {
-                    alone = batches < 3 ? 0 : (batches == 3 ? 1 : (batches == 4 ? 2 : (batches <= 6 ? 3 : (batches < 16 ? 7 : 15))));
-                    alone = std::min(alone, CHIP_CUS / (int)ns - 1);
+                    const int busy = batches < 3 ? 0 : (batches == 3 ? 1 : (batches == 4 ? 2 : (batches <= 6 ? 3 : (batches < 16 ? 7 : 15))));
+                    alone = std::min(busy, CHIP_CUS / (int)ns - 1);
+                    helpers = std::min(busy, SHARE_MAX_WGS / (int)ns - 1);
                 }
+                a.chunk_us = 12.f + 2.f * batches;
                 a.j_end = jend;
                 if (!wide && !big) {
                     const dim3 gp((unsigned)(jend - j0), (unsigned)ns);
