@@ -408,7 +408,9 @@ constexpr size_t OVERLAP_RESTART_WORK = 4096; // the same for the third piece an
 constexpr int SHARE_MAX_WGS = 128;            // evolution workgroups at most where helpers run beside outputs
 constexpr float SHARE_BESIDE = 1.2f;          // a piece beside outputs has helpers while its chain takes longer than this times the outputs:
                                               // they take compute units from the outputs (4 x 2048 tokens, 256 features, eta = lambda =
-                                              // 256 852 us without them in the second piece, 794 with; 512 958 and 759)
+                                              // 256 852 us without them in the second piece, 794 with; 512 958 and 759;
+                                              // with 0.95 the third piece has them too: 772 for 788 at 256, but 809 for 770 at
+                                              // eta 512, lambda 1024)
 
 // us of the whole chip per output workgroup of 64 queries of one head at the run-time shapes: key blocks of 128 and the rest.  By
 // kernel trace beside the evolution, scaled to the chip: 0.031 (2 blocks, 128 features), 0.063 (5, 256), 0.119 (13, 256) at

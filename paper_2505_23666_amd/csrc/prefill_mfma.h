@@ -2653,7 +2653,7 @@ __global__ __launch_bounds__(512) void step_update_wide_kernel(StepUpdateArgs a)
 // of 32 are dealt to several workgroups per stream.  A group takes 2.6 us with 256 features (1.9 above, where two tiles of 16 per
 // wavefront share every operand, so that many streams and large budgets stay there), the start 10 us, the fold 7.  Step at the 8B shape, 256
 // features, us before and after: eta = lambda = 256 47.7 -> 30.9 (batch 2), 48.7 -> 34.2 (4), 52.6 -> 43.3 (8); 512 49.2 -> 33.8,
-// 50.1 -> 40.2, 54.7 -> 51.4; 1024 51.0 -> 39.6, 52.7 -> 48.1, 62.0 -> 62.1.
+// 50.1 -> 40.2, 54.7 -> 48.5; 1024 51.0 -> 39.6, 52.7 -> 44.5, 62.0 -> 59.8.
 //
 // Scratch of a stream: the cached pairs' scores [0, lambda), the leaving pair's at lambda, then STEP_* words.
 constexpr int STEP_ARRIVED = 1, STEP_STEADY = 2;   // behind the leaving pair's score
