@@ -118,7 +118,7 @@ typedef struct {
      * bytes whose contents mean nothing between calls, never read before written, not touched by
      * lola_state_init.  With it, at the run-time-parameter shapes and with few streams
      * (batch * n_kv_heads <= 64 for the update, <= 128 at lambda >= 512; <= 85 for the outputs at window + lambda > 480), the
-     * step spreads a stream's work over several workgroups: the cached pairs' scores (equal to rounding), the fold of
+     * step spreads a stream's work over several workgroups: the cached pairs' scores and the fold of
      * the chosen pair (same bits as without it) and the outputs' sums over the keys (same result up to the order of the
      * fp32 sums).
      * Calls on states that share one scratch must not overlap. */

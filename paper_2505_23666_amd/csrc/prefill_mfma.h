@@ -2526,7 +2526,7 @@ __global__ __launch_bounds__(512) void step_update_wide_kernel(StepUpdateArgs a)
                 const float v4[4] = {bf_lo(vv[u].x), bf_hi(vv[u].x), bf_lo(vv[u].y), bf_hi(vv[u].y)};
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    const float err = (acc[u][i] + (acc2[u][i] + acc3[u][i])) * rd[u] - v4[i];
+                    const float err = fmaf(acc[u][i] + (acc2[u][i] + acc3[u][i]), rd[u], -v4[i]);
                     esum[u] = fmaf(err, err, esum[u]);
                 }
             }
@@ -2565,7 +2565,7 @@ __global__ __launch_bounds__(512) void step_update_wide_kernel(StepUpdateArgs a)
             float rec = 0.f;
 #pragma unroll
             for (int ks = 0; ks < KF; ks++) rec += partp[ks][tid];
-            err = rec * rdp_s - __uint_as_float((uint32_t)pvb[tid] << 16);
+            err = fmaf(rec, rdp_s, -__uint_as_float((uint32_t)pvb[tid] << 16));
         }
         err = wsum(err * err);
         if (lane == 0) errp[w] = err;
@@ -2649,26 +2649,34 @@ __global__ __launch_bounds__(512) void step_update_wide_kernel(StepUpdateArgs a)
 // above is bounded by is its compute unit's intake: every wavefront reads all of W_k (from L2) for its own candidates and all
 // of the split H^T (from LDS).  Here a wavefront owns 16 rows of H^T as operands in registers and 16 projections of W_k, and the
 // workgroup takes 32 candidates at a time: projections to LDS, features to LDS as bf16 high + low operands, recall of all 32
-// against the wavefront's rows, squared errors summed over the wavefronts.  Nothing is read twice by a workgroup, and the groups
-// of 32 are dealt to several workgroups per stream.  A group takes 2.6 us with 256 features (1.9 above, where two tiles of 16 per
+// against the wavefront's rows, errors to LDS and their squares summed per candidate.  Nothing is read twice by a workgroup, and the groups
+// of 32 are dealt to several workgroups per stream.  A group takes 2.9 us with 256 features (1.9 above, where two tiles of 16 per
 // wavefront share every operand, so that many streams and large budgets stay there), the start 10 us, the fold 7.  Step at the 8B shape, 256
-// features, us before and after: eta = lambda = 256 47.7 -> 30.9 (batch 2), 48.7 -> 34.2 (4), 52.6 -> 43.3 (8); 512 49.2 -> 33.8,
-// 50.1 -> 40.2, 54.7 -> 48.5; 1024 51.0 -> 39.6, 52.7 -> 44.5, 62.0 -> 59.8.
+// features, eta = 256, us before and after: lambda = 256 48.4 -> 32.0 (batch 2), 48.6 -> 34.7 (4), 53.2 -> 45.0 (8); 512 49.1 -> 34.8,
+// 50.3 -> 40.8, 54.5 -> 49.3; 1024 50.6 -> 40.5, 52.2 -> 45.7, 63.3 -> 62.4.
+// Which pair leaves must not depend on the form that a step takes (a shard of the streams, or a step without the scratch, takes
+// another one), so every sum behind a score is taken in the order of the form above.  Sums over all of a candidate's lanes at once
+// would be as exact and 2 % of a step faster (31.3, 34.2, 44.4; 34.0, 39.4, 48.7; 39.5, 44.3, 61.2), but decide near ties differently.
 //
 // Scratch of a stream: the cached pairs' scores [0, lambda), the leaving pair's at lambda, then STEP_* words.
 constexpr int STEP_ARRIVED = 1, STEP_STEADY = 2;   // behind the leaving pair's score
+
+using First = std::integral_constant<int, 0xA0>;    // quad permutations: the first lane of each pair to both,
+using Second = std::integral_constant<int, 0xF5>;   // the second
 
 template <int DH, int DF>
 __global__ __launch_bounds__(512) void step_score_kernel(StepUpdateArgs a) {
     constexpr int M = DF / 2, KS = DH / 32, NZT = M / 16, KF = DF / 32, NCT = DH / 16;
     constexpr int UZ = NZT == 8 ? 2 : 1;    // candidate tiles per wavefront in the projections (8 wavefronts: NZT tiles of W_k x 2 / UZ)
     constexpr int UR = NCT == 8 ? 2 : 1;    // ... and in the recall
-    constexpr int PL = M / 16, ZS = M + 4;  // projections per lane when features are made; row stride of the projections
+    constexpr int PL = M / 8, TL = PL / 4;  // projections per lane when features are made: four of each of TL tiles of 16
+    constexpr int ZP = M == 128 ? 16 : 0, ZS = M + ZP + 4, ES = DH + 4;   // pad behind 64 projections, row strides
     __shared__ __attribute__((aligned(16))) float s_l[DF];
     __shared__ __attribute__((aligned(16))) float zl[32 * ZS];                // projections of 32 candidates
+    __shared__ __attribute__((aligned(16))) float err_l[32 * ES];             // their errors per value column
     __shared__ __attribute__((aligned(16))) uint16_t ph[2][2][KF * 512];      // [tile][part][k-step][lane]: their features
     __shared__ __attribute__((aligned(16))) float zp[M];                      // projections of the leaving pair
-    __shared__ float rd_l[2][32], err_l[2][NCT][32], errp_l[DH], errp[2];
+    __shared__ float rd_l[32], errp_l[DH], errp[2];
 
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
     const int si = blockIdx.x, h = si % a.Hkv, LAM = a.lam, ETA = a.eta, part = blockIdx.y, nparts = a.nparts, ng = LAM / 32;
@@ -2746,7 +2754,7 @@ __global__ __launch_bounds__(512) void step_score_kernel(StepUpdateArgs a) {
             d0 = fmaf(hreg[ks][1].x, p[4], d0); d0 = fmaf(hreg[ks][1].y, p[5], d0); d0 = fmaf(hreg[ks][1].z, p[6], d0); d0 = fmaf(hreg[ks][1].w, p[7], d0);
             rec += grp_sum(d0);
         }
-        if (w < NCT && g4 == 0) errp_l[16 * ct + r16] = rec * rdp - pv;
+        if (w < NCT && g4 == 0) errp_l[16 * ct + r16] = fmaf(rec, rdp, -pv);
         lds_barrier();
         if (tid < 128) {
             float err = tid < DH ? errp_l[tid < DH ? tid : 0] : 0.f;
@@ -2765,89 +2773,117 @@ __global__ __launch_bounds__(512) void step_score_kernel(StepUpdateArgs a) {
         const float x8[8] = {hreg[ks][0].x, hreg[ks][0].y, hreg[ks][0].z, hreg[ks][0].w, hreg[ks][1].x, hreg[ks][1].y, hreg[ks][1].z, hreg[ks][1].w};
         split8(x8, Ah[ks], Al[ks]);
     }
-    // the sum of a group's squared errors over the row tiles, one group behind
-    auto finish = [&](int gi, int buf) {
-        if (tid < 32) {
-            float e = 0.f;
+    // the sum of a group's squared errors over the columns, one group behind: a candidate's four lanes add their columns up in
+    // the order of the row tiles
+    auto finish = [&](int gi) {
+        if (w >= 4 && w < 6) {   // (the wavefronts beside those that make features)
+            float es = 0.f;
 #pragma unroll
-            for (int c = 0; c < NCT; c++) e += err_l[buf][c][tid];
-            scr[32 * gi + tid] = sqrtf(e);
+            for (int c = 0; c < NCT; c++) {
+                const float4 e = *reinterpret_cast<const float4 *>(&err_l[(16 * (w & 1) + r16) * ES + 16 * c + 4 * g4]);
+                es = fmaf(e.x, e.x, es); es = fmaf(e.y, e.y, es); es = fmaf(e.z, e.z, es); es = fmaf(e.w, e.w, es);
+            }
+            es = grp_sum(es);
+            if (g4 == 0) scr[32 * gi + 16 * (w & 1) + r16] = sqrtf(es);
         }
     };
-    int buf = 0;
 #pragma unroll 1
-    for (int gi = part; gi < ng; gi += nparts, buf ^= 1) {
+    for (int gi = part; gi < ng; gi += nparts) {
         // projections: this wavefront's 16 rows of W_k
 #pragma unroll
         for (int u = 0; u < UZ; u++) {
             f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < KS; ks++) z = mfma16(W[ks], BK[u][ks], z);
-            *reinterpret_cast<f32x4 *>(&zl[(16 * (uz0 + u) + r16) * ZS + 16 * mz + 4 * g4]) = z;
+            *reinterpret_cast<f32x4 *>(&zl[(16 * (uz0 + u) + r16) * ZS + 16 * mz + (mz >= 4 ? ZP : 0) + 4 * g4]) = z;
         }
         uint2 vc[UR];
 #pragma unroll
         for (int u = 0; u < UR; u++) vc[u] = vv[u];
         if (gi + nparts < ng) load_group(gi + nparts);
         lds_barrier();
-        if (gi != part) finish(gi - nparts, buf ^ 1);
-        {   // features: sixteen lanes per candidate, PL projections each
-            const int c = 4 * w + g4, q = r16;
-            float z[PL];
+        if (gi != part) finish(gi - nparts);
+        if (w < 4) {
+            // Features: eight lanes per candidate on four wavefronts.  Lanes 2 g and 2 g + 1 share what lane group g has in the tile form
+            // (projections 16 mt + 4 g + 0..3, half of the tiles each); a sum over a lane group's projections goes through
+            // the first lane and on through the second, every addition in the order of the tile form.
+            const int c = 8 * w + (lane >> 3), g = (lane >> 1) & 3, mt0 = TL * (lane & 1);
+            float p[PL], n[PL];
+            {
+                float z[PL], cp = 0.f, cn = 0.f;
 #pragma unroll
-            for (int x = 0; x < PL; x += 4) {
-                const float4 t = *reinterpret_cast<const float4 *>(&zl[c * ZS + PL * q + x]);
-                z[x] = t.x; z[x + 1] = t.y; z[x + 2] = t.z; z[x + 3] = t.w;
+                for (int t = 0; t < TL; t++) {
+                    const float4 z4 = *reinterpret_cast<const float4 *>(&zl[c * ZS + 16 * (mt0 + t) + (mt0 >= 4 ? ZP : 0) + 4 * g]);
+                    z[4 * t] = z4.x; z[4 * t + 1] = z4.y; z[4 * t + 2] = z4.z; z[4 * t + 3] = z4.w;
+                }
+                if (a.phi_kind != 1) {
+                    float zmax = z[0], zmin = z[0];
+#pragma unroll
+                    for (int x = 1; x < PL; x++) { zmax = fmaxf(zmax, z[x]); zmin = fminf(zmin, z[x]); }
+                    zmax = fmaxf(zmax, dpp_f<0xB1>(zmax)); zmax = fmaxf(zmax, dpp_f<0x4E>(zmax)); zmax = fmaxf(zmax, dpp_f<0x141>(zmax));
+                    zmin = fminf(zmin, dpp_f<0xB1>(zmin)); zmin = fminf(zmin, dpp_f<0x4E>(zmin)); zmin = fminf(zmin, dpp_f<0x141>(zmin));
+                    cp = -zmax * LOG2E; cn = zmin * LOG2E;
+                }
+#pragma unroll
+                for (int x = 0; x < PL; x++) { p[x] = fexp2(fmaf(z[x], LOG2E, cp)); n[x] = fexp2(fmaf(z[x], -LOG2E, cn)); }
             }
-            float cp = 0.f, cn = 0.f;
+            auto group_sum = [&](float v) { v += dpp_f<0x4E>(v); v += dpp_f<0x141>(v); return v; };   // (as grp_sum: 0 + 1, 2 + 3, then both)
             if (a.phi_kind != 1) {
-                float zmax = z[0], zmin = z[0];
+                float sp = 0.f, sn = 0.f;
+                auto turn = [&](auto quad) {   // one lane's part of the sums, handed to both
 #pragma unroll
-                for (int x = 1; x < PL; x++) { zmax = fmaxf(zmax, z[x]); zmin = fminf(zmin, z[x]); }
-                zmax = fmaxf(zmax, dpp_f<0xB1>(zmax)); zmax = fmaxf(zmax, dpp_f<0x4E>(zmax)); zmax = fmaxf(zmax, dpp_f<0x141>(zmax)); zmax = fmaxf(zmax, dpp_f<0x140>(zmax));
-                zmin = fminf(zmin, dpp_f<0xB1>(zmin)); zmin = fminf(zmin, dpp_f<0x4E>(zmin)); zmin = fminf(zmin, dpp_f<0x141>(zmin)); zmin = fminf(zmin, dpp_f<0x140>(zmin));
-                cp = -zmax * LOG2E; cn = zmin * LOG2E;
-            }
-            float p[PL], n[PL], sp = 0.f, sn = 0.f, dp = 0.f, dm = 0.f;
+                    for (int x = 0; x < PL; x++) { sp += p[x]; sn += n[x]; }
+                    sp = dpp_f<decltype(quad)::value>(sp); sn = dpp_f<decltype(quad)::value>(sn);
+                };
+                turn(First{}); turn(Second{});
+                const float ip = frcp(group_sum(sp)), in_ = frcp(group_sum(sn));
 #pragma unroll
-            for (int x = 0; x < PL; x++) {
-                p[x] = fexp2(fmaf(z[x], LOG2E, cp)); n[x] = fexp2(fmaf(z[x], -LOG2E, cn));
-                sp += p[x]; sn += n[x];
-                dp = fmaf(p[x], s_l[PL * q + x], dp); dm = fmaf(n[x], s_l[M + PL * q + x], dm);
+                for (int x = 0; x < PL; x++) { p[x] *= ip; n[x] *= in_; }
             }
-            auto row_sum = [&](float v) { v += dpp_f<0xB1>(v); v += dpp_f<0x4E>(v); v += dpp_f<0x141>(v); v += dpp_f<0x140>(v); return v; };
-            float ip = 1.f, in_ = 1.f;
-            if (a.phi_kind != 1) { ip = frcp(row_sum(sp)); in_ = frcp(row_sum(sn)); }
-            const float dn = row_sum(fmaf(dp, ip, dm * in_));
-            if (q == 0) rd_l[buf][c] = dn > 0.f ? 1.0f / dn : 0.f;   // recall = 0 while nothing was folded
+            float dn = 0.f;
+            auto turn = [&](auto quad) {
+#pragma unroll
+                for (int t = 0; t < TL; t++) {
+                    const float4 sp4 = *reinterpret_cast<const float4 *>(&s_l[16 * (mt0 + t) + 4 * g]);
+                    const float4 sn4 = *reinterpret_cast<const float4 *>(&s_l[M + 16 * (mt0 + t) + 4 * g]);
+                    dn = fmaf(p[4 * t], sp4.x, dn); dn = fmaf(p[4 * t + 1], sp4.y, dn);
+                    dn = fmaf(p[4 * t + 2], sp4.z, dn); dn = fmaf(p[4 * t + 3], sp4.w, dn);
+                    dn = fmaf(n[4 * t], sn4.x, dn); dn = fmaf(n[4 * t + 1], sn4.y, dn);
+                    dn = fmaf(n[4 * t + 2], sn4.z, dn); dn = fmaf(n[4 * t + 3], sn4.w, dn);
+                }
+                dn = dpp_f<decltype(quad)::value>(dn);
+            };
+            turn(First{}); turn(Second{});
+            dn = group_sum(dn);
+            if ((lane & 7) == 0) rd_l[c] = dn > 0.f ? 1.0f / dn : 0.f;   // recall = 0 while nothing was folded
+            // Tiles 2 ks and 2 ks + 1 are the two halves of a lane group's operand of k-step ks; the candidate's place XOR-swizzled by
+            // k-step and lane group, which spreads these stores over the banks.
 #pragma unroll
             for (int sg_ = 0; sg_ < 2; sg_++)
 #pragma unroll
-                for (int x = 0; x < PL; x += 4) {
-                    // quad of features f .. f + 3: k-step f / 32, its half (f % 32) / 16, lane group (f % 16) / 4; the candidate's place
-                    // XOR-swizzled by the k-step, which spreads these stores over the banks
-                    const int f = PL * q + x + (sg_ ? M : 0), off = ((f >> 5) * 64 + 16 * ((f & 15) >> 2) + ((c & 15) ^ (((f >> 5) & 3) << 2))) * 8 + 4 * ((f >> 4) & 1);
-                    uint32_t hb[2], lb[2];
+                for (int t = 0; t < TL; t += 2) {
+                    const int ks = (mt0 + t) / 2 + (sg_ ? M / 32 : 0), off = (ks * 64 + 16 * g + ((c & 15) ^ ((ks & 3) << 2) ^ g)) * 8;
+                    uint32_t hb[4], lb[4];
 #pragma unroll
-                    for (int y = 0; y < 2; y++) {
-                        const f32x2 v = {(sg_ ? n[x + 2 * y] * in_ : p[x + 2 * y] * ip), (sg_ ? n[x + 2 * y + 1] * in_ : p[x + 2 * y + 1] * ip)};
+                    for (int y = 0; y < 4; y++) {
+                        const f32x2 v = {sg_ ? n[4 * t + 2 * y] : p[4 * t + 2 * y], sg_ ? n[4 * t + 2 * y + 1] : p[4 * t + 2 * y + 1]};
                         hb[y] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
                         const f32x2 r = {v[0] - __uint_as_float(hb[y] << 16), v[1] - __uint_as_float(hb[y] & 0xFFFF0000u)};
                         lb[y] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
                     }
-                    *reinterpret_cast<uint2 *>(&ph[c >> 4][0][off]) = make_uint2(hb[0], hb[1]);
-                    *reinterpret_cast<uint2 *>(&ph[c >> 4][1][off]) = make_uint2(lb[0], lb[1]);
+                    *reinterpret_cast<uint4 *>(&ph[c >> 4][0][off]) = make_uint4(hb[0], hb[1], hb[2], hb[3]);
+                    *reinterpret_cast<uint4 *>(&ph[c >> 4][1][off]) = make_uint4(lb[0], lb[1], lb[2], lb[3]);
                 }
         }
         lds_barrier();
-        // recall of this wavefront's rows, squared errors against the values (the operands of four k-steps are read while the four
+        // recall of this wavefront's rows, its errors against the values (the operands of four k-steps are read while the four
         // before them are multiplied: left to itself the compiler reads each just before its use)
         bf16x8 B[2][8];
         auto read_ops = [&](int x) {   // x: four k-steps of a tile
             const int u = x / (KF / 4), ks0 = x % (KF / 4) * 4;
 #pragma unroll
             for (int y = 0; y < 4; y++) {
-                const int off = ((ks0 + y) * 64 + (lane ^ (y << 2))) * 8;
+                const int off = ((ks0 + y) * 64 + (lane ^ ((y << 2) | g4))) * 8;
                 B[x & 1][y] = as_bf16x8(*reinterpret_cast<const uint4 *>(&ph[ur0 + u][0][off]));
                 B[x & 1][4 + y] = as_bf16x8(*reinterpret_cast<const uint4 *>(&ph[ur0 + u][1][off]));
             }
@@ -2869,20 +2905,16 @@ __global__ __launch_bounds__(512) void step_score_kernel(StepUpdateArgs a) {
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            const float rd = rd_l[buf][16 * (ur0 + u) + r16];
+            const float rd = rd_l[16 * (ur0 + u) + r16];
             const float v4[4] = {bf_lo(vc[u].x), bf_hi(vc[u].x), bf_lo(vc[u].y), bf_hi(vc[u].y)};
-            float es = 0.f;
+            f32x4 err;
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const float err = (acc[i] + (acc2[i] + acc3[i])) * rd - v4[i];
-                es = fmaf(err, err, es);
-            }
-            es = grp_sum(es);
-            if (g4 == 0) err_l[buf][ct][16 * (ur0 + u) + r16] = es;
+            for (int i = 0; i < 4; i++) err[i] = fmaf(acc[i] + (acc2[i] + acc3[i]), rd, -v4[i]);
+            *reinterpret_cast<f32x4 *>(&err_l[(16 * (ur0 + u) + r16) * ES + 16 * ct + 4 * g4]) = err;
         }
     }
     lds_barrier();
-    if (part < ng) finish(part + (ng - 1 - part) / nparts * nparts, buf ^ 1);
+    if (part < ng) finish(part + (ng - 1 - part) / nparts * nparts);
 }
 
 // What follows the scores: arg-min (ties: the larger token index goes), phi of the folded pair, rank-1 fold, slot and ring

@@ -379,3 +379,31 @@ def test_generation_step_in_groups_of_candidates(B, Hkv, d, D, eta, lam, kw):
         assert torch.allclose(outs[0], outs[1], rtol=1e-5, atol=2e-6), i
         for nm in FIELDS:
             assert torch.equal(getattr(lays[0], nm), getattr(lays[1], nm)), (i, nm)
+
+
+@pytest.mark.parametrize("B,Hkv,d,D,eta,lam,kw", [(1, 2, 128, 256, 65, 256, {}), (3, 1, 64, 128, 100, 192, {}), (8, 8, 128, 128, 30, 256, {}), (4, 4, 64, 256, 128, 320, {}),
+                                                 (2, 4, 128, 256, 64, 512, dict(phi_kind=1)), (16, 4, 128, 128, 128, 64, {}), (9, 8, 128, 256, 64, 512, {})])
+def test_generation_step_ranks_ties_alike_with_the_scratch(B, Hkv, d, D, eta, lam, kw):
+    """Which pair leaves does not depend on whether the step has the scratch, also where the scores are equal up to their last
+    bits: every value is a permutation of one vector, H and s hold one number each, so that the recalls of all pairs are the same
+    number and the scores differ by the rounding of their sums alone.  Every memory equal bit for bit at every step."""
+    Hq = 2 * Hkv
+    sh = wl.Shape("ties", "bf16", B, Hq, Hkv, d, D, T=0, eta=eta, lam=lam, C=64, seed=0)
+    T, nd = eta + lam + 70, 12
+    q, k, v, Wq, Wk = case_inputs(700 + d + D + lam, B, Hq, Hkv, d, D, T + nd, wscale=0.5 if kw.get("phi_kind") else 1.0)
+    v = wl.rng(d + lam, 11).permuted(np.broadcast_to(v[:1, :1, :1], v.shape), axis=-1)
+    dWq, dWk = P.w_to_dev(Wq, "bf16"), P.w_to_dev(Wk, "bf16")
+    print("ties", B, Hkv, d, D, eta, lam, kw, flush=True)
+    lays = [P.make_layer(sh, step_scratch=x, **kw) for x in (True, False)]
+    lays[1].prefill(None, P.to_dev(np.ascontiguousarray(k[:, :, :T]), "bf16"), P.to_dev(np.ascontiguousarray(v[:, :, :T]), "bf16"), None, dWk)
+    for nm in FIELDS:
+        getattr(lays[0], nm).copy_(getattr(lays[1], nm))
+    for i in range(nd):
+        sq, sk, sv = (P.to_dev(np.ascontiguousarray(x[:, :, T + i]), "bf16") for x in (q, k, v))
+        for lay in lays:
+            lay.H.fill_(0.37)
+            lay.s.fill_(0.53)
+            lay.decode_step(sq, sk, sv, dWq, dWk)
+        torch.cuda.synchronize()
+        for nm in FIELDS:
+            assert torch.equal(getattr(lays[0], nm), getattr(lays[1], nm)), (i, nm)
