@@ -117,7 +117,8 @@ typedef struct {
      * given with LOLA_SCORE_SRE too: it is then scratch of lola_decode_step, lola_step_scratch_bytes(cfg)
      * bytes whose contents mean nothing between calls, never read before written, not touched by
      * lola_state_init.  With it, at the run-time-parameter shapes and with few streams
-     * (batch * n_kv_heads <= 64 for the update, <= 128 at lambda >= 512; <= 85 for the outputs at window + lambda > 480), the
+     * (batch * n_kv_heads <= 64 for the update, at head_dim 64 up to a number of pairs, <= 128 at lambda >= 512; <= 85 for the
+     * outputs at window + lambda > 480), the
      * step spreads a stream's work over several workgroups: the cached pairs' scores and the fold of
      * the chosen pair (same bits as without it) and the outputs' sums over the keys (same result up to the order of the
      * fp32 sums).

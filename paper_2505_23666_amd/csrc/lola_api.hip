@@ -304,22 +304,30 @@ lola_status run_decode(const lola_config *c, const lola_state *st, const void *q
             ua.Hkv = a.dm.Hkv; ua.lam = a.dm.lam; ua.eta = a.dm.eta; ua.phi_kind = a.dm.phi_kind;
             ua.scr_stride = (int)step_scratch_floats(c);
             // At most 64 streams (and the scratch for the scores, sp_score, which a self-recall-error state may carry): groups
-            // of 32 candidates dealt to several workgroups per stream, then arg-min and fold, the rows of H^T dealt likewise.  128
-            // workgroups read the state less often than 256 would and are faster up to 4 groups each (eta = lambda = 256, batch 4:
-            // 34.2 us a step against 39.3; eta 512, lambda 1024: 51.5 against 48.1 with 8 groups each); the leaving pair has a
-            // workgroup of its own where one is left.
-            const int ns = a.dm.B * a.dm.Hkv, npass = a.dm.lam / 256, ngroups = a.dm.lam / 32;
-            // (At head_dim 64 the kernel with one workgroup per stream has less to read: from 8 groups per workgroup on it stays,
-            // 31.6 us against 32.8 at eta 64, lambda 1024, batch 8.)
-            const bool split = !a.dm.score_kind && st->sp_score && ns <= 64 && (c->head_dim == 128 || ngroups * ns <= 6 * CHIP_CUS);
-            ua.nparts = std::max(1, std::min(ngroups, CHIP_CUS / 2 / ns));
-            if (ngroups > 4 * ua.nparts) ua.nparts = std::min(ngroups, CHIP_CUS / ns);
+            // of 32 candidates dealt to several workgroups per stream, then arg-min and fold, the rows of H^T dealt likewise.  The
+            // leaving pair has a workgroup of its own where one is left; where every group would have one and the leaving pair none,
+            // two groups share one (eta = lambda = 256, 256 features, batch 4: 34.9 us a step against 35.8; more groups each are
+            // slower: lambda = 512 40.6 with four, 39.1 with two; 1024 52.5 with eight, 45.8 with four).
+            const int ns = a.dm.B * a.dm.Hkv, npass = a.dm.lam / 256, ngroups = a.dm.lam / 32, work = ngroups * ns;
+            const bool spread = !a.dm.score_kind && st->sp_score;
+            // At head_dim 64 the kernel with one workgroup per stream has less to read.  Where the compute units suffice for one tile of
+            // 16 pairs per wavefront (lambda / 128 workgroups per stream) its score part on single tiles is faster from 3 groups per
+            // compute unit on: lambda = 512, 64 streams, 128 features 25.2 us a step against 27.0, 256 features 35.0 against 36.5; 1024, 32
+            // streams 27.4 against 28.2 and 34.5 against 35.5; but 1024, 24 streams 26.0 against 25.7.
+            const bool single = spread && c->head_dim == 64 && ns >= 32 && ns <= 64 && a.dm.lam >= 512 && a.dm.lam % 128 == 0 &&
+                                work >= 3 * CHIP_CUS && work <= 4 * CHIP_CUS;
+            // Beyond, the pairs of tiles: at head_dim 64 from 6 groups per compute unit on (lambda = 1024, 48 streams 30.1 against 30.7; but
+            // 2048, 24 streams 32.8 against 31.9), at 128 from 16 on (2048, 64 streams, 256 features 88 against 93; 48 streams 84 against 78).
+            const bool split = spread && !single && ns <= 64 && (c->head_dim == 128 ? work < 16 * CHIP_CUS : work <= (ns <= 32 ? 6 : 5) * CHIP_CUS);
+            ua.nparts = std::max(1, std::min(ngroups, CHIP_CUS / ns));   // (more than CHIP_CUS streams: not used)
+            if (ua.nparts == ngroups && ns * (ngroups + 1) > CHIP_CUS) ua.nparts = (ngroups + 1) / 2;
             const dim3 grids(ns, ua.nparts + (ns * (ua.nparts + 1) <= CHIP_CUS ? 1 : 0));
             const int fp = ns <= 32 ? 8 : 4;   // parts of H^T in the fold
             // Up to 128 streams and several passes over the cached pairs: the scoring is split over two workgroups per stream, a
             // second launch does the rest (batch 16 at lambda = 512: 69.5 us a step, 78.5 in one launch, 72.9 as above).
             int parts = 1;
-            if (!a.dm.score_kind && st->sp_score && npass >= 2 && 2 * ns <= CHIP_CUS) parts = std::min(npass, CHIP_CUS / ns);
+            if (single) parts = a.dm.lam / 128;
+            else if (spread && npass >= 2 && 2 * ns <= CHIP_CUS) parts = std::min(npass, CHIP_CUS / ns);
             const dim3 grid1(ns, parts);
 #define LOLA_FOLD(DHV, DFV, FPV) hipLaunchKernelGGL((fast::step_fold_kernel<DHV, DFV, FPV>), dim3(ns, FPV), dim3(512), 0, stream, ua)
 #define LOLA_UPD(DHV, DFV) do { if (a.dm.score_kind) hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, true>), grid, dim3(512), 0, stream, ua); \
@@ -327,7 +335,8 @@ lola_status run_decode(const lola_config *c, const lola_state *st, const void *q
                                     hipLaunchKernelGGL((fast::step_score_kernel<DHV, DFV>), grids, dim3(512), 0, stream, ua); \
                                     if (fp == 8 && DHV * DFV > 64 * 128) LOLA_FOLD(DHV, DFV, (DHV * DFV > 64 * 128 ? 8 : 4)); else LOLA_FOLD(DHV, DFV, 4); \
                                 } else if (parts == 1) hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, false>), grid, dim3(512), 0, stream, ua); \
-                                else { hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, false, 1>), grid1, dim3(512), 0, stream, ua); \
+                                else { if (DHV == 64 && single) hipLaunchKernelGGL((fast::step_update_wide_kernel<64, DFV, false, 1, 1>), grid1, dim3(512), 0, stream, ua); \
+                                       else hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, false, 1>), grid1, dim3(512), 0, stream, ua); \
                                        hipLaunchKernelGGL((fast::step_update_wide_kernel<DHV, DFV, false, 2>), grid, dim3(512), 0, stream, ua); } } while (0)
             if (c->head_dim == 128) { if (c->feat_dim == 256) LOLA_UPD(128, 256); else LOLA_UPD(128, 128); }
             else { if (c->feat_dim == 256) LOLA_UPD(64, 256); else LOLA_UPD(64, 128); }

@@ -2260,11 +2260,14 @@ __device__ __forceinline__ void fill_step(const StepUpdateArgs &a, int si, int64
 // split off: MODE 1 = grid (streams, parts), workgroup (stream, part) scores the passes part, part + parts, ... into
 // sp_score (scratch in this mode) and changes nothing else; MODE 2 = one workgroup per stream reads those scores and does
 // the rest (the leaving pair's score, steps 3 and 4).  The scores are computed by the same instructions in either form.
-template <int DH, int DF, bool SCORED, int MODE = 0>
+// NTP: tiles of 16 candidates a wavefront takes per pass (2: the operands of H^T and W_k serve both; 1 for the score
+// part where there are compute units enough to give every wavefront a single tile).
+template <int DH, int DF, bool SCORED, int MODE = 0, int NTP = 2>
 __global__ __launch_bounds__(512) void step_update_wide_kernel(StepUpdateArgs a) {
     static_assert(MODE == 0 || !SCORED, "the split forms score by self-recall error");
+    static_assert(NTP == 2 || (NTP == 1 && MODE == 1), "single tiles: score part only");
     constexpr int M = DF / 2, KS = DH / 32, NZT = M / 16, KF = DF / 32, NCT = DH / 16, NP = NCT * KF / 8, PR = DH / 8;
-    constexpr int LAMMAX = STEP_UPDATE_LAMMAX, NTP = 2;   // tiles of 16 candidates per pass: the operands of H^T and W_k serve both
+    constexpr int LAMMAX = STEP_UPDATE_LAMMAX;
     __shared__ __attribute__((aligned(16))) uint4 HA[NCT * KF * 2 * 64];     // [row tile][k-step][part][lane]
     __shared__ __attribute__((aligned(16))) float s_l[DF];
     __shared__ __attribute__((aligned(16))) float phif[DF];                  // phi of the folded pair

@@ -382,7 +382,7 @@ def test_generation_step_in_groups_of_candidates(B, Hkv, d, D, eta, lam, kw):
 
 
 @pytest.mark.parametrize("B,Hkv,d,D,eta,lam,kw", [(1, 2, 128, 256, 65, 256, {}), (3, 1, 64, 128, 100, 192, {}), (8, 8, 128, 128, 30, 256, {}), (4, 4, 64, 256, 128, 320, {}),
-                                                 (2, 4, 128, 256, 64, 512, dict(phi_kind=1)), (16, 4, 128, 128, 128, 64, {}), (9, 8, 128, 256, 64, 512, {})])
+                                                 (2, 4, 128, 256, 64, 512, dict(phi_kind=1)), (16, 4, 128, 128, 128, 64, {}), (9, 8, 128, 256, 64, 512, {}), (8, 8, 64, 128, 64, 512, {}), (4, 8, 64, 256, 64, 1024, {})])
 def test_generation_step_ranks_ties_alike_with_the_scratch(B, Hkv, d, D, eta, lam, kw):
     """Which pair leaves does not depend on whether the step has the scratch, also where the scores are equal up to their last
     bits: every value is a permutation of one vector, H and s hold one number each, so that the recalls of all pairs are the same
