@@ -488,15 +488,21 @@ void launch_output_kernel(const lola_config *c, const generic::PrefillArgs<bf16_
     // for the group: 441 against 467 at eta 512 / lambda 1024).
     const int nch = r1 - r0, G = c->feat_dim == 256 && a.dm.g % 4 == 0 ? 4 : (a.dm.g % 2 == 0 ? 2 : 1);
     const bool f32o = c->out_dtype == LOLA_F32;
-    // streams (and groups of G query heads) run fastest, so that a stream's chunks meet in one XCD's L2
-    const int groups = a.dm.B * a.dm.Hkv * (a.dm.g / G);
-    const int ny = std::min(nch, 32768);
-    const dim3 ga((unsigned)groups, (unsigned)ny, (unsigned)((nch + ny - 1) / ny));
+    // streams (and groups of G query heads) run fastest, so that a stream's chunks meet in one XCD's L2; a dimension of a grid has
+    // less than 2^32 threads
+    const int ns = a.dm.B * a.dm.Hkv, ngr = a.dm.g / G, ny = std::min(nch, 32768);
+    const int per_launch = std::min(ngr, (int)(0xFFFFFFFFu / (128u * (unsigned)G) / (unsigned)ns));
+    for (int g0 = 0; g0 < ngr; g0 += per_launch) {
+        ao.q = a.q + (size_t)g0 * G * a.T_tokens * a.dm.d;
+        ao.Wq = a.Wq + (size_t)g0 * G * a.dm.m * a.dm.d;
+        ao.out = (char *)a.out + (size_t)g0 * G * a.T_tokens * a.dm.d * (f32o ? 4 : 2);
+        const dim3 ga((unsigned)(ns * std::min(per_launch, ngr - g0)), (unsigned)ny, (unsigned)((nch + ny - 1) / ny));
 #define LOLA_ATT2(DHV, DFV, GV) do { if (f32o) hipLaunchKernelGGL((fast::attend_group_kernel<DHV, DFV, GV, float>), ga, dim3(fast::AttendShape<DHV, DFV, GV>::NTHR), (fast::AttendShape<DHV, DFV, GV>::lds(c->sparse_budget)), so, ao); \
-                                     else hipLaunchKernelGGL((fast::attend_group_kernel<DHV, DFV, GV, bf16_t>), ga, dim3(fast::AttendShape<DHV, DFV, GV>::NTHR), (fast::AttendShape<DHV, DFV, GV>::lds(c->sparse_budget)), so, ao); } while (0)
+                                         else hipLaunchKernelGGL((fast::attend_group_kernel<DHV, DFV, GV, bf16_t>), ga, dim3(fast::AttendShape<DHV, DFV, GV>::NTHR), (fast::AttendShape<DHV, DFV, GV>::lds(c->sparse_budget)), so, ao); } while (0)
 #define LOLA_ATT(DHV, DFV) do { if (DFV == 256 && G == 4) LOLA_ATT2(DHV, 256, 4); else if (G == 2) LOLA_ATT2(DHV, DFV, 2); else LOLA_ATT2(DHV, DFV, 1); } while (0)
-    if (c->head_dim == 128) { if (c->feat_dim == 256) LOLA_ATT(128, 256); else LOLA_ATT(128, 128); }
-    else { if (c->feat_dim == 256) LOLA_ATT(64, 256); else LOLA_ATT(64, 128); }
+        if (c->head_dim == 128) { if (c->feat_dim == 256) LOLA_ATT(128, 256); else LOLA_ATT(128, 128); }
+        else { if (c->feat_dim == 256) LOLA_ATT(64, 256); else LOLA_ATT(64, 128); }
+    }
 #undef LOLA_ATT
 #undef LOLA_ATT2
 }

@@ -407,3 +407,27 @@ def test_generation_step_ranks_ties_alike_with_the_scratch(B, Hkv, d, D, eta, la
         torch.cuda.synchronize()
         for nm in FIELDS:
             assert torch.equal(getattr(lays[0], nm), getattr(lays[1], nm)), (i, nm)
+
+
+def test_outputs_of_more_heads_than_a_grid_has_threads():
+    """65 535 sequences of 513 query heads on one memory each: with one workgroup per head and chunk in the grid's first dimension
+    it would pass 2^32 threads, more than a launch takes.  The first, a middle and the last sequence against layers of their own."""
+    from paper_2505_23666_amd import binding as lb
+    B, Hq, d, D = 65535, 513, 64, 128
+    torch.cuda.empty_cache()
+    g = torch.Generator(device=P.DEV).manual_seed(8)
+    mk = lambda *shape: torch.randn(shape, generator=g, device=P.DEV, dtype=torch.bfloat16)
+    q, k, v, Wq, Wk = mk(B, Hq, 1, d), mk(B, 1, 1, d), mk(B, 1, 1, d), mk(Hq, D // 2, d) / 8, mk(1, D // 2, d) / 8
+    lay = lb.LolaLayer(B, Hq, 1, d, D, 0, 0, 64, out_dtype="bf16")
+    assert lay.lola_path[0] == "mixed"
+    H, s = torch.randn((d, D), generator=g, device=P.DEV), torch.rand((D,), generator=g, device=P.DEV)
+    lay.H.copy_(H), lay.s.copy_(s)
+    out = lay.prefill(q, k, v, Wq, Wk)
+    torch.cuda.synchronize()
+    for b in (0, 40000, B - 1):
+        one = lb.LolaLayer(1, Hq, 1, d, D, 0, 0, 64, out_dtype="bf16")
+        one.H.copy_(H), one.s.copy_(s)
+        want = one.prefill(*(x[b:b + 1].contiguous() for x in (q, k, v)), Wq, Wk)
+        assert float(want.float().std()) > 0 and torch.equal(out[b], want[0]), b
+    del q, out, lay
+    torch.cuda.empty_cache()
