@@ -62,8 +62,9 @@ struct AttendShape {
     static constexpr int FS = SB / (4 * DH), NHS = DF / FS;   // features per H^T stage (all rows, high + low parts)
     static constexpr int FC = 32;                          // features whose B operands are held at a time
     static constexpr int PR = DH / 8, RPI = 64 / PR;       // 16-byte pieces per row, rows per direct load
-    // bytes of LDS: two slots, s, the cache's rows (LR: lambda in whole wavefronts) and their addresses
-    static constexpr int LR(int lam) { return (lam + 63) / 64 * 64; }
+    // bytes of LDS: two slots, s, the cache's rows (LR: lambda in whole wavefronts, one at least: positions below the first key
+    // look at row 0, also without a cache) and their addresses
+    static constexpr int LR(int lam) { return lam < 64 ? 64 : (lam + 63) / 64 * 64; }
     static constexpr int lds(int lam) { return 2 * SB + DF * 4 + LR(lam) * (4 + 16); }
 };
 
@@ -72,6 +73,7 @@ __global__ __launch_bounds__((AttendShape<DH, DF, G>::NTHR), 2) void attend_grou
     using S = AttendShape<DH, DF, G>;
     constexpr int M = S::M, NI = S::NI, PR = S::PR, KS = DH / 16, NCT = DH / 32;
     static_assert((DH == 64 || DH == 128) && (DF == 128 || DF == 256), "shape");
+    static_assert(S::LR(0) > 0, "row 0 exists");
     static_assert(DF % S::FS == 0 && S::FS % S::FC == 0 && M % S::FC == 0 && S::NI >= 2 && (S::NWS == 1 || S::NWS * S::PW == M), "stages");
     extern __shared__ __attribute__((aligned(1024))) unsigned char ring[];
     __shared__ int gneg_l;   // the chunk's cache has an empty slot
