@@ -49,13 +49,13 @@ bool wide_decode_ok(const lola_config *c) {
     return wide_step_out_ok(c) && c->sparse_budget >= 64 && c->sparse_budget % 64 == 0 && c->sparse_budget <= fast::STEP_UPDATE_LAMMAX;
 }
 
-// Floats per stream of the generation step's optional scratch: the cached pairs' scores, later the output kernel's
-// shares (both launches of a step use it one after the other).
+// Floats per stream of the generation step's optional scratch: the cached pairs' scores and the words behind them, later the
+// output kernel's shares (the launches of a step use it one after the other).
 size_t step_scratch_floats(const lola_config *c) {
     if (c->score_kind != LOLA_SCORE_SRE || !wide_step_out_ok(c)) return 0;
     const int G = c->n_q_heads / c->n_kv_heads <= 4 ? 4 : 8;
     const size_t shares = (size_t)fast::STEP_OUT_PARTS_MAX * (G * c->head_dim + 2 * G);
-    return std::max(shares, (size_t)c->sparse_budget);
+    return std::max(shares, (size_t)c->sparse_budget + fast::STEP_WORDS);
 }
 
 lola_status check_config(const lola_config *c) {

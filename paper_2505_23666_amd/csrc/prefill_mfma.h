@@ -2661,8 +2661,8 @@ __global__ __launch_bounds__(512) void step_update_wide_kernel(StepUpdateArgs a)
 // another one), so every sum behind a score is taken in the order of the form above.  Sums over all of a candidate's lanes at once
 // would be as exact and 2 % of a step faster (31.3, 34.2, 44.4; 34.0, 39.4, 48.7; 39.5, 44.3, 61.2), but decide near ties differently.
 //
-// Scratch of a stream: the cached pairs' scores [0, lambda), the leaving pair's at lambda, then STEP_* words.
-constexpr int STEP_ARRIVED = 1, STEP_STEADY = 2;   // behind the leaving pair's score
+// Scratch of a stream: the cached pairs' scores [0, lambda), then STEP_WORDS words: the leaving pair's score and what follows.
+constexpr int STEP_ARRIVED = 1, STEP_STEADY = 2, STEP_WORDS = 3;
 
 using First = std::integral_constant<int, 0xA0>;    // quad permutations: the first lane of each pair to both,
 using Second = std::integral_constant<int, 0xF5>;   // the second
