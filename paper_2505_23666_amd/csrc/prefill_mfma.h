@@ -1485,7 +1485,7 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
         };
         int nown = NE;   // candidates [0, nown) are scored here, the others by helpers
         if constexpr (SHARED) {
-            // the first batches travel while the snapshot drains (lambda + 64 candidates are at least NBUF batches): 1.93 ->
+            // the first batches travel while the snapshot drains (the stream's own: helpers leave it NBUF - 1, below): 1.93 ->
             // 1.87 ms for 2 x 4096 tokens at eta 512 / lambda 1024, 1.01 -> 0.99 for 4 x 2048 at eta = lambda = 256
 #pragma unroll
             for (int b = 0; b < NBUF - 1; b++) wide_issue<DH, DF>(pool, b, b, tid, phirow, vrow);
@@ -1494,7 +1494,7 @@ __global__ __launch_bounds__(DH * 4) void scan_wide_kernel(generic::PrefillArgs<
             __syncthreads();                      // the snapshot and the last chunk's compaction are complete
             if (tid == 0) {
                 const int nh = agent_load(&sh->joined);
-                const int bh = max(1, (NBATCH - SHARE_LEAD + nh) / (nh + 1)), used = min(nh, (NBATCH - 1) / bh);
+                const int bh = max(1, (NBATCH - SHARE_LEAD + nh) / (nh + 1)), used = min(nh, (NBATCH - (NBUF - 1)) / bh);
                 if (used > 0) {
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
                     agent_store(&sh->go, ((unsigned long long)(j - a.jb + 1) << 16) | (unsigned long long)((nf < C ? 1 << 15 : 0) | (bh << 8) | used));

@@ -202,12 +202,16 @@ def test_helpers_beside_outputs(B, Hq, d, D, eta, lam, T, first, second):
 @pytest.mark.parametrize("B,Hkv,d,D,eta,lam,T,limit,kw", [
     (1, 1, 128, 256, 64, 1024, 1600, None, {}), (1, 3, 64, 256, 128, 512, 1111, None, {}), (4, 8, 128, 128, 64, 512, 2100, None, dict(prefill_overlap=1)),
     (4, 8, 128, 256, 64, 512, 960, None, {}), (1, 2, 64, 128, 64, 768, 1000, 0, {}), (2, 8, 128, 256, 64, 1024, 1537, 40 << 20, dict(phi_kind=1)),
-    (2, 8, 128, 256, 64, 1024, 4200, None, dict(prefill_overlap=1)), (4, 4, 128, 256, 128, 256, 4130, None, dict(prefill_overlap=1)), (2, 32, 128, 256, 64, 512, 800, None, {})])
+    (2, 8, 128, 256, 64, 1024, 4200, None, dict(prefill_overlap=1)), (4, 4, 128, 256, 128, 256, 4130, None, dict(prefill_overlap=1)), (2, 32, 128, 256, 64, 512, 800, None, {}),
+    (1, 8, 128, 128, 128, 128, 900, None, {}), (2, 3, 64, 128, 64, 192, 1010, None, {}), (1, 5, 128, 256, 64, 64, 700, None, {}), (3, 8, 64, 128, 128, 320, 1100, None, {}),
+    (1, 2, 128, 256, 192, 128, 1001, None, {}), (4, 8, 128, 256, 64, 192, 1100, None, {}), (2, 8, 64, 256, 64, 192, 900, None, dict(phi_kind=1)), (1, 8, 128, 256, 64, 448, 1300, None, {}), (2, 4, 64, 256, 128, 448, 1400, None, {})])
 def test_evolution_shared_among_workgroups(B, Hkv, d, D, eta, lam, T, limit, kw):
     """With outputs and few streams the candidates' scores come from several workgroups per stream; an update-only call
     stays on one. The same instructions on the same operands: the memories agree bit for bit, over several launches and
     workspace passes, a ragged last chunk and a second call that starts with a full cache.  With the outputs beside it the
-    evolution runs in pieces of its own, one or several helpers per stream in the first and the second."""
+    evolution runs in pieces of its own, one or several helpers per stream in the first and the second.  The stream's own
+    workgroup keeps the batches that it requests ahead (2 with 256 features, 1 with 128) also where there are as many helpers
+    as batches: 3, 4, 6, 8 and 16 batches."""
     sh = wl.Shape("shared", "bf16", B, 2 * Hkv, Hkv, d, D, T=0, eta=eta, lam=lam, C=64, seed=0)
     q, k, v, Wq, Wk = case_inputs(90 + d + D + lam, B, 2 * Hkv, Hkv, d, D, T + 130, wscale=0.5 if kw.get("phi_kind") else 1.0)
     dq, dk, dv, dWq, dWk = P.to_dev(q, "bf16"), P.to_dev(k, "bf16"), P.to_dev(v, "bf16"), P.w_to_dev(Wq, "bf16"), P.w_to_dev(Wk, "bf16")
@@ -221,6 +225,8 @@ def test_evolution_shared_among_workgroups(B, Hkv, d, D, eta, lam, T, limit, kw)
         print("   helpers", joined.max(1), "shares", done.max(1), flush=True)
         if limit is None:   # (a pass of one chunk may be over before a helper has joined)
             assert bool((joined[0] > 0).all()) and bool((done > 0).any(0).all())
+            scored = -(-T // 64) - (eta + lam) // 64 if a == 0 else -(-(b - a) // 64)   # chunks
+            assert int(done.sum(0).max()) <= scored * ((lam + 64) // (32 if D == 256 else 64) - (2 if D == 256 else 1))
         if kw.get("prefill_overlap") and a == 0:   # (the second call is too short for pieces)
             assert bool((joined[1] > 0).all()) and bool((done[1] > 0).all())
             apart = P.make_layer(sh)
