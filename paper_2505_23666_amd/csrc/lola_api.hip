@@ -191,19 +191,17 @@ lola_status decode_feasible(const lola_config *c) {
     return score_tile_rows(dm, decode_fixed_floats(dm), dm.score_kind != 0) > 0 ? LOLA_OK : LOLA_ERR_UNSUPPORTED;
 }
 
-// The MFMA kernels of the prefill cover the Llama 8B and 1B head shapes (head_dim 128 / 64, 128 features) with
-// chunk = window = 64.
-// shapes of the MFMA prefill kernels; the output kernel serves every score kind (its inputs are the snapshots, whoever
-// took them), the state-evolution kernel ranks by self-recall error only
-bool fast_output_ok(const lola_config *c) {
+// Shapes of the state-evolution kernels with compile-time window and sparse budget: the Llama 8B and 1B head shapes (head_dim
+// 128 / 64, 128 features) with chunk = window = 64; they rank by self-recall error only
+bool fast_shape(const lola_config *c) {
     return c->dtype == LOLA_BF16 && (c->head_dim == 128 || c->head_dim == 64) && c->feat_dim == 128 && c->window == 64 && c->chunk == 64 &&
            (c->sparse_budget == 0 || c->sparse_budget == 64 || c->sparse_budget == 128 || c->sparse_budget == 256);
 }
-bool fast_attend_ok(const lola_config *c) { return fast_output_ok(c) && c->score_kind == LOLA_SCORE_SRE; }
-// shapes of the MFMA output kernel with run-time window and sparse budget (any score kind: its inputs are the snapshots)
-bool wide_output_ok(const lola_config *c) {
+bool fast_attend_ok(const lola_config *c) { return fast_shape(c) && c->score_kind == LOLA_SCORE_SRE; }
+// shapes of the MFMA output kernel, those above among them (any score kind: its inputs are the snapshots, whoever took them)
+bool mfma_output_ok(const lola_config *c) {
     return c->dtype == LOLA_BF16 && (c->head_dim == 128 || c->head_dim == 64) && (c->feat_dim == 128 || c->feat_dim == 256) &&
-           c->chunk == 64 && c->sparse_budget <= 1024;
+           c->chunk == 64 && c->sparse_budget <= fast::ATTEND_MAXLAM;
 }
 
 // shapes of the MFMA state-evolution kernel with run-time window and sparse budget (multiples of 64; it ranks by
@@ -212,7 +210,7 @@ bool wide_scan_ok(const lola_config *c) {
     // (the compile-time shapes keep their own state-evolution kernel for the self-recall error; with the
     // query-dependent scores, which are given to the selection instead of being computed by it, they come here too)
     // (sparse budget 0: no selection, every leaving pair is folded; at window 64 the row-split kernel is faster)
-    return wide_output_ok(c) && (!fast_output_ok(c) || (c->score_kind != LOLA_SCORE_SRE && c->sparse_budget > 0)) &&
+    return mfma_output_ok(c) && (!fast_shape(c) || (c->score_kind != LOLA_SCORE_SRE && c->sparse_budget > 0)) &&
            c->sparse_budget % 64 == 0 && c->window >= 64 && c->window % 64 == 0;
 }
 
@@ -551,9 +549,7 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
     const size_t scan_fixed = scan_fixed_floats(a.dm);
     a.R = score_tile_rows(a.dm, scan_fixed);
     a.QT = attend_tile_queries(a.dm);
-    const bool fast_att = a.want_out && fast_output_ok(c);
-    const bool wide_att = a.want_out && !fast_att && wide_output_ok(c);
-    a.snap_split = (fast_att || wide_att) ? 1 : 0;
+    a.snap_split = a.want_out && mfma_output_ok(c) ? 1 : 0;
     // The MFMA evolution kernels do every scored chunk, a ragged last one included; what comes before the first of them has
     // a closed form (generic_kernels.h, first_scored_chunk).
     a.fill_closed = std::is_same<T, bf16_t>::value && (wide_scan_ok(c) || (fast_attend_ok(c) && lam > 0)) ? 1 : 0;
@@ -773,13 +769,7 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
         if (a.want_out) {
             bool done = false;
             if constexpr (std::is_same<T, bf16_t>::value) {
-                if (fast_att) {   // the generic evolution took the snapshots in the MFMA output kernel's layout
-                    launch_output_kernel(c, a, a.j0, a.j1, stream);
-                    done = true;
-                }
-            }
-            if constexpr (std::is_same<T, bf16_t>::value) {
-                if (!done && wide_att) {   // any window / budget, 128 or 256 features: the run-time form of the MFMA output kernel
+                if (a.snap_split) {   // the generic evolution took the snapshots in the MFMA output kernel's layout
                     launch_output_kernel(c, a, a.j0, a.j1, stream);
                     done = true;
                 }
@@ -985,7 +975,7 @@ const char *lola_kernel_path(const lola_config *c, int32_t which) {
     if (which == 1 && wide_decode_ok(c)) return "mfma";      // update and outputs on MFMA
     if (which == 1 && wide_step_out_ok(c)) return "mixed";   // outputs on MFMA, update shape-generic
     if (which == 0 && (fast_attend_ok(c) || wide_scan_ok(c))) return "mfma";
-    if (which == 0 && (fast_output_ok(c) || wide_output_ok(c))) return "mixed";
+    if (which == 0 && mfma_output_ok(c)) return "mixed";
     return "generic";
 }
 
