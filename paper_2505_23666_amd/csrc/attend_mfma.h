@@ -103,8 +103,18 @@ __global__ __launch_bounds__((AttendShape<DH, DF, G>::NTHR), 2) void attend_grou
     const size_t qrow0 = ((size_t)b * a.dm.Hq + hq0) * Tn + (size_t)j * 64;
     const bf16_t *Wq = a.Wq + (size_t)hq0 * M * DH;   // [G][M][DH]
     const float scale2 = a.dm.scale * LOG2E;          // logits are kept in units of log2(e)
-    const int NKS = (NKEYS + S::KB - 1) / S::KB;   // (the last one's positions may begin below 0)
     const int wlo = aj < ETA ? -(int)aj : -ETA;      // first window position that holds a token, relative to the chunk
+    // Stages of keys, from the chunk down to the cache (the last one's positions may begin below 0).  In a filling chunk the positions
+    // from the first unused slot to the window's first token are empty: the stages that lie wholly among them, `gap` positions from
+    // pskip + KB down, are passed over.  Read as zeros and masked, as before, they are work for nothing and all fetch the same
+    // row: 8 x 32 ungrouped heads with 64 columns, 333 tokens at eta 512 / lambda 1024 412 us a call, 231 without them; 8 sequences of 1000
+    // tokens of the 8B shape there 507 and 267.
+    int NKS = (NKEYS + S::KB - 1) / S::KB, pskip = NKEYS, gap = 0;
+    if (filling) {
+        const int used = spc_in + generic::left_after(a, a0, j * 64);
+        const int i0 = (NKEYS - P - wlo + S::KB - 1) / S::KB, nskip = max(0, (used > 0 ? (NKEYS - used) / S::KB : NKS) - i0);
+        NKS -= nskip; gap = nskip * S::KB; pskip = NKEYS - (i0 + 1) * S::KB;
+    }
 
     // Rows of Q, K, V and W_q lie row-major in their slot, their 16-byte pieces XOR-swizzled (a lane of a direct load chooses
     // which piece it fetches) so that neither the operand reads (16 rows, one piece each) nor the transposing reads
@@ -133,8 +143,8 @@ __global__ __launch_bounds__((AttendShape<DH, DF, G>::NTHR), 2) void attend_grou
         r.x = (vr < 0 ? zr : kr) + off; r.y = (vr < 0 ? zr : vv) + off;
         return r;
     };
-    auto issue_keys = [&](unsigned char *slot, int i) {   // (from the chunk down to the cache)
-        const int p0 = NKEYS - (i + 1) * S::KB, tok0 = j * 64 + p0 - P;   // (call token of the stage's first position, behind the cache)
+    auto issue_keys = [&](unsigned char *slot, int p0) {   // positions p0 ..
+        const int tok0 = j * 64 + p0 - P;   // (call token of the stage's first position, behind the cache)
         const int ln = opaque_lane();
         if (p0 >= 0 && p0 + S::KB <= LAM) {
 #pragma unroll
@@ -211,7 +221,7 @@ __global__ __launch_bounds__((AttendShape<DH, DF, G>::NTHR), 2) void attend_grou
         if (n + 1 < S::NQS) issue_q(slot_of(n + 1), n + 1);
         else {
             if (n == 0) lds_barrier();   // (the addresses are there)
-            issue_keys(slot_of(n + 1), 0);
+            issue_keys(slot_of(n + 1), NKEYS - S::KB);
         }
         if (S::NQS == 1 || n == hl * 64 / S::QROWS) {
             const uint16_t *Ql = reinterpret_cast<const uint16_t *>(slot_of(n));
@@ -229,16 +239,20 @@ __global__ __launch_bounds__((AttendShape<DH, DF, G>::NTHR), 2) void attend_grou
     float mrun = 0.f;
 #pragma unroll
     for (int ct = 0; ct < NCT; ct++) out[ct] = zero_f32x16();
+    int pnext = NKEYS - S::KB;   // first position of the stage that was requested last
 #pragma unroll 1
     for (int n = 0; n < NKS; n++) {
         begin();
         const unsigned char *slot = slot_of(S::NQS + n);
-        if (n + 1 < NKS) issue_keys(slot_of(S::NQS + n + 1), n + 1);
+        const int ps = pnext;
+        pnext -= S::KB;
+        if (pnext == pskip) pnext -= gap;
+        if (n + 1 < NKS) issue_keys(slot_of(S::NQS + n + 1), pnext);
         else issue_w(slot_of(S::NQS + n + 1), 0);
         const uint16_t *Kl = reinterpret_cast<const uint16_t *>(slot), *Vl = Kl + S::SB / 4;
 #pragma unroll
         for (int sub = 0; sub < S::KB / S::KSUB; sub++) {
-            const int p0 = NKEYS - (n + 1) * S::KB + sub * S::KSUB;
+            const int p0 = ps + sub * S::KSUB;
             if (p0 + S::KSUB <= 0) continue;
             f32x16 sc[S::KSUB / 32];
 #pragma unroll

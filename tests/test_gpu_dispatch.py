@@ -343,11 +343,14 @@ def test_shared_evolution_replayed_from_a_graph():
     (1, 2, 1, 128, 128, 64, 128, 330, {}), (1, 1, 2, 64, 128, 1, 3, 129, {}), (1, 1, 3, 128, 256, 28, 100, 257, {}), (2, 1, 4, 128, 256, 54, 10, 193, {}),
     (1, 1, 4, 64, 256, 65, 127, 385, {}), (1, 1, 6, 128, 128, 200, 0, 300, {}), (1, 1, 8, 64, 256, 7, 64, 200, {}), (1, 1, 4, 128, 128, 64, 64, 64, {}),
     (1, 1, 4, 128, 256, 64, 192, 449, dict(query_hide=1)), (1, 1, 4, 64, 128, 64, 64, 321, dict(query_hide=2)), (1, 2, 2, 128, 128, 40, 72, 331, dict(query_hide=3)),
-    (1, 1, 4, 128, 256, 96, 160, 517, dict(phi_kind=1)), (1, 1, 2, 64, 256, 64, 1024, 1300, {})])
+    (1, 1, 4, 128, 256, 96, 160, 517, dict(phi_kind=1)), (1, 1, 2, 64, 256, 64, 1024, 1300, {}),
+    (1, 1, 1, 64, 256, 512, 1024, 333, {}), (2, 1, 4, 128, 256, 128, 512, 577, {}), (1, 2, 2, 128, 128, 320, 192, 449, {}), (1, 1, 2, 64, 128, 192, 0, 130, {}),
+    (1, 1, 1, 128, 128, 64, 1024, 70, {}), (1, 1, 6, 64, 128, 64, 256, 200, dict(query_hide=2))])
 def test_output_kernel_edges(B, Hkv, g, d, D, eta, lam, T, kw):
     """The chunk-parallel output kernel where its stages are ragged: groups of 1, 2, 4 heads and what is left of others, positions
     that begin inside the first stage, caches and windows that end inside one, a last chunk of few queries, restricted queries,
-    a second call that starts inside a chunk.  Against the oracle at the bounds of the other shapes."""
+    stages without a single pair while cache and window fill, a second call that starts inside a chunk.  Against the oracle at
+    the bounds of the other shapes."""
     sh = wl.Shape("edges", "bf16", B, g * Hkv, Hkv, d, D, T=0, eta=eta, lam=lam, C=64, seed=0)
     q, k, v, Wq, Wk = case_inputs(300 + d + D + lam + g, B, g * Hkv, Hkv, d, D, T + 70, wscale=0.5 if kw.get("phi_kind") else 1.0)
     print("edges", B, Hkv, g, d, D, eta, lam, T, kw, flush=True)
