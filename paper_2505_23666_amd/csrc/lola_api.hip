@@ -477,6 +477,9 @@ SideStream *side_stream(hipStream_t caller) {
     return state[dev] == 1 ? &table[dev] : nullptr;
 }
 
+// Query heads per workgroup of the output kernel (by the shape alone: the pieces of a call have the same bits as the whole)
+int output_heads(const lola_config *c, const Dims &dm) { return c->feat_dim == 256 && dm.g % 4 == 0 ? 4 : (dm.g % 2 == 0 ? 2 : 1); }
+
 // outputs of the chunks [r0, r1) by the MFMA output kernel
 void launch_output_kernel(const lola_config *c, const generic::PrefillArgs<bf16_t> &a, int r0, int r1, hipStream_t so) {
     generic::PrefillArgs<bf16_t> ao = a;
@@ -484,7 +487,7 @@ void launch_output_kernel(const lola_config *c, const generic::PrefillArgs<bf16_
     // Heads per workgroup: with 128 features two (two workgroups per compute unit cover each other's waits: 369 us against 401 with
     // four, 16 x 1536 tokens of the 8B shape; 18.9 against 23.4 for one sequence of 384), with 256 four (keys and snapshot read once
     // for the group: 441 against 467 at eta 512 / lambda 1024).
-    const int nch = r1 - r0, G = c->feat_dim == 256 && a.dm.g % 4 == 0 ? 4 : (a.dm.g % 2 == 0 ? 2 : 1);
+    const int nch = r1 - r0, G = output_heads(c, a.dm);
     const bool f32o = c->out_dtype == LOLA_F32;
     // streams (and groups of G query heads) run fastest, so that a stream's chunks meet in one XCD's L2; a dimension of a grid has
     // less than 2^32 threads
@@ -690,16 +693,21 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                 joiner.side = side; joiner.stream = stream;
                 // Piece boundaries: each piece `shrink` times shorter than the one before it, so that the outputs of a piece are
                 // hidden behind the evolution of the next; the last piece, whose outputs nothing hides, is at least one
-                // round of output workgroups on the chip (two per compute unit).  At the compile-time shapes the outputs of a
-                // chunk take about a third of its evolution (4.4 against 12.5 us at 4 sequences of the 8B shape), at the run-time
-                // ones up to half; a piece fewer is a restart of the evolution fewer.
+                // round of output workgroups on the chip (two per compute unit).  A third where the outputs of a chunk take about a
+                // third of its evolution (4.4 against 12.5 us at 4 sequences of the 8B shape): a piece fewer is a restart of the evolution
+                // fewer.  At the compile-time shapes that is up to so many heads x sequences, fewer where groups of odd size do
+                // not share keys; us a call of 3072 tokens at lambda = 128 by halves / by thirds: head_dim 128 618 / 609 (128), 682 / 704 (144),
+                // 635 / 658 (160), 682 / 719 (192); 64 503 / 496 (192), 521 / 522 (224; 4096 tokens at lambda = 64 579 / 607); ungrouped or by three,
+                // head_dim 128 608 / 596 (96), 732 / 756 (112), 774 / 796 (128), 64 476 / 468 (96), 540 / 547 (112), 553 / 574 (128), 530 / 550 (192).
+                // At the run-time shapes halves (4 sequences x 2048 at eta = lambda = 512 795 / 849, 256 791 / 800).
                 int bnd[SideStream::NEV + 1];
                 bnd[0] = j0; bnd[1] = jend;
                 int npieces = 1;
                 if (side) {
                     side_lock.lock();
                     const int per_chunk = a.dm.Hq * a.dm.B;   // output workgroups per chunk
-                    const int shrink = wide || a.dm.Hq * a.dm.B > 192 ? 2 : 3;
+                    const int thirds = output_heads(c, a.dm) == 1 ? 96 : (c->head_dim == 128 ? 128 : 192);
+                    const int shrink = wide || a.dm.Hq * a.dm.B > thirds ? 2 : 3;
                     int last = (2 * CHIP_CUS + per_chunk - 1) / per_chunk;
                     if (last < 2) last = 2;
                     auto units = [&](int n) { int u = 0, x = 1; for (int i = 0; i < n; i++, x *= shrink) u += x; return u; };
