@@ -405,24 +405,27 @@ struct SideStream {
 constexpr int SCAN_RT128 = LOLA_SCAN_RT128;   // row tiles of H^T per wavefront in the MFMA scan at head_dim 128
 constexpr size_t OVERLAP_MAX_STREAMS = 128;   // beyond this many streams the serial evolution fills the chip by itself
 constexpr int OVERLAP_MIN_PIECE = 8;          // chunks per piece on average at least
-constexpr size_t OVERLAP_MIN_WORK = 2048;     // output workgroups (in units of 64 head columns) per piece at least: below
-                                              // this the restart of the evolution costs more than the overlap hides (4 x 2048
-                                              // tokens at eta = lambda = 256 1.04 ms with 4096, 1.00 with 2048 and with 1024)
+constexpr size_t OVERLAP_MIN_WORK = 2048;     // chunks x query heads (x 64 head columns) per piece at least: below this the restart of
+                                              // the evolution costs more than the overlap hides (4 x 2048 tokens at eta = lambda = 256,
+                                              // 256 features 848 us with 4096, 773 with 2048, 767 with 1024; 2 x 2048 at the 1B shape 256,
+                                              // 256 and 279; but 2 x 2048 at the 8B shape 374, 390 and 390)
 constexpr size_t OVERLAP_RESTART_WORK = 4096; // the same for the third piece and on at lambda <= 128 and head_dim 64, where a restart
                                               // recomputes the cached keys' features on four wavefronts: 8 x 2048 tokens at the 1B
-                                              // shape 371 us in two pieces, 379 in four, 8 x 4096 667 and 677; but 4 x 3000 444 in
-                                              // one and 422 in two (at head_dim 128 4 x 2048 tokens 457 in two, 450 in four)
+                                              // shape 334 us, with 2048 342; 8 x 4096 600, with 2048 615 and with 8192 611; but 4 x 3000
+                                              // 414 in one and 405 in two (at head_dim 128 4 x 2048 tokens 416 in two, 417 in four)
 constexpr int SHARE_MAX_WGS = 128;            // evolution workgroups at most where helpers run beside outputs
 constexpr float SHARE_BESIDE = 1.2f;          // a piece beside outputs has helpers while its chain takes longer than this times the outputs:
                                               // they take compute units from the outputs (4 x 2048 tokens, 256 features, eta = lambda =
                                               // 256 852 us without them in the second piece, 794 with; 512 958 and 759;
                                               // with 0.95 the third piece has them too: 772 for 788 at 256, but 809 for 770 at
-                                              // eta 512, lambda 1024)
+                                              // eta 512, lambda 1024; with 1.4 fewer have: 8 x 3072 tokens at 256 with 64 columns 1396
+                                              // for 1275)
 
-// us of the whole chip per output workgroup of 64 queries of one head at the run-time shapes: key blocks of 128 and the rest.  By
-// kernel trace beside the evolution, scaled to the chip: 0.031 (2 blocks, 128 features), 0.063 (5, 256), 0.119 (13, 256) at
-// head_dim 128.
-float output_wg_us(const lola_config *c) {
+// us of the whole chip for the outputs of 64 queries of one head at the run-time shapes: key blocks of 128 and the rest.  By kernel
+// trace beside the evolution, scaled to the chip: 0.031 (2 blocks, 128 features), 0.063 (5, 256), 0.119 (13, 256) at head_dim 128 with
+// two heads and with four per workgroup.  Head_dim 64 and ungrouped heads by proportion, without a trace of their own: there
+// calls of 3072 tokens take the same time within 3 % whatever the factor above from 0.4 to 1.2 (21 and 12 shapes).
+float output_head_us(const lola_config *c) {
     const float blocks = (float)((c->sparse_budget + c->window + 64 + 127) / 128);
     return (float)c->head_dim / 128.f * (0.007f * blocks + (c->feat_dim == 256 ? 0.0273f : 0.0165f));
 }
@@ -477,16 +480,19 @@ SideStream *side_stream(hipStream_t caller) {
     return state[dev] == 1 ? &table[dev] : nullptr;
 }
 
-// Query heads per workgroup of the output kernel (by the shape alone: the pieces of a call have the same bits as the whole)
+// Query heads per workgroup of the output kernel: with 128 features two (two workgroups per compute unit cover each other's waits:
+// 369 us against 401 with four, 16 x 1536 tokens of the 8B shape; 18.9 against 23.4 for one sequence of 384; us a call with two and with
+// one, whose keys nobody shares: 16 x 1024 tokens of the 1B shape 275 and 318, 8 x 1024 of the 8B shape 293 and 301, the same where a
+// launch has few workgroups), with 256 four (keys and snapshot read once for the group: 441 against 467 at eta 512 / lambda 1024; 8 x
+// 1024 tokens at eta = lambda = 256 474 us a call, with two 488, with one 506).  By the shape alone, so that the pieces of a call have
+// the same bits as the whole, although two are faster than four where the workgroups have a compute unit each (1 x 512 tokens
+// there 69 against 75).
 int output_heads(const lola_config *c, const Dims &dm) { return c->feat_dim == 256 && dm.g % 4 == 0 ? 4 : (dm.g % 2 == 0 ? 2 : 1); }
 
 // outputs of the chunks [r0, r1) by the MFMA output kernel
 void launch_output_kernel(const lola_config *c, const generic::PrefillArgs<bf16_t> &a, int r0, int r1, hipStream_t so) {
     generic::PrefillArgs<bf16_t> ao = a;
     ao.j0 = r0; ao.j1 = r1; ao.scan_mode = 0;
-    // Heads per workgroup: with 128 features two (two workgroups per compute unit cover each other's waits: 369 us against 401 with
-    // four, 16 x 1536 tokens of the 8B shape; 18.9 against 23.4 for one sequence of 384), with 256 four (keys and snapshot read once
-    // for the group: 441 against 467 at eta 512 / lambda 1024).
     const int nch = r1 - r0, G = output_heads(c, a.dm);
     const bool f32o = c->out_dtype == LOLA_F32;
     // streams (and groups of G query heads) run fastest, so that a stream's chunks meet in one XCD's L2; a dimension of a grid has
@@ -692,8 +698,11 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                 } joiner;
                 joiner.side = side; joiner.stream = stream;
                 // Piece boundaries: each piece `shrink` times shorter than the one before it, so that the outputs of a piece are
-                // hidden behind the evolution of the next; the last piece, whose outputs nothing hides, is at least one
-                // round of output workgroups on the chip (two per compute unit).  A third where the outputs of a chunk take about a
+                // hidden behind the evolution of the next; the last piece, whose outputs nothing hides, is at least half a round
+                // of the output kernel, 512 heads x chunks of the 1024 that the compute units hold at a time (two wavefronts each): a
+                // whole round is faster by 0.5 - 1.6 % at some compile-time shapes (4 x 4096 tokens of the 8B shape 809 us for 816), slower by 2 -
+                // 3 % at others (5 x 3072 at lambda = 256 861 for 837) and by more at the run-time ones (4 x 2048 at eta = lambda =
+                // 256 859 for 791, 512 954 for 795).  A third where the outputs of a chunk take about a
                 // third of its evolution (4.4 against 12.5 us at 4 sequences of the 8B shape): a piece fewer is a restart of the evolution
                 // fewer.  At the compile-time shapes that is up to so many heads x sequences, fewer where groups of odd size do
                 // not share keys; us a call of 3072 tokens at lambda = 128 by halves / by thirds: head_dim 128 618 / 609 (128), 682 / 704 (144),
@@ -705,7 +714,7 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                 int npieces = 1;
                 if (side) {
                     side_lock.lock();
-                    const int per_chunk = a.dm.Hq * a.dm.B;   // output workgroups per chunk
+                    const int per_chunk = a.dm.Hq * a.dm.B;   // heads of outputs per chunk
                     const int thirds = output_heads(c, a.dm) == 1 ? 96 : (c->head_dim == 128 ? 128 : 192);
                     const int shrink = wide || a.dm.Hq * a.dm.B > thirds ? 2 : 3;
                     int last = (2 * CHIP_CUS + per_chunk - 1) / per_chunk;
@@ -738,7 +747,7 @@ lola_status run_prefill(const lola_config *c, const lola_state *st, const void *
                     // What runs beside this piece: the outputs from the piece before it on, on the compute units that the evolution
                     // leaves.  While they take longer than the chain from here on, a helper's compute unit is theirs (the chain
                     // as if every chunk were scored; the kernel, which knows, looks again).
-                    a.beside_us = side && ip > 0 ? SHARE_BESIDE * output_wg_us(c) * (float)(jend - prev0) * a.dm.Hq * a.dm.B * CHIP_CUS / (float)(CHIP_CUS - (int)ns) : 0.f;
+                    a.beside_us = side && ip > 0 ? SHARE_BESIDE * output_head_us(c) * (float)(jend - prev0) * a.dm.Hq * a.dm.B * CHIP_CUS / (float)(CHIP_CUS - (int)ns) : 0.f;
                     const int nhelp = a.beside_us > 0.f ? (a.chunk_us * (float)(jend - p0) > a.beside_us ? helpers : 0) : alone;
                     if (wide) {
 #define LOLA_WSCAN(DHV, DFV) do { if (side && ip > 0 && hipEventRecord(side->fork[ip - 1], stream) != hipSuccess) return LOLA_ERR_HIP; \
